@@ -37,11 +37,13 @@ enum SweepPath { PATH_FUSED = 0, PATH_DIRECT = 1, PATH_GATHER = 3, PATH_TOEPLITZ
 struct SweepConfig {
     int path = PATH_DIRECT;
     int P = 2;
-    int G = 1;       // node groups per tile (fused path)
+    int G = 1;       // node groups per tile (fused path), or blocks per tile
     size_t lds = 0;  // dynamic LDS bytes; 0 marks a fused shape that does not fit
+    int W = 4;       // wavefronts along the points of a tile (fused path)
 };
 
 constexpr int kMaxP = 4;
+constexpr int kMinTile = 64;  // smallest tile of any kernel shape (the tile maps are sized for it)
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -59,10 +61,12 @@ struct Instance {
     bsde::GaussBand band[bsde::kMaxOrder + 1];  // per layer j (exact)
     int toep_off[bsde::kMaxOrder + 1] = {};       // band j in the device table
     const double *toep_w = nullptr;
+    const bsde::NodeRecB *d_recb = nullptr;
+    int2 *d_addr = nullptr;  // fused sweep: node addresses of the bound shape
     int steps;  // layers computed: N - K - n_stop + 1
     bsde::DriverParams drv;
     std::vector<int> m, win_lo, win_hi;
-    std::vector<double> B, C, D, cfy, cfz, cz, cy, cyz, dw;
+    std::vector<double> B, C, D, phi, cfy, cfz, cz, cy, cyz, dw;
     bsde::NodeTable dtab;
     size_t ring_off, fin_off, stat_off;
     int nwaves;  // per-wave statistics slots (P = 1 has the most waves)
@@ -78,7 +82,7 @@ struct Group {
     SweepConfig cfg;
     std::vector<int> members;
     std::vector<int> tile_prefix, spline_prefix;  // members + 1 entries
-    int *d_tile_inst = nullptr;    // grid tile -> instance (sized for P = 1)
+    int *d_tile_inst = nullptr;    // grid tile -> instance (sized for kMinTile)
     int *d_spline_inst = nullptr;  // spline tile -> instance
     int max_steps = 0;
     size_t part_off = 0;  // partial sums in the workspace: Toeplitz splits or direct chunks
@@ -316,7 +320,7 @@ bool build_instance(const bsde_problem &p, Instance &in)
     const int K = in.K, L = p.L;
     in.m.assign(K * L, 0);
     in.B.assign(K * L, 0.0);
-    in.C = in.D = in.cfy = in.cfz = in.cz = in.cyz = in.dw = in.B;
+    in.C = in.D = in.phi = in.cfy = in.cfz = in.cz = in.cyz = in.dw = in.B;
     in.cy.assign(L, 0.0);
     in.win_lo.assign(K + 1, 0);
     in.win_hi.assign(K + 1, 0);
@@ -338,7 +342,7 @@ bool build_instance(const bsde_problem &p, Instance &in)
             const double wl = w[l] * inv_sqrt_pi;
             in.m[k] = m;
             in.dw[k] = dW;
-            in.B[k] = phi;
+            in.B[k] = in.phi[k] = phi;
             in.C[k] = dx26 * (u * u * u - u);
             in.D[k] = dx26 * (phi * phi * phi - phi);
             in.cfy[k] = (j <= p.k_y) ? p.k_y * in.dt * gy[j] * wl : 0.0;
@@ -379,7 +383,7 @@ bool build_instance(const bsde_problem &p, Instance &in)
     // right ghosts cover the overhang of the last tile of any configuration
     in.pad_r = std::max(0, in.m_max) + kBlock * kMaxP + 2 + (in.exact ? 64 : 0);
     in.npad = in.pad_l + in.nx + in.pad_r;
-    in.drv = bsde::DriverParams{p.p[0], p.p[1], p.p[2], p.p[3], p.p[4]};
+    in.drv = bsde::DriverParams{p.p[0], p.p[1], p.p[2], p.p[3], p.p[4], 1.0 / p.p[3]};
     in.nwaves = (in.nx + kBlock - 1) / kBlock * (kBlock / 64);
     return true;
 }
@@ -515,7 +519,7 @@ bsde::Sweep2Args sweep2_args(const Instance2 &in, char *ws, bool stats)
     a.rows = in.d_rows;
     a.nodes = in.d_nodes;
     a.m1 = in.d_m1;
-    a.drv = bsde::DriverParams{in.pb.p[0], in.pb.p[1], in.pb.p[2], in.pb.p[3], in.pb.p[4]};
+    a.drv = bsde::DriverParams{in.pb.p[0], in.pb.p[1], in.pb.p[2], in.pb.p[3], in.pb.p[4], 0.0};
     a.dt = in.dt;
     a.h0 = in.h0;
     a.picard_max = in.pb.picard_max;
@@ -533,43 +537,179 @@ bsde::Sweep2Args sweep2_args(const Instance2 &in, char *ws, bool stats)
     return a;
 }
 
-// The fused kernel with P points per lane and G node groups for every
-// member of a group, or lds = 0 if some member's windows do not fit.
-SweepConfig fused_config(const std::vector<Instance> &all, const std::vector<int> &members,
-                         bool f32, int P, int G, size_t max_lds)
+// Dynamic LDS of one block of the fused sweep (fused.h), in bytes: the
+// layers' windows (the partial sums may reuse them), the spline filter's
+// arrays, the boundary values and the driver's time factors.
+struct FusedLds {
+    int win[bsde::kMaxOrder + 1], d, a, edge, drv, tm, part;
+    size_t total;
+};
+
+FusedLds fused_layout(const Instance &in, int P, int W, int G)
 {
-    SweepConfig c;
-    c.path = PATH_FUSED;
-    c.P = P;
-    c.G = G;
-    const int T = kBlock * P, NT = kBlock * G;
+    FusedLds l{};
+    const int T = 64 * P * W;
+    auto slots = [&](int n) { return P % 2 == 0 ? n + n / P + 1 : n; };
+    size_t off = 0;
+    int w1 = 0;
+    for (int j = 1; j <= in.K; ++j) {
+        const int n = T + in.win_hi[j] - in.win_lo[j] + (in.f32 ? 1 : 3);
+        if (j == 1) w1 = n;
+        l.win[j] = (int)off;
+        off += (size_t)slots(n) * 16;
+    }
+    // the partial sums: over the windows, or beside them where that is little
+    // (one barrier less)
+    const size_t part = P > 1 || G > 1 ? (size_t)G * T * 16 : 0;
+    l.part = part <= 8192 ? (int)off : 0;
+    off = part <= 8192 ? off + part : std::max(off, part);
+    l.d = (int)off;
+    off += (size_t)(w1 + 2 * bsde::kHalo + 2 + bsde::kFirOver) * 16;
+    l.a = (int)off;
+    off += (size_t)(w1 + 48 + bsde::kFirOver) * 16;
+    l.edge = (int)off;
+    off += (size_t)2 * in.K * 16;
+    l.drv = (int)off;
+    off += in.pb.driver == BSDE_DRIVER_EXP ? align_up((size_t)3 * (in.K + 1) * sizeof(double), 16) : 0;
+    l.tm = (int)off;
+    off += in.f32 ? align_up((size_t)in.K * in.pb.L * sizeof(int), 16) : 0;
+    l.total = off;
+    return l;
+}
+
+// The fused sweep with tiles of 64 P W points and G node groups for every
+// member of a group, or lds = 0 if some member's windows do not fit.
+SweepConfig fused_config(const std::vector<Instance> &all, const std::vector<int> &members, int P, int W,
+                         int G, size_t max_lds)
+{
+    SweepConfig c{PATH_FUSED, P, G, 0, W};
     size_t lds = 0;
     for (int b : members) {
         const Instance &in = all[b];
         // the fused kernel serves the E[z] form of the z equation only
-        if (in.gather || in.exact || in.pb.z_form != BSDE_ZFORM_EZ)
-            return SweepConfig{PATH_FUSED, P, G, 0};
-        int wmax = 0, reach = 0;
-        for (int j = 2; j <= in.K; ++j) {
-            wmax = std::max(wmax, T + in.win_hi[j] - in.win_lo[j] + 1);
-            reach = std::max(reach, in.win_hi[j] - in.win_lo[j] + 1);
+        if (in.gather || in.exact || in.pb.z_form != BSDE_ZFORM_EZ || in.pb.L > 64) return c;
+        // node offsets beyond any window that could fit (and int arithmetic)
+        if ((long)in.m_max - in.m_min > (long)(max_lds / 16)) return c;
+        // FP32 form: wider reaches stay on the direct kernel (its sums, in
+        // another order, are part of the form's results)
+        if (in.f32) {
+            int reach = 0;
+            for (int j = 2; j <= in.K; ++j) reach = std::max(reach, in.win_hi[j] - in.win_lo[j] + 1);
+            if (reach > 320 || in.win_hi[1] - in.win_lo[1] + 1 > 160) return c;
         }
-        const int reach1 = in.win_hi[1] - in.win_lo[1] + 1;
-        const int w1 = T + reach1;
-        const size_t window = bsde::fused_window_lds(P, f32);
-        const size_t need = window + (size_t)in.K * in.pb.L * sizeof(int);
-        const size_t reduce_bytes = (size_t)(G - 1) * kBlock * P * 2 * sizeof(double);
-        const bool fits = reach <= bsde::kMaxReach2 && reach1 <= bsde::kMaxReach1 &&
-                          wmax + bsde::kHalo <= bsde::window_elems(P) &&
-                          w1 + 2 * bsde::kHalo <= bsde::window_elems(P) &&
-                          w1 + 2 * bsde::kHalo + 2 <= bsde::pcr_values(P) &&
-                          w1 + 2 * bsde::kHalo + 2 <= NT * bsde::pcr_slots(P, NT) &&
-                          in.pb.L <= 64 && reduce_bytes <= window && need <= max_lds;
-        if (!fits) return SweepConfig{PATH_FUSED, P, G, 0};
+        // the FP64 form holds a group's node addresses one per lane
+        if (!in.f32 && G < 4 && in.K * in.pb.L > 64 * G) return c;
+        const size_t need = fused_layout(in, P, W, G).total;
+        if (need > max_lds) return c;
         lds = std::max(lds, need);
     }
     c.lds = lds;
     return c;
+}
+
+// Position of node (j, l) in the FP64 fused sweep's tables: by class l mod 8,
+// in a class by layer K, ..., 1, in a layer by l.
+int fused_position(int K, int L, int j, int l)
+{
+    const int c = l & 7;
+    const int per = (L - c + 7) / 8;  // nodes of the class in a layer
+    return K * (c * (L >> 3) + std::min(c, L & 7)) + (K - j) * per + (l >> 3);
+}
+
+// Node addresses for a shape with P points per lane (FusedHot::addr).
+std::vector<int2> fused_addresses(const Instance &in, const FusedLds &lds, int P)
+{
+    const int L = in.pb.L;
+    std::vector<int2> v((size_t)in.K * L);
+    for (int j = 1; j <= in.K; ++j)
+        for (int l = 0; l < L; ++l) {
+            const int m = in.m[(j - 1) * L + l], off = m - in.win_lo[j];
+            const int slot = P % 2 == 0 ? off + off / P : off;
+            const int at = in.f32 ? (j - 1) * L + l : fused_position(in.K, L, j, l);
+            v[at] = make_int2((lds.win[j] + 16 * slot) | (off % P), m * 16 + j);
+        }
+    return v;
+}
+
+struct Shape {
+    int P, W, G;
+};
+// Shapes that the plan and the autotuner choose from: all of them add the
+// nodes in the same order, so they give the same bits.
+constexpr Shape kShapes64[] = {{1, 1, 8}, {2, 1, 8}, {4, 1, 8}, {4, 4, 4}};
+constexpr Shape kShapes32[] = {{1, 2, 1}, {1, 4, 1}, {1, 8, 1}, {1, 16, 1}};
+
+// Estimated time of a step of a group (clock cycles of a CU) with a fused
+// shape, summed over four steps spread over the group's length (the set of
+// active instances shrinks).  256 CUs share the active tiles; a tile costs its
+// node loops (`cn` instructions per node and point, 64 lanes a clock) and its
+// window loads, and every round of co-resident blocks the latency of its
+// first loads, spline, barriers and finish: 7000 cycles measured on small
+// grids, 11000 where a CU holds one block, whose phases nothing overlaps.
+// Measured (FP64 bid-ask, K = 4, L = 16): 262144 points 21.4 ms with 1024-point
+// tiles, 24.1 ms with 256; a batch of 48 instances 10.6 against 9.5 ms; 4000
+// points 1.51 ms with 64-point tiles, 2.2 ms with 256.
+double fused_cost(const std::vector<Instance> &all, const std::vector<int> &members, const SweepConfig &c)
+{
+    const int T = 64 * c.P * c.W, NT = 64 * c.W * c.G;
+    const int res = std::max(1, std::min((int)(163840 / c.lds), 2048 / NT));
+    int longest = 1;
+    for (int b : members) longest = std::max(longest, all[b].steps);
+    double cost = 0.0;
+    for (int k = 0; k < 4; ++k) {
+        double tiles = 0.0, work = 0.0;
+        for (int b : members) {
+            const Instance &in = all[b];
+            if (in.steps <= (long)longest * k / 4) continue;
+            const double t = (in.nx + T - 1) / T;
+            const double cn = in.f32 ? 23.0 : in.pb.driver == BSDE_DRIVER_EXP ? 55.0 : 18.0;
+            double rec = 0.0;
+            for (int j = 1; j <= in.K; ++j) rec += T + in.win_hi[j] - in.win_lo[j];
+            tiles += t;
+            work += t * (T * cn * in.K * in.pb.L / 64.0 + rec * 0.5);
+        }
+        const double per_cu = std::ceil(tiles / 256.0);
+        cost += work / tiles * per_cu + (res == 1 ? 11000.0 : 7000.0) * std::ceil(per_cu / res);
+    }
+    return cost;
+}
+
+// The cheapest fused shape, or lds = 0 if none fits.
+SweepConfig best_fused(const std::vector<Instance> &all, const std::vector<int> &members, bool f32,
+                       size_t max_lds)
+{
+    SweepConfig best{PATH_FUSED, 1, 1, 0, 4};
+    double cost = 0.0;
+    auto consider = [&](const Shape &q) {
+        const SweepConfig c = fused_config(all, members, q.P, q.W, q.G, max_lds);
+        if (!c.lds) return;
+        const double t = fused_cost(all, members, c);
+        if (!best.lds || t < cost) {
+            best = c;
+            cost = t;
+        }
+    };
+    if (f32)
+        for (const Shape &q : kShapes32) consider(q);
+    else
+        for (const Shape &q : kShapes64) consider(q);
+    return best;
+}
+
+// Which of the shapes fit an instance: instances of one group fit the same
+// ones, so that none forces a smaller shape on the others.
+unsigned fitting_shapes(const std::vector<Instance> &all, int b, size_t max_lds)
+{
+    unsigned mask = 0, bit = 1;
+    auto test = [&](const Shape &q) {
+        if (fused_config(all, {b}, q.P, q.W, q.G, max_lds).lds) mask |= bit;
+        bit <<= 1;
+    };
+    if (all[b].f32)
+        for (const Shape &q : kShapes32) test(q);
+    else
+        for (const Shape &q : kShapes64) test(q);
+    return mask;
 }
 
 // Blocks per tile of the direct sweep with one point per lane: enough for
@@ -601,10 +741,10 @@ SweepConfig direct_config(const std::vector<Instance> &all, const std::vector<in
     return c;
 }
 
-// Default shape: the fused kernel with one point per lane (most waves for
-// latency hiding), else the widest tile that fits; the direct kernel when no
-// window fits in LDS.  BSDE_SWEEP = "fused:P:G" or "direct:P" overrides;
-// bsde_autotune replaces the choice by the fastest measured shape.
+// Default shape: the fused kernel in the shape that the cost estimate favours;
+// the direct kernel when no window fits in LDS.  BSDE_SWEEP = "fused:P:G",
+// "fused:P:G:W" or "direct:P:S" overrides; bsde_autotune replaces the choice
+// by the fastest measured shape.
 bool group_gathers(const std::vector<Instance> &all, const std::vector<int> &members)
 {
     for (int b : members)
@@ -649,33 +789,36 @@ SweepConfig default_config(const std::vector<Instance> &all, const Group &g, siz
     if (group_exact(all, g.members)) return toeplitz_config(all, g.members);
     const char *env = std::getenv("BSDE_SWEEP");
     if (env) {
-        int P = 0, G = 1;
-        if (std::sscanf(env, "fused:%d:%d", &P, &G) >= 1 && bsde::fused_supported(P, G)) {
-            SweepConfig c = fused_config(all, g.members, g.f32, P, G, max_lds);
+        int P = 0, G = 1, W = 4;
+        if (std::sscanf(env, "fused:%d:%d:%d", &P, &G, &W) >= 1 &&
+            bsde::fused_supported(P, W, G, g.f32)) {
+            SweepConfig c = fused_config(all, g.members, P, W, G, max_lds);
             if (c.lds) return c;
         }
         int S = 0;
         if (std::sscanf(env, "direct:%d:%d", &P, &S) >= 1 && bsde::direct_p_supported(P))
             return direct_config(all, g.members, g.f32, P, S);
     }
-    const int ps[3] = {1, 2, 4};
-    for (int P : ps) {
-        SweepConfig c = fused_config(all, g.members, g.f32, P, 1, max_lds);
-        if (c.lds) return c;
-    }
+    const SweepConfig cf = best_fused(all, g.members, g.f32, max_lds);
+    if (cf.lds) return cf;
     // the direct kernel: split over blocks on a small grid, else two points per lane
     const SweepConfig c1 = direct_config(all, g.members, g.f32, 1);
     return c1.G > 1 ? c1 : direct_config(all, g.members, g.f32, 2);
 }
 
-int sweep_tiles(const Instance &in, int P) { return (in.nx + kBlock * P - 1) / (kBlock * P); }
+int sweep_tiles(const Instance &in, const SweepConfig &c)
+{
+    const int T = c.path == PATH_FUSED ? 64 * c.P * c.W : kBlock * c.P;
+    return (in.nx + T - 1) / T;
+}
+int tiles_of(const Instance &in, int T) { return (in.nx + T - 1) / T; }
 int spline_tiles(const Instance &in) { return (in.nx + bsde::kSplineTile - 1) / bsde::kSplineTile; }
 
 // Bind a kernel shape to a group: tile numbering, descriptors, LDS limit.
 bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
 {
     if (c.path == PATH_FUSED && c.lds > 65536)
-        HIP_OK(bsde::set_fused_lds_limit(c.P, c.G, g.f32, g.driver, c.lds));
+        HIP_OK(bsde::set_fused_lds_limit(c.P, c.W, c.G, g.f32, g.driver, c.lds));
     if (c.path == PATH_TOEPLITZ && c.lds > 65536) HIP_OK(bsde::set_toeplitz_lds_limit());
     g.cfg = c;
     g.tile_prefix.assign(g.members.size() + 1, 0);
@@ -688,7 +831,41 @@ bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
         d.tile_base = g.tile_prefix[k];
         d.spline_base = g.spline_prefix[k];
         d.spline_tiles = spline_tiles(in);
-        d.a.ntiles = sweep_tiles(in, c.P);
+        d.a.ntiles = sweep_tiles(in, c);
+        d.coef = c.path == PATH_FUSED && !in.f32 ? 1 : 0;
+        if (c.path == PATH_FUSED) {
+            const FusedLds l = fused_layout(in, c.P, c.W, c.G);
+            const std::vector<int2> addr = fused_addresses(in, l, c.P);
+            HIP_OK(hipMemcpy(in.d_addr, addr.data(), addr.size() * sizeof(int2), hipMemcpyHostToDevice));
+            bsde::FusedHot &h = d.hot;
+            h.ring_off = d.ring_off;
+            h.addr = in.d_addr;
+            h.recb = in.d_recb;
+            h.rec32 = d.a.tab.rec32;
+            h.nx = in.nx;
+            h.npad = in.npad;
+            h.pad_l = in.pad_l;
+            h.K = in.K;
+            h.Ky = in.pb.k_y;
+            h.L = in.pb.L;
+            h.n0 = d.n0;
+            h.n0_mod = d.n0 % (in.K + 1);
+            h.mod_magic = (65536 + in.K) / (in.K + 1);
+            h.tile_base = d.tile_base;
+            h.ntiles = d.a.ntiles;
+            for (int j = 0; j <= in.K; ++j) {
+                h.win_lo[j] = in.win_lo[j];
+                h.win_hi[j] = in.win_hi[j];
+                h.lds_win[j] = l.win[j];
+            }
+            h.lds_d = l.d;
+            h.lds_a = l.a;
+            h.lds_edge = l.edge;
+            h.lds_drv = l.drv;
+            h.lds_tm = l.tm;
+            h.m = d.a.tab.m;
+            h.lds_part = l.part;
+        }
         g.tile_prefix[k + 1] = g.tile_prefix[k] + d.a.ntiles;
         g.spline_prefix[k + 1] = g.spline_prefix[k] + d.spline_tiles;
         tmap.insert(tmap.end(), d.a.ntiles, b);
@@ -734,6 +911,7 @@ bsde::StepArgs step_args(const bsde_plan_s &pl, const Group &g, char *ws, int s,
         a.tile_inst = spline_map ? g.d_spline_inst : g.d_tile_inst;
     }
     a.s = s;
+    a.s_mod = s % 420;
     a.stats = stats ? 1 : 0;
     a.part = (g.cfg.path == PATH_TOEPLITZ || g.cfg.path == PATH_DIRECT) && g.cfg.G > 1
                  ? reinterpret_cast<double *>(ws + g.part_off)
@@ -754,7 +932,7 @@ bsde_status enqueue_step(const bsde_plan_s &pl, const Group &g, char *ws, int s,
     const int blocks = g.tile_prefix[act];
     if (tm) HIP_OK(tm->mark(tm->sweep, st));
     if (c.path == PATH_FUSED) {
-        HIP_OK(bsde::launch_sweep_fused(c.P, c.G, g.f32, g.driver, a, blocks, c.lds, st));
+        HIP_OK(bsde::launch_sweep_fused(c.P, c.W, c.G, g.f32, g.driver, a, blocks, c.lds, st));
         if (tm) HIP_OK(tm->mark(tm->sweep, st));
     } else {
         if (c.path == PATH_GATHER)
@@ -795,9 +973,13 @@ bsde_status enqueue_init(const bsde_plan_s &pl, char *ws, const bsde_io *io, hip
     for (const Group &g : pl.groups) {
         int kmax = 0;
         for (int b : g.members) kmax = std::max(kmax, pl.inst[b].K);
-        for (int r = 0; r < kmax; ++r)
-            HIP_OK(bsde::launch_spline(g.f32, step_args(pl, g, ws, r, false, true), 0,
-                                       g.spline_prefix.back(), s));
+        // fused FP64 groups keep a layer's spline by its B-spline coefficients
+        const bool coef = g.cfg.path == PATH_FUSED && !g.f32;
+        for (int r = 0; r < kmax; ++r) {
+            const bsde::StepArgs a = step_args(pl, g, ws, r, false, true);
+            HIP_OK(coef ? bsde::launch_coef(a, g.spline_prefix.back(), s)
+                        : bsde::launch_spline(g.f32, a, 0, g.spline_prefix.back(), s));
+        }
     }
     return BSDE_OK;
 }
@@ -1335,20 +1517,22 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
     // whose windows do not fit a shape does not force it on the others);
     // members by number of steps, most first
     std::vector<SweepConfig> own(batch);
+    std::vector<unsigned> fits(batch, 0);
     for (int b = 0; b < batch; ++b) {
         Instance &in = pl->inst[b];
         Group one;
         one.f32 = in.f32;
         one.members = {b};
         own[b] = default_config(pl->inst, one, pl->max_lds);
+        if (own[b].path == PATH_FUSED) fits[b] = fitting_shapes(pl->inst, b, pl->max_lds);
         int gi = -1;
         for (size_t k = 0; k < pl->groups.size(); ++k) {
             const Group &g = pl->groups[k];
             const SweepConfig &c = own[g.members[0]];
-            // the split count of the Toeplitz and direct sweeps follows the group
+            // the shape of the fused sweep and the split count of the Toeplitz
+            // and direct sweeps follow the group
             if (g.f32 == in.f32 && g.driver == in.pb.driver && c.path == own[b].path &&
-                (c.path == PATH_TOEPLITZ || (c.path == PATH_DIRECT && c.P == own[b].P) ||
-                 (c.P == own[b].P && c.G == own[b].G)))
+                (c.path != PATH_DIRECT || c.P == own[b].P) && fits[g.members[0]] == fits[b])
                 gi = (int)k;
         }
         if (gi < 0) {
@@ -1375,8 +1559,10 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         toff[b] = tbytes;
         const size_t kl = (size_t)in.K * in.pb.L;
         tbytes += align_up(kl * sizeof(int), 256) + align_up(kl * sizeof(bsde::NodeRec), 256) +
-                  align_up(kl * sizeof(bsde::NodeRec32), 256) + align_up(kl * sizeof(double), 256);
+                  align_up(kl * sizeof(bsde::NodeRec32), 256) + align_up(kl * sizeof(double), 256) +
+                  align_up(kl * sizeof(bsde::NodeRecB), 256);
         size_t nbw = 0;
+        tbytes += align_up(kl * sizeof(int2), 256);
         for (int j = 1; j <= in.K; ++j) nbw += 4 * in.band[j].ev.size();
         tbytes += align_up(nbw * sizeof(double), 256);
         tbytes += align_up(in.ctab.size() * sizeof(double), 256);
@@ -1387,7 +1573,7 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
     for (size_t k = 0; k < pl->groups.size(); ++k) {
         size_t tiles = 0, stiles = 0;
         for (int b : pl->groups[k].members) {
-            tiles += sweep_tiles(pl->inst[b], 1);
+            tiles += tiles_of(pl->inst[b], kMinTile);
             stiles += spline_tiles(pl->inst[b]);
         }
         map_off[k] = tbytes;
@@ -1411,6 +1597,7 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         };
         std::vector<bsde::NodeRec> recs(kl);
         std::vector<bsde::NodeRec32> recs32(kl);
+        std::vector<bsde::NodeRecB> recsb(kl);
         for (size_t k = 0; k < kl; ++k) {
             const int l = (int)(k % in.pb.L), j = (int)(k / in.pb.L) + 1;
             const double cy = (j == in.pb.k_y) ? in.cy[l] : 0.0;
@@ -1420,11 +1607,33 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
                                         (float)in.cfy[k], (float)in.cfz[k], (float)in.cz[k],
                                         (float)cy,        (float)in.cyz[k], in.cz[k],
                                         cy,               in.cyz[k],        0.0};
+            // cubic B-spline weights at the fraction; for the linear driver
+            // f = p0 y + p1 z + p3 folded into the weights
+            const double ph = in.phi[k], u = 1.0 - ph;
+            bsde::NodeRecB &rb = recsb[fused_position(in.K, in.pb.L, j, l)];
+            rb.b0 = u * u * u / 6.0;
+            rb.b1 = 2.0 / 3.0 - 0.5 * ph * ph * (2.0 - ph);
+            rb.b2 = 2.0 / 3.0 - 0.5 * u * u * (2.0 - u);
+            rb.b3 = ph * ph * ph / 6.0;
+            if (in.pb.driver == BSDE_DRIVER_LINEAR) {
+                rb.w0 = in.cfy[k] * in.pb.p[0] + cy;
+                rb.w1 = in.cfy[k] * in.pb.p[1];
+                rb.w2 = in.cfz[k] * in.pb.p[0];
+                rb.w3 = in.cfz[k] * in.pb.p[1] + in.cz[k];
+            } else {
+                rb.w0 = in.cfy[k];
+                rb.w1 = in.cfz[k];
+                rb.w2 = in.cz[k];
+                rb.w3 = cy;
+            }
         }
         in.dtab.rec = static_cast<const bsde::NodeRec *>(put(recs.data(), kl * sizeof(bsde::NodeRec)));
         in.dtab.rec32 =
             static_cast<const bsde::NodeRec32 *>(put(recs32.data(), kl * sizeof(bsde::NodeRec32)));
+        in.d_recb =
+            static_cast<const bsde::NodeRecB *>(put(recsb.data(), kl * sizeof(bsde::NodeRecB)));
         in.dtab.m = static_cast<const int *>(put(in.m.data(), kl * sizeof(int)));
+        in.d_addr = static_cast<int2 *>(put(std::vector<int2>(kl).data(), kl * sizeof(int2)));
         in.dtab.dw = static_cast<const double *>(put(in.dw.data(), kl * sizeof(double)));
         std::vector<double> bw;
         for (int j = 1; j <= in.K; ++j) {
@@ -1447,7 +1656,7 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
     for (size_t k = 0; k < pl->groups.size(); ++k) {
         Group &g = pl->groups[k];
         size_t tiles = 0;
-        for (int b : g.members) tiles += sweep_tiles(pl->inst[b], 1);
+        for (int b : g.members) tiles += tiles_of(pl->inst[b], kMinTile);
         g.d_tile_inst = reinterpret_cast<int *>(dev + map_off[k]);
         g.d_spline_inst = reinterpret_cast<int *>(dev + map_off[k] + align_up(tiles * sizeof(int), 256));
     }
@@ -1473,7 +1682,7 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         const int S = toeplitz_splits(pl->inst, g.members);
         if (S == 1) continue;
         size_t tiles = 0;
-        for (int b : g.members) tiles += sweep_tiles(pl->inst[b], 1);
+        for (int b : g.members) tiles += tiles_of(pl->inst[b], kBlock);
         g.part_off = off;
         off += align_up(tiles * S * 2 * bsde::kToepTile * sizeof(double), 256);
     }
@@ -1484,7 +1693,7 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         if (direct_splits(pl->inst, g.members) == 1) continue;
         size_t tiles = 0;
         for (int b : g.members) {
-            tiles += sweep_tiles(pl->inst[b], 1);
+            tiles += tiles_of(pl->inst[b], kBlock);
             g.dchunks = std::max(g.dchunks, bsde::direct_chunks(pl->inst[b].K, pl->inst[b].pb.L));
         }
         g.part_off = off;
@@ -1556,6 +1765,10 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
                 t.cz_wy[j] = (fz * p0 + (j == 1 && ydw ? 1.0 / in.dt : 0.0)) / gz[0];
                 t.cz_wz[j] = fz * p1 / gz[0];
             }
+        }
+        for (size_t k = 0; k < in.cfy.size(); ++k) {
+            d.lin_y += in.cfy[k] * in.pb.p[3];
+            d.lin_z += in.cfz[k] * in.pb.p[3];
         }
         d.ring_off = in.ring_off;
         d.fin_off = in.fin_off;
@@ -1711,12 +1924,14 @@ bsde_status bsde_autotune(bsde_plan_t plan, void *ws, const bsde_io *io, void *s
     int tried = 0;
     for (Group &g : plan->groups) {
         std::vector<SweepConfig> cand;
-        const int ps[3] = {1, 2, 4};
-        for (int P : ps)
-            for (int G = 1; G <= 2; ++G) {
-                SweepConfig c = fused_config(plan->inst, g.members, g.f32, P, G, plan->max_lds);
-                if (c.lds) cand.push_back(c);
-            }
+        auto consider = [&](const Shape &q) {
+            const SweepConfig c = fused_config(plan->inst, g.members, q.P, q.W, q.G, plan->max_lds);
+            if (c.lds) cand.push_back(c);
+        };
+        if (g.f32)
+            for (const Shape &q : kShapes32) consider(q);
+        else
+            for (const Shape &q : kShapes64) consider(q);
         if (group_gathers(plan->inst, g.members)) cand.assign(1, SweepConfig{PATH_GATHER, 1, 1, 0});
         if (group_exact(plan->inst, g.members)) cand.assign(1, toeplitz_config(plan->inst, g.members));
         if (cand.empty()) {

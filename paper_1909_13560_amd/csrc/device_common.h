@@ -15,6 +15,7 @@ constexpr int kPcrRounds = 5;      // PCR strides 1, 2, 4, 8, 16
 constexpr int kHalo = 32;          // > 1 + 2 + 4 + 8 + 16: reach of the truncated PCR
 constexpr int kPcrMaxPerThread = 8;// spline windows of at most kBlock * 8 records
 constexpr int kSplineTile = 512;   // grid points per block of the standalone spline kernel
+constexpr int kSplineSlots = kSplineTile + 2 * kHalo + 24;  // window of a spline tile, with overhang
 
 // Coefficients of one Gauss-Hermite node (j, l), the same for every grid
 // point.  With phi the fraction of the node's cell offset, the spline value
@@ -44,6 +45,15 @@ struct alignas(16) NodeRec32 {
     double cz, cy, cyz, pad;
 };
 
+// Coefficients of a node for layers kept by their B-spline coefficients (the
+// FP64 fused sweep): the value is sum_k b_k c_{p-1+k}.  Weights w: (cfy, cfz,
+// cz, cy) as in NodeRec; for the linear driver f = a y + b z + c its
+// coefficients are folded in, Y += w0 y + w1 z and Z += w2 y + w3 z.
+struct alignas(16) NodeRecB {
+    double b0, b1, b2, b3;
+    double w0, w1, w2, w3;
+};
+
 // Node table of one instance (device memory).  K*L entries, row j-1 holds the
 // L nodes of layer n+j.
 struct NodeTable {
@@ -58,30 +68,7 @@ struct NodeTable {
 constexpr int kMaxOrder = 6;  // largest K of Tables 1-2
 
 constexpr int kMaxNodes = 6 * 64;      // K * L at most
-constexpr int kMaxReach1 = 160;        // widest node reach of layer n+1 in the fused kernel
-constexpr int kMaxReach2 = 320;        // widest node reach of layers n+2.. in the fused kernel
-static_assert(kMaxReach2 >= kMaxReach1 + kHalo, "layer n+1 window must fit the window arrays");
-
-// PCR slots per thread of a fused block of NT threads and P points per lane
-// (the newest layer's window, its halo and the two extra staged values).
-__host__ __device__ constexpr int pcr_slots(int P, int NT)
-{
-    return (kBlock * P + 2 * kHalo + 2 + kMaxReach1 + NT - 1) / NT;
-}
-
-// Fixed LDS window capacity (slots) of the fused kernel with P points per
-// lane: the widest window of any layer plus the spline halo.  Being a
-// compile-time constant, the z array sits at an immediate offset from y.
-// The reach limits are sized so that the fused kernel with one point per
-// lane keeps four 256-thread blocks on a CU (LDS <= 40 KB per block) up to a
-// stability ratio of about 17 at K = 4, L = 16; wider reaches take the
-// direct path.
-__host__ __device__ constexpr int window_elems(int P) { return kBlock * P + kMaxReach2 + kHalo; }
-__host__ __device__ constexpr int window_slots(int P)
-{
-    return (P % 2 == 0) ? window_elems(P) + window_elems(P) / P + 1 : window_elems(P);
-}
-__host__ __device__ constexpr int pcr_values(int P) { return kBlock * P + kMaxReach1 + 2 * kHalo + 2; }
+constexpr int kFirOver = 28;           // entries of the spline filter's arrays past their range
 
 // Slot of window element e in the LDS window arrays.  With an even number P
 // of points per lane a pad slot follows every P elements, so the lanes of a
@@ -96,6 +83,7 @@ struct WinLayout {
 
 struct DriverParams {
     double p0, p1, p2, p3, p4;
+    double inv3;  // 1 / p3
 };
 
 // Coefficients of the truncated parallel cyclic reduction of (1, 4, 1).
@@ -183,12 +171,32 @@ struct SweepArgs {
     unsigned long long *st_nonconv;   // per-wave count of unconverged point-steps
 };
 
+// What a block of the fused sweep needs before its first load, in one piece
+// so that it comes with one round of scalar loads: read where it is used, each
+// value was a scalar-cache miss of its own (a launch starts with cold caches)
+// and the window loads went out 2000 cycles late.
+struct alignas(64) FusedHot {
+    size_t ring_off;
+    const int2 *addr;            // FP64, per node: LDS byte offset of its first record | offset mod P, m << 4 | j
+    const int *m;                // FP32: node offsets
+    const NodeRecB *recb;        // node coefficients (FP64), in processing order
+    const NodeRec32 *rec32;      // and for the FP32 form
+    int nx, npad, pad_l, K;
+    int Ky, L, n0, n0_mod;       // n0 mod (K + 1)
+    int tile_base, ntiles, lds_d, lds_a;
+    int lds_edge, lds_part, lds_drv, lds_tm;
+    int win_lo[kMaxOrder + 1], win_hi[kMaxOrder + 1];
+    int lds_win[kMaxOrder + 1];  // byte offsets in a block's dynamic LDS, as lds_*
+    int mod_magic;               // ceil(2^16 / (K + 1))
+};
+
 // One instance of a (batched) solve as the kernels see it: its SweepArgs
 // with the workspace parts given as byte offsets, bound to the workspace
 // address at launch.  The kernels of one launch serve a group of instances
 // (same precision, driver and tile shape); the grid's tiles are numbered
 // instance after instance.
-struct InstDesc {
+struct alignas(64) InstDesc {
+    FusedHot hot;         // fused sweep
     SweepArgs a;          // ring, fin_*, st_* unset; n unset
     size_t ring_off;      // ring of K+1 slots
     size_t fin_off;       // layer n_stop: n_x doubles of y, then of z
@@ -199,6 +207,8 @@ struct InstDesc {
     int tile_base;        // first tile of the instance in its group's sweep grid
     int spline_base;      // first tile of the instance in its group's spline grid
     int spline_tiles;     // tiles of the standalone spline kernel
+    int coef;             // the ring's second plane holds B-spline coefficients
+    double lin_y, lin_z;  // FP64 fused sweep, linear driver: its constant term's part of Y, Z
     // window bounds of the layers (NodeTable::win_lo/win_hi point here once
     // bound, so they load together with the descriptor)
     int win_lo[kMaxOrder + 1], win_hi[kMaxOrder + 1];
@@ -209,6 +219,7 @@ struct StepArgs {
     const InstDesc *desc;
     const int *tile_inst;  // grid tile -> descriptor index; NULL: every tile is of desc[0]
     int s;                 // step: each instance computes layer n0 - s
+    int s_mod;             // s mod 420 (a multiple of every K + 1)
     int stats;             // bind the statistics slots
     double *part;          // partial sums: Toeplitz sweep split over S blocks per tile, or
                            // the node chunks of a split direct sweep
@@ -244,7 +255,7 @@ template <typename T>
 struct Driver<BSDE_DRIVER_BIDASK, T> {  // -r y - theta z + s (R - r) min(y - z/sigma, 0)
     T mr, mth, c, inv_sg;
     __device__ Driver(const DriverParams &p, double)
-        : mr(-p.p0), mth(-p.p2), c(p.p4 * (p.p1 - p.p0)), inv_sg(1.0 / p.p3) {}
+        : mr(-p.p0), mth(-p.p2), c(p.p4 * (p.p1 - p.p0)), inv_sg(p.inv3) {}
     __device__ T operator()(T y, T z) const
     {
         const T m = fmin(fma(-z, inv_sg, y), T(0));
@@ -263,6 +274,8 @@ struct Driver<BSDE_DRIVER_EXP, T> {  // Example 2: (e^{t^2} - 4ty - 3e^{t^2 - y 
     T t, t2, et, emt;
     __device__ Driver(const DriverParams &, double tt)
         : t(tt), t2(tt * tt), et(exp(tt * tt)), emt(exp(-tt * tt)) {}
+    // from (t, exp(t^2), exp(-t^2)) computed once
+    __device__ explicit Driver(const double *c) : t(c[0]), t2(c[0] * c[0]), et(c[1]), emt(c[2]) {}
     __device__ T operator()(T y, T z) const
     {
         return T(0.5) * (et - T(4) * t * y - T(3) * exp(t2 - y * emt) + z * z * emt);
@@ -355,12 +368,12 @@ __device__ inline double rtilde_global(const Rec &g, int nx, int k, bool zf)
 
 // Window of one layer in LDS.  Element e (slot WinLayout<P>::slot(e)) holds
 // grid point lo - kHalo + e, in the ring's two fragments:
-//   FP64 form: (y, z) in wy[slot], (M_y, M_z) in wy[slot + window_slots(P)].
+//   FP64 form: (y, z) in wy[slot], (M_y, M_z) in wy[slot + kSplineSlots].
 //   FP32 form: (y, z, M_y, M_z) in w[slot].
 template <int P>
 struct WinStore64 {
     double2 *wy;
-    static constexpr int kM = window_slots(P);
+    static constexpr int kM = kSplineSlots;
     __device__ void put(int sl, const double2 &v, const double2 &m) const
     {
         wy[sl] = v;
@@ -702,6 +715,19 @@ __device__ inline NodeRec load_node(const NodeRec *p)
     r.cyz = const_load(&p->cyz);
     return r;
 }
+__device__ inline NodeRecB load_node(const NodeRecB *p)
+{
+    NodeRecB r;
+    r.b0 = const_load(&p->b0);
+    r.b1 = const_load(&p->b1);
+    r.b2 = const_load(&p->b2);
+    r.b3 = const_load(&p->b3);
+    r.w0 = const_load(&p->w0);
+    r.w1 = const_load(&p->w1);
+    r.w2 = const_load(&p->w2);
+    r.w3 = const_load(&p->w3);
+    return r;
+}
 __device__ inline NodeRec32 load_node(const NodeRec32 *p)
 {
     NodeRec32 r;
@@ -843,6 +869,48 @@ __device__ inline void layer_nodes(const Src &src, const typename Prec<F32>::Nod
     }
 }
 
+// The implicit y equation y = Y + h0 f(t_n, y, z) by Picard iteration from y.
+// it, conv: iterations taken, tolerance met.  With a fixed number of
+// iterations (no tolerance) an iterate that repeats the one before it, or the
+// one before that (rounding can leave the iteration alternating between two
+// neighbours), settles every later iterate, so the loop ends there with the
+// value that the last iteration would give.
+template <int DRV>
+__device__ inline double picard_solve(const SweepArgs &a, const Driver<DRV, double> &f0, double y,
+                                      double Yq, double zq, unsigned int &it, bool &conv)
+{
+    it = 0;
+    const unsigned int itmax = (unsigned int)a.picard_max;
+    if (a.picard_tol > 0.0) {
+        conv = false;
+        while (it < itmax) {
+            const double yn = fma(a.h0, f0(y, zq), Yq);
+            ++it;
+            const double dy = fabs(yn - y);
+            y = yn;
+            if (dy <= a.picard_tol * fmax(1.0, fabs(y))) {
+                conv = true;
+                break;
+            }
+        }
+    } else {
+        conv = true;
+        double y2 = y;  // the iterate before y
+        while (it < itmax) {
+            const double yn = fma(a.h0, f0(y, zq), Yq);
+            ++it;
+            if (yn == y || yn == y2) {
+                if (yn == y || ((itmax - it) & 1u) == 0) y = yn;
+                it = itmax;
+                break;
+            }
+            y2 = y;
+            y = yn;
+        }
+    }
+    return y;
+}
+
 // z^n is complete in Z; the implicit y equation y = Y + h0 f(t_n, y, z^n) is
 // solved by Picard iteration (double precision in both forms) from
 // y^{n+1}_i; results go to layer n, and at n = n_stop also to fin_y, fin_z.
@@ -860,23 +928,9 @@ __device__ inline void finish_points(const SweepArgs &a, int first, const Acc<P>
         const bool valid = i < a.nx;
         double y = prev.val(min(i, a.nx - 1)).x;
         const double zq = acc.Z[q], Yq = acc.Y[q];
-        int it = 0;
-        bool conv = true;
-        if (a.picard_tol > 0.0) {
-            conv = false;
-            while (it < a.picard_max) {
-                const double yn = fma(a.h0, f0(y, zq), Yq);
-                ++it;
-                const double dy = fabs(yn - y);
-                y = yn;
-                if (dy <= a.picard_tol * fmax(1.0, fabs(y))) {
-                    conv = true;
-                    break;
-                }
-            }
-        } else {
-            for (; it < a.picard_max; ++it) y = fma(a.h0, f0(y, zq), Yq);
-        }
+        unsigned int it;
+        bool conv;
+        y = picard_solve(a, f0, y, Yq, zq, it, conv);
         if (valid) {
             if constexpr (F32) {
                 // error feedback: residual of y^{n+K_y} (y recurrence) and of
@@ -891,7 +945,7 @@ __device__ inline void finish_points(const SweepArgs &a, int first, const Acc<P>
                 a.fin_y[i] = y;
                 a.fin_z[i] = zq;
             }
-            it_max = max(it_max, (unsigned int)it);
+            it_max = max(it_max, it);
             it_sum += it;
             nonconv += conv ? 0u : 1u;
         }

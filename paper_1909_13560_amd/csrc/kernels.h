@@ -28,13 +28,13 @@ struct GatherChunk {
     double *z0[kChunk];
 };
 
-bool fused_supported(int P, int G);
+bool fused_supported(int P, int WP, int G, bool f32);
 bool direct_p_supported(int P);
-size_t fused_window_lds(int P, bool f32);  // window + PCR arrays
 
-hipError_t launch_sweep_fused(int P, int G, bool f32, int driver, const StepArgs &a, int blocks,
+// fused sweep: tiles of 64 P WP points, G node groups (fused.h)
+hipError_t launch_sweep_fused(int P, int WP, int G, bool f32, int driver, const StepArgs &a, int blocks,
                               size_t lds, hipStream_t s);
-hipError_t set_fused_lds_limit(int P, int G, bool f32, int driver, size_t lds);
+hipError_t set_fused_lds_limit(int P, int WP, int G, bool f32, int driver, size_t lds);
 hipError_t launch_sweep_direct(int P, bool f32, int driver, const StepArgs &a, int blocks,
                                size_t lds, hipStream_t s);
 // state-dependent forward coefficients: one point per lane, nodes located per point
@@ -49,6 +49,8 @@ hipError_t launch_sweep_toeplitz(const StepArgs &a, int tiles, int S, hipStream_
 hipError_t set_toeplitz_lds_limit();
 // mode 0: initial layer s of every instance; mode 1: layer n0 - s (direct path)
 hipError_t launch_spline(bool f32, const StepArgs &a, int mode, int blocks, hipStream_t s);
+// B-spline coefficients of initial layer s of every instance (FP64 fused groups)
+hipError_t launch_coef(const StepArgs &a, int blocks, hipStream_t s);
 hipError_t launch_scatter(const ScatterChunk &c, char *ws, const InstDesc *desc, int blocks_x,
                           hipStream_t s);
 hipError_t launch_gather(const GatherChunk &c, char *ws, const InstDesc *desc, int blocks_x,

@@ -9,65 +9,18 @@
 // layer; instances are sorted by their number of steps, so the active ones
 // are a prefix of the group and the launch covers exactly their tiles.
 //
-// Two sweep kernels compute layer n from layers n+1..n+K:
-//   sweep_fused  a block owns a tile of kBlock*P consecutive grid points.  For
-//                each layer j it stages the records its nodes touch (the tile
-//                widened by the node offsets of layer j) in LDS; for j = 1 it
-//                first solves that layer's natural spline on the window by
-//                truncated PCR and writes the tile's second derivatives back
-//                to HBM, so no separate spline launch is needed.  Each lane
-//                handles P consecutive points.
-//   sweep_direct (node reach too wide for the LDS windows): records are read
-//                straight from HBM/L2, P consecutive points per lane; the
-//                natural spline of the new layer is a separate launch.
+// The sweep kernels that compute layer n from layers n+1..n+K:
+//   sweep_fused  (fused.h) LDS windows of every layer, the spline of layer n+1
+//                built in-kernel: one launch per step.
+//   sweep_direct (windows too wide for LDS): records are read straight from
+//                HBM/L2, P consecutive points per lane; the natural spline of
+//                the new layer is a separate launch.
+//   sweep_gather (state-dependent coefficients): nodes located per point.
 #include "device_common.h"
+#include "fused.h"
 #include "kernels.h"
 
 namespace bsde {
-
-// Node records read from the LDS window (fused kernel).  Window element e of
-// the lane's q-th record is lane_pt + off + q with off = ebase + m >= 0; with
-// the padded layout its slot is
-//   (P+1) tig + off + off/P + q + [q >= P - off % P]   (tig = lane_pt / P),
-// so the per-record offsets are one of P compile-time patterns.  The FP64
-// form reads (y, z) and, window_slots(P) slots further, (M_y, M_z).
-template <int P, int B, bool PAD, int NA, typename V>
-__device__ inline void fetch_slots(const V *w, int base, V (&r)[NA][P + 1])
-{
-    const V *p = w + base;
-#pragma unroll
-    for (int q = 0; q <= P; ++q) {
-        const int sl = q + ((PAD && q >= P - B) ? 1 : 0);
-#pragma unroll
-        for (int k = 0; k < NA; ++k) r[k][q] = p[sl + k * window_slots(P)];
-    }
-}
-
-template <int P, bool F32>
-struct LdsWindow {
-    using V = typename Prec<F32>::V;
-    static constexpr int NA = Prec<F32>::NA;
-    const V *w;
-    int ebase;  // kHalo - (lowest node offset of the layer): off = ebase + m
-    int lane;   // slot of the lane's first element at off = 0: (P+1) tig padded, P tig not
-    template <int PP>
-    __device__ void fetch(int m, V (&r)[NA][PP + 1]) const
-    {
-        static_assert(PP == P, "window layout and fetch width differ");
-        const int off = ebase + m;
-        if constexpr (!WinLayout<P>::kPad) {
-            fetch_slots<P, 0, false, NA>(w, lane + off, r);
-        } else {
-            const int base = lane + off + off / P;
-            switch (off % P) {
-            case 0: fetch_slots<P, 0, true, NA>(w, base, r); break;
-            case 1: fetch_slots<P, 1, true, NA>(w, base, r); break;
-            case 2: fetch_slots<P, (P > 2 ? 2 : 1), true, NA>(w, base, r); break;
-            default: fetch_slots<P, (P > 3 ? 3 : 1), true, NA>(w, base, r); break;
-            }
-        }
-    }
-};
 
 // Node records read straight from the layer in HBM (direct kernel).
 template <bool F32>
@@ -92,11 +45,7 @@ struct GlobalWindow {
     }
 };
 
-// YW: the kernel serves the E[y^{n+1} dW]/dt form of the z equation too (the
-// direct kernel).  The fused kernel leaves it out: its two extra node-loop
-// variants cost the kernel scalar registers (more spills) for a form that the
-// plan sends to the direct kernel.
-template <int P, int DRV, bool F32, bool YW, typename Src>
+template <int P, int DRV, bool F32, typename Src>
 __device__ inline void layer_dispatch(const Src &src, const int *tm, int j, int l0, int LS,
                                       const SweepArgs &a, Acc<P> &acc, int lend)
 // nodes l = l0, l0 + LS, ... < lend of layer j
@@ -106,211 +55,17 @@ __device__ inline void layer_dispatch(const Src &src, const int *tm, int j, int 
     const int row = (j - 1) * a.L;
     const Node *nodes = node_recs(a.tab, static_cast<Node *>(nullptr)) + row;
     const bool last_y = j == a.Ky;
-    if constexpr (YW) {
-        if (j == 1 && a.zform) {
-            if (last_y)
-                layer_nodes<P, DRV, kNodeLastY | kNodeYW, F32>(src, nodes, tm + row, l0, LS, lend,
-                                                               f, acc);
-            else
-                layer_nodes<P, DRV, kNodeYW, F32>(src, nodes, tm + row, l0, LS, lend, f, acc);
-            return;
-        }
+    if (j == 1 && a.zform) {
+        if (last_y)
+            layer_nodes<P, DRV, kNodeLastY | kNodeYW, F32>(src, nodes, tm + row, l0, LS, lend, f, acc);
+        else
+            layer_nodes<P, DRV, kNodeYW, F32>(src, nodes, tm + row, l0, LS, lend, f, acc);
+        return;
     }
     if (last_y)
         layer_nodes<P, DRV, kNodeLastY, F32>(src, nodes, tm + row, l0, LS, lend, f, acc);
     else
         layer_nodes<P, DRV, 0, F32>(src, nodes, tm + row, l0, LS, lend, f, acc);
-}
-
-// LDS bytes of the window arrays of the fused kernel.
-template <bool F32>
-__host__ __device__ constexpr size_t window_lds_bytes(int P)
-{
-    return (size_t)window_slots(P) * (F32 ? sizeof(float4) : 2 * sizeof(double2));
-}
-
-// ---------------------------------------------------------------------------
-// Fused sweep of one tile: LDS-staged windows, in-kernel spline of layer n+1.
-// A block of G*kBlock threads owns a tile of kBlock*P points; thread group g
-// (kBlock threads) takes the nodes l = g, g+G, ... of every layer, and the G
-// partial sums meet in LDS before group 0 finishes the points.
-// Dynamic LDS: the window arrays, the four PCR arrays (pcr_values(P)
-// doubles each) and the node offsets (K*L int).
-// ---------------------------------------------------------------------------
-// Wave priority of a node loop with `left` more node loops to go in this
-// block: a block that is behind gets the higher priority (up to 3), so the
-// blocks sharing a CU, which start together, also end close together (the
-// launch ends with its last block).
-__device__ inline void node_loop_priority(int left)
-{
-    switch (left) {
-    case 0: __builtin_amdgcn_s_setprio(0); break;
-    case 1: __builtin_amdgcn_s_setprio(1); break;
-    case 2: __builtin_amdgcn_s_setprio(2); break;
-    default: __builtin_amdgcn_s_setprio(3); break;
-    }
-}
-
-template <int P, int G, int DRV, bool F32>
-__device__ inline void fused_tile(const SweepArgs &a, int tile, char *smem)
-{
-    using PR = Prec<F32>;
-    using E = typename PR::E;
-    using V = typename PR::V;
-    constexpr int T = kBlock * P;
-    constexpr int NT = kBlock * G;
-    constexpr int CAP1 = pcr_values(P);
-    V *wbase = reinterpret_cast<V *>(smem);
-    const typename PR::template Win<P> win{wbase};
-    double *R = reinterpret_cast<double *>(smem + window_lds_bytes<F32>(P));
-    int *tm = reinterpret_cast<int *>(R + 4 * CAP1);
-
-    const int tid = threadIdx.x;
-    // kBlock is a multiple of the wavefront size: the group is wave-uniform
-    const int grp = __builtin_amdgcn_readfirstlane(tid / kBlock);
-    const int lane_pt = (tid % kBlock) * P;
-    const int t0 = tile * T;
-
-    Acc<P> acc;
-#pragma unroll
-    for (int q = 0; q < P; ++q) acc.Y[q] = acc.Z[q] = 0.0;
-
-    // Layers are processed in the order 2, 3, ..., K, 1, rotated per tile: the
-    // records of layers n+2.. are complete (their splines were built by
-    // earlier launches) and their windows are prefetched into registers one
-    // layer ahead, while the raw values of layer n+1 (written by the previous
-    // launch) are loaded at the start and turned into its spline at its turn.
-    // The rotation key (tile / 32) differs between the blocks that share a CU
-    // (tiles 32 apart under the XCD-aware numbering), so their spline and
-    // node phases fall at different times; it depends on the tile alone, so a
-    // tile computes the same in a batch as on its own.
-    constexpr int kPre = (T + kMaxReach2 + NT - 1) / NT;
-    constexpr int kRaw = pcr_slots(P, NT);
-    using FT = typename Slot<F32>::T;
-    struct Frag {  // plain scalars, so that the array lives in registers
-        FT y, z, My, Mz;
-    } pre[kPre];   // the next window, both fragments
-    auto prefetch = [&](int j) {
-        const Slot<F32> g = ring_slot<F32>(a, a.n + j);
-        const int lo = t0 + a.tab.win_lo[j];
-        const int W = T + (a.tab.win_hi[j] - a.tab.win_lo[j]) + 1;
-#pragma unroll
-        for (int u = 0; u < kPre; ++u) {
-            const int e = tid + u * NT;
-            if (e < W) {
-                const E v = g.val(lo + e), m = g.der(lo + e);
-                pre[u] = Frag{v.x, v.y, m.x, m.y};
-            }
-        }
-    };
-    const int rot = ((tile >> 5) & 3) % a.K;
-    // Issue priority: everything but the node loops (staging waits, the
-    // spline's barriers, Picard) runs at the highest wave priority, so a
-    // block's latency-bound phases go ahead of the node loops of the blocks
-    // sharing its CU instead of queueing behind them; the node loops
-    // (throughput work) run lower, the lower the further the block has got
-    // (node_loop_priority).
-    __builtin_amdgcn_s_setprio(3);
-    auto layer_at = [&](int jj) {  // the jj-th layer of this tile's order
-        const int q = (jj + rot) % a.K;
-        return q + 1 < a.K ? q + 2 : 1;
-    };
-    auto next_window = [&](int jj) {  // first layer after position jj other than n+1
-        for (int q = jj + 1; q < a.K; ++q)
-            if (layer_at(q) != 1) return layer_at(q);
-        return 0;
-    };
-    SplineRaw<kRaw, typename PR::Raw> raw1;
-    {
-        const Slot<F32> g1 = ring_slot<F32>(a, a.n + 1);
-        const int W1 = T + (a.tab.win_hi[1] - a.tab.win_lo[1]) + 1;
-        const int j0 = layer_at(0) != 1 ? layer_at(0) : next_window(0);
-        if (j0) prefetch(j0);
-        spline_load<NT, kRaw>(g1, a.nx, t0 + a.tab.win_lo[1], W1, raw1);
-    }
-    // node offsets into LDS only now: their stores wait for the loads, which
-    // must not hold back the issue of the window loads above (published by
-    // the first barrier)
-    for (int i = tid; i < a.K * a.L; i += NT) tm[i] = a.tab.m[i];
-
-    for (int jj = 0; jj < a.K; ++jj) {
-        const int j = layer_at(jj);
-        const Slot<F32> g = ring_slot<F32>(a, a.n + j);
-        const int mlo = a.tab.win_lo[j], mhi = a.tab.win_hi[j];
-        const int W = T + (mhi - mlo) + 1;
-        const int lo = t0 + mlo;
-        if (j == 1) {
-            // spline of layer n+1 on the window; the tile's part goes back to
-            // HBM for the later steps, with the ghost records
-            spline_window<NT, kRaw, P>(g, a.nx, lo, W, win, R, CAP1, a.pcr, raw1);
-            const int kend = min(t0 + T, a.nx);
-            for (int k = t0 + tid; k < kend; k += NT) {
-                const double2 d = win.ders(WinLayout<P>::slot(k - lo + kHalo));
-                g.set_der(k, d.x, d.y);
-            }
-            if (tile == 0) {
-                const auto e0 = g.val(0);
-                for (int k = tid; k < a.pad_l; k += NT) {
-                    g.set_val(k - a.pad_l, e0);
-                    g.set_der(k - a.pad_l, 0.0, 0.0);
-                }
-            }
-            if (tile == a.ntiles - 1) {
-                const auto e1 = g.val(a.nx - 1);
-                for (int k = tid; k < a.pad_r; k += NT) {
-                    g.set_val(a.nx + k, e1);
-                    g.set_der(a.nx + k, 0.0, 0.0);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < kPre; ++u) {
-                const int e = tid + u * NT;
-                if (e < W)
-                    win.put(WinLayout<P>::slot(kHalo + e), E{pre[u].y, pre[u].z},
-                            E{pre[u].My, pre[u].Mz});
-            }
-            const int jn = next_window(jj);
-            if (jn) prefetch(jn);
-            __syncthreads();
-        }
-        const LdsWindow<P, F32> src{wbase, kHalo - mlo,
-                                    WinLayout<P>::kPad ? lane_pt + lane_pt / P : lane_pt};
-        node_loop_priority(a.K - 1 - jj);
-        layer_dispatch<P, DRV, F32, false>(src, tm, j, grp, G, a, acc, a.L);
-        __builtin_amdgcn_s_setprio(3);
-        __syncthreads();  // the window is reused by the next layer
-    }
-    if (G > 1) {  // partial sums of groups 1..G-1 meet group 0 in LDS, in group order
-        double *red = reinterpret_cast<double *>(smem);
-        if (grp > 0) {
-#pragma unroll
-            for (int q = 0; q < P; ++q) {
-                red[(((grp - 1) * kBlock + tid % kBlock) * P + q) * 2] = acc.Y[q];
-                red[(((grp - 1) * kBlock + tid % kBlock) * P + q) * 2 + 1] = acc.Z[q];
-            }
-        }
-        __syncthreads();
-        if (grp > 0) return;
-        for (int h = 1; h < G; ++h) {
-#pragma unroll
-            for (int q = 0; q < P; ++q) {
-                acc.Y[q] += red[(((h - 1) * kBlock + tid) * P + q) * 2];
-                acc.Z[q] += red[(((h - 1) * kBlock + tid) * P + q) * 2 + 1];
-            }
-        }
-    }
-    finish_points<P, DRV, F32>(a, t0 + lane_pt, acc, (tile * kBlock + tid) >> 6);
-}
-
-template <int P, int G, int DRV, bool F32>
-__global__ void __launch_bounds__(kBlock * G) sweep_fused(const StepArgs s)
-{
-    extern __shared__ double2 smem_fused[];
-    const int idx = xcd_tile(blockIdx.x, gridDim.x);
-    const InstDesc &d = block_desc(s, idx);
-    const SweepArgs a = bind_instance(d, s.ws, s.s, s.stats != 0);
-    fused_tile<P, G, DRV, F32>(a, idx - d.tile_base, reinterpret_cast<char *>(smem_fused));
 }
 
 // ---------------------------------------------------------------------------
@@ -346,7 +101,7 @@ __global__ void __launch_bounds__(kBlock) sweep_direct(const StepArgs s)
             Acc<P> ch;
 #pragma unroll
             for (int q = 0; q < P; ++q) ch.Y[q] = ch.Z[q] = 0.0;
-            layer_dispatch<P, DRV, F32, true>(src, tm, j, h * kDirectChunk, 1, a, ch,
+            layer_dispatch<P, DRV, F32>(src, tm, j, h * kDirectChunk, 1, a, ch,
                                               min(a.L, (h + 1) * kDirectChunk));
             if constexpr (SPLIT) {
                 double *p = s.part + ((size_t)tg * s.dchunks + c) * 2 * kBlock;
@@ -482,8 +237,8 @@ __global__ void __launch_bounds__(kBlock) spline_layer(const StepArgs s, int mod
 {
     using V = typename Prec<F32>::V;
     constexpr int WE = kSplineTile + 2 * kHalo, WS = WE + 2;
-    static_assert(WE <= window_slots(1), "spline tile exceeds the window layout");
-    __shared__ V wsm[window_lds_bytes<F32>(1) / sizeof(V)];
+    static_assert(WE <= kSplineSlots, "spline tile exceeds the window layout");
+    __shared__ V wsm[(F32 ? 1 : 2) * kSplineSlots];
     __shared__ double R[4 * WS];
     const int idx = xcd_tile(blockIdx.x, gridDim.x);
     const InstDesc &d = block_desc(s, idx);
@@ -657,11 +412,26 @@ reduce_stats(char *ws, const InstDesc *desc, unsigned long long *totals)
 // ---------------------------------------------------------------------------
 namespace {
 
-template <int P, int G, int DRV, bool F32>
-hipError_t launch_fused_t(const StepArgs &a, int blocks, size_t lds, hipStream_t s)
+// One shape of the fused sweep: allow its dynamic LDS, or launch it.
+template <int P, int WP, int G, int DRV, bool F32>
+hipError_t fused_t(const StepArgs *a, int blocks, size_t lds, hipStream_t s)
 {
-    hipLaunchKernelGGL((sweep_fused<P, G, DRV, F32>), dim3(blocks), dim3(kBlock * G), lds, s, a);
+    if (!a)
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep_fused<P, WP, G, DRV, F32>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL((sweep_fused<P, WP, G, DRV, F32>), dim3(blocks), dim3(64 * WP * G), lds, s, *a);
     return hipGetLastError();
+}
+
+template <int P, int WP, int G, bool F32>
+hipError_t fused_by_driver(int driver, const StepArgs *a, int blocks, size_t lds, hipStream_t s)
+{
+    switch (driver) {
+    case BSDE_DRIVER_LINEAR: return fused_t<P, WP, G, BSDE_DRIVER_LINEAR, F32>(a, blocks, lds, s);
+    case BSDE_DRIVER_BIDASK: return fused_t<P, WP, G, BSDE_DRIVER_BIDASK, F32>(a, blocks, lds, s);
+    case BSDE_DRIVER_CUBIC: return fused_t<P, WP, G, BSDE_DRIVER_CUBIC, F32>(a, blocks, lds, s);
+    default: return fused_t<P, WP, G, BSDE_DRIVER_EXP, F32>(a, blocks, lds, s);
+    }
 }
 
 template <int P, int DRV, bool F32>
@@ -690,13 +460,6 @@ hipError_t launch_gather_t(const StepArgs &a, int blocks, size_t, hipStream_t s)
     return hipGetLastError();
 }
 
-template <int P, int G, int DRV, bool F32>
-hipError_t allow_lds_t(size_t lds)
-{
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep_fused<P, G, DRV, F32>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-}
-
 #define BSDE_BY_DRIVER(F, TP, ...)                                     \
     switch (driver) {                                                  \
     case BSDE_DRIVER_LINEAR: return F<TP, BSDE_DRIVER_LINEAR, F32>(__VA_ARGS__); \
@@ -704,20 +467,6 @@ hipError_t allow_lds_t(size_t lds)
     case BSDE_DRIVER_CUBIC: return F<TP, BSDE_DRIVER_CUBIC, F32>(__VA_ARGS__);   \
     default: return F<TP, BSDE_DRIVER_EXP, F32>(__VA_ARGS__);                    \
     }
-
-template <int P, int G, bool F32>
-hipError_t fused_by_driver(int driver, const StepArgs &a, int blocks, size_t lds, hipStream_t s)
-{
-#define BSDE_PG P, G
-    BSDE_BY_DRIVER(launch_fused_t, BSDE_PG, a, blocks, lds, s)
-}
-
-template <int P, int G, bool F32>
-hipError_t allow_by_driver(int driver, size_t lds)
-{
-    BSDE_BY_DRIVER(allow_lds_t, BSDE_PG, lds)
-#undef BSDE_PG
-}
 
 template <int P, bool F32>
 hipError_t direct_by_driver(int driver, const StepArgs &a, int blocks, size_t lds, hipStream_t s)
@@ -733,37 +482,60 @@ hipError_t gather_by_driver(int driver, const StepArgs &a, int blocks, hipStream
 
 #undef BSDE_BY_DRIVER
 
-#define BSDE_FUSED_CASES(F, ...)                                        \
-    switch (P * 8 + G) {                                                \
-    case 1 * 8 + 1: return F32 ? F<1, 1, true>(__VA_ARGS__) : F<1, 1, false>(__VA_ARGS__); \
-    case 1 * 8 + 2: return F32 ? F<1, 2, true>(__VA_ARGS__) : F<1, 2, false>(__VA_ARGS__); \
-    case 2 * 8 + 1: return F32 ? F<2, 1, true>(__VA_ARGS__) : F<2, 1, false>(__VA_ARGS__); \
-    case 2 * 8 + 2: return F32 ? F<2, 2, true>(__VA_ARGS__) : F<2, 2, false>(__VA_ARGS__); \
-    case 4 * 8 + 1: return F32 ? F<4, 1, true>(__VA_ARGS__) : F<4, 1, false>(__VA_ARGS__); \
-    case 4 * 8 + 2: return F32 ? F<4, 2, true>(__VA_ARGS__) : F<4, 2, false>(__VA_ARGS__); \
-    default: return hipErrorInvalidValue;                               \
+// The shapes built: X(P, WP, G, forms), forms 1 FP64, 2 FP32, 3 both.  The
+// four-wavefront shapes with one or two groups are for requests (BSDE_SWEEP).
+#define BSDE_FUSED_SHAPES(X) \
+    X(1, 4, 1, 3)            \
+    X(1, 4, 2, 3)            \
+    X(2, 4, 1, 3)            \
+    X(2, 4, 2, 3)            \
+    X(4, 4, 1, 3)            \
+    X(4, 4, 2, 3)            \
+    X(1, 1, 8, 1)            \
+    X(2, 1, 8, 1)            \
+    X(4, 1, 8, 1)            \
+    X(4, 4, 4, 1)            \
+    X(1, 2, 1, 2)            \
+    X(1, 8, 1, 2)            \
+    X(1, 16, 1, 2)
+
+// a = NULL: allow the shape's dynamic LDS instead of launching it
+hipError_t fused_shape(int P, int WP, int G, bool f32, int driver, const StepArgs *a, int blocks,
+                       size_t lds, hipStream_t s)
+{
+#define BSDE_SHAPE(p, w, g, forms)                                                   \
+    if (P == p && WP == w && G == g) {                                               \
+        if constexpr ((forms) & 2)                                                   \
+            if (f32) return fused_by_driver<p, w, g, true>(driver, a, blocks, lds, s); \
+        if constexpr ((forms) & 1)                                                   \
+            if (!f32) return fused_by_driver<p, w, g, false>(driver, a, blocks, lds, s); \
     }
+    BSDE_FUSED_SHAPES(BSDE_SHAPE)
+#undef BSDE_SHAPE
+    return hipErrorInvalidValue;
+}
 
 }  // namespace
 
-bool fused_supported(int P, int G) { return (P == 1 || P == 2 || P == 4) && (G == 1 || G == 2); }
+bool fused_supported(int P, int WP, int G, bool f32)
+{
+#define BSDE_SHAPE(p, w, g, forms) \
+    if (P == p && WP == w && G == g && ((forms) & (f32 ? 2 : 1))) return true;
+    BSDE_FUSED_SHAPES(BSDE_SHAPE)
+#undef BSDE_SHAPE
+    return false;
+}
 bool direct_p_supported(int P) { return P == 1 || P == 2 || P == 4; }
 
-size_t fused_window_lds(int P, bool f32)
-{
-    return (f32 ? window_lds_bytes<true>(P) : window_lds_bytes<false>(P)) +
-           (size_t)pcr_values(P) * 4 * sizeof(double);
-}
-
-hipError_t launch_sweep_fused(int P, int G, bool F32, int driver, const StepArgs &a, int blocks,
+hipError_t launch_sweep_fused(int P, int WP, int G, bool F32, int driver, const StepArgs &a, int blocks,
                               size_t lds, hipStream_t s)
 {
-    BSDE_FUSED_CASES(fused_by_driver, driver, a, blocks, lds, s)
+    return fused_shape(P, WP, G, F32, driver, &a, blocks, lds, s);
 }
 
-hipError_t set_fused_lds_limit(int P, int G, bool F32, int driver, size_t lds)
+hipError_t set_fused_lds_limit(int P, int WP, int G, bool F32, int driver, size_t lds)
 {
-    BSDE_FUSED_CASES(allow_by_driver, driver, lds)
+    return fused_shape(P, WP, G, F32, driver, nullptr, 0, lds, nullptr);
 }
 
 hipError_t launch_sweep_direct(int P, bool F32, int driver, const StepArgs &a, int blocks,
@@ -792,6 +564,12 @@ hipError_t launch_spline(bool f32, const StepArgs &a, int mode, int blocks, hipS
         hipLaunchKernelGGL(spline_layer<true>, dim3(blocks), dim3(kBlock), 0, s, a, mode);
     else
         hipLaunchKernelGGL(spline_layer<false>, dim3(blocks), dim3(kBlock), 0, s, a, mode);
+    return hipGetLastError();
+}
+
+hipError_t launch_coef(const StepArgs &a, int blocks, hipStream_t s)
+{
+    hipLaunchKernelGGL(coef_layer, dim3(blocks), dim3(kBlock), 0, s, a);
     return hipGetLastError();
 }
 

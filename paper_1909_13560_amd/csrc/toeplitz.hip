@@ -298,7 +298,7 @@ __device__ inline void spline_window_ends(int nx, int lo, int W, const WinStore6
 __global__ void __launch_bounds__(256) toeplitz_finish(const StepArgs s, int S)
 {
     constexpr int W = kToepTile, WS = W + 2 * kHalo + 2, U = (WS + 255) / 256;
-    __shared__ double2 wsm[2 * window_slots(1)];  // (y, z), then (M_y, M_z): WinStore64<1>
+    __shared__ double2 wsm[2 * kSplineSlots];  // (y, z), then (M_y, M_z): WinStore64<1>
     __shared__ double R[4 * WS];
     const int tg = xcd_tile(blockIdx.x, gridDim.x);
     const InstDesc &d = block_desc(s, tg);
