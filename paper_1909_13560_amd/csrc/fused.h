@@ -263,16 +263,21 @@ __device__ inline void fetch_records(const V *p, int res, V (&r)[NR])
     if constexpr (!WinLayout<P>::kPad) {
         fetch_pattern<P, 0, NR>(p, r);
     } else if constexpr (P == 2) {
-        if (res & 1)
+        // (the comments keep the patterns apart: merged into one, every read
+        // would compute its address and lose its alignment)
+        if (res & 1) {
             fetch_pattern<P, 1, NR>(p, r);
-        else
+            asm volatile("; pattern 1");
+        } else {
             fetch_pattern<P, 0, NR>(p, r);
+            asm volatile("; pattern 0");
+        }
     } else {
         switch (res & 3) {
-        case 0: fetch_pattern<P, 0, NR>(p, r); break;
-        case 1: fetch_pattern<P, 1, NR>(p, r); break;
-        case 2: fetch_pattern<P, 2, NR>(p, r); break;
-        default: fetch_pattern<P, 3, NR>(p, r); break;
+        case 0: fetch_pattern<P, 0, NR>(p, r); asm volatile("; pattern 0"); break;
+        case 1: fetch_pattern<P, 1, NR>(p, r); asm volatile("; pattern 1"); break;
+        case 2: fetch_pattern<P, 2, NR>(p, r); asm volatile("; pattern 2"); break;
+        default: fetch_pattern<P, 3, NR>(p, r); asm volatile("; pattern 3"); break;
         }
     }
 }
