@@ -107,7 +107,19 @@ struct Instance2 {
     bool f32 = false;  // FP32 form: float ring planes with residual planes
     int K, n0, n1, pad0, pad0r, pad1, pad1r, npad0, npad1;
     int win;  // LDS window columns of the sweep kernel
-    size_t plane;
+    // B-spline form (FP64, natural spline): its tables
+    bool bspline = false;
+    int nl = 0, nr = 0, spread = 0;
+    std::vector<bsde::Row2B> rowsb;
+    std::vector<bsde::Node2B> nodesb;
+    std::vector<double4> corr_l, corr_r;
+    const bsde::Row2B *d_rowsb = nullptr;
+    const bsde::Node2B *d_nodesb = nullptr;
+    const double4 *d_corr_l = nullptr, *d_corr_r = nullptr;
+    double lin_y = 0.0, lin_z1 = 0.0, lin_z2 = 0.0;
+    int planes() const { return bspline ? bsde::kPlanes2B : f32 ? 15 : 12; }
+    size_t plane, tmp_off = 0;
+    int reach = 0;  // widest node offset
     double dx0, dx1, dt, h0, R;
     std::vector<bsde::Node2Row> rows;
     std::vector<bsde::Node2> nodes;
@@ -388,6 +400,86 @@ bool build_instance(const bsde_problem &p, Instance &in)
     return true;
 }
 
+// Tables of the two-dimensional B-spline form (sweep2b): node rows, nodes,
+// and the corrections of the columns next to the ends of axis 1 (see sweep2b:
+// node offset m errs by w b_3 at column -1 - m and by w b_0 at column -m, and
+// mirrored at the other end).  a, w: Gauss-Hermite; m, weights as in
+// build_instance2.
+void build_instance2b(const bsde_problem &p, Instance2 &in, const double *a, const double *w,
+                      const double *gy, const double *gz, int m1min, int m1max)
+{
+    const int K = in.K, L = p.L;
+    const double inv_pi = 0.56418958354775628695 * 0.56418958354775628695;
+    auto basis = [](double ph, double *b) {
+        const double u = 1.0 - ph;
+        b[0] = u * u * u / 6.0;
+        b[1] = 2.0 / 3.0 - 0.5 * ph * ph * (2.0 - ph);
+        b[2] = 2.0 / 3.0 - 0.5 * u * u * (2.0 - u);
+        b[3] = ph * ph * ph / 6.0;
+    };
+    in.rowsb.assign((size_t)K * L, bsde::Row2B{});
+    in.nodesb.assign((size_t)K * L * L, bsde::Node2B{});
+    in.nl = std::min(std::max(0, -m1min) + 1, in.n1);
+    in.nr = std::min(std::max(0, m1max) + 2, in.n1);
+    in.corr_l.assign((size_t)K * L * in.nl, make_double4(0, 0, 0, 0));
+    in.corr_r.assign((size_t)K * L * in.nr, make_double4(0, 0, 0, 0));
+    const bool ydw = p.z_form == BSDE_ZFORM_YDW;
+    for (int j = 1; j <= K; ++j) {
+        const double sq = std::sqrt(2.0 * j * in.dt);
+        const double fy = j <= p.k_y ? p.k_y * in.dt * gy[j] : 0.0, fz = j <= p.k_z ? gz[j] / gz[0] : 0.0;
+        const double yw = j == 1 && ydw ? 1.0 / (in.dt * gz[0]) : 0.0;
+        for (int l0 = 0; l0 < L; ++l0) {
+            const size_t ri = (size_t)(j - 1) * L + l0;
+            const double dW0 = sq * a[l0];
+            const double s0 = (p.drift[0] * j * in.dt + p.vol[0][0] * dW0) / in.dx0;
+            bsde::Row2B &r = in.rowsb[ri];
+            r.m0 = in.rows[ri].m0;
+            r.m1lo = in.rows[ri].m1lo;
+            r.m1hi = in.rows[ri].m1hi;
+            in.spread = std::max(in.spread, r.m1hi - r.m1lo);
+            basis(s0 - std::floor(s0), r.b);
+            r.H = fy;
+            r.Gu = fz * dW0;
+            r.Gy = yw * dW0;
+            r.C = ((j == 1 && !ydw ? 1.0 : 0.0) - (j <= p.k_z ? gz[j] : 0.0)) / gz[0];
+            r.ey = j == p.k_y ? 1.0 : 0.0;
+            r.extra = j == p.k_y || (j == 1 && ydw) ? 1 : 0;
+            for (int l1 = 0; l1 < L; ++l1) {
+                const size_t k = ri * L + l1;
+                const double dW1 = sq * a[l1];
+                const double s1 =
+                    (p.drift[1] * j * in.dt + p.vol[1][0] * dW0 + p.vol[1][1] * dW1) / in.dx1;
+                const double wgt = w[l0] * w[l1] * inv_pi;
+                double b[4];
+                basis(s1 - std::floor(s1), b);
+                bsde::Node2B &nd = in.nodesb[k];
+                nd.w0 = wgt * b[0];
+                nd.w1 = wgt * b[1];
+                nd.w2 = wgt * b[2];
+                nd.w3 = wgt * b[3];
+                nd.gu = fz * dW1;  // t carries the quadrature weight
+                nd.gy = yw * dW1;
+                const int m = in.m1[k];
+                auto add = [&](std::vector<double4> &t, int n, int c, double v) {
+                    if (c < 0 || c >= n) return;
+                    double4 &q = t[ri * n + c];
+                    q.x += v;
+                    q.y += v * nd.gu;
+                    q.z += v * nd.gy;
+                };
+                add(in.corr_l, in.nl, -1 - m, nd.w3);
+                add(in.corr_l, in.nl, -m, nd.w0);
+                add(in.corr_r, in.nr, m, nd.w0);      // distance from the last column
+                add(in.corr_r, in.nr, m + 1, nd.w3);
+                const double c3 = p.p[3] * wgt;
+                in.lin_y += fy * c3;
+                in.lin_z1 += fz * dW0 * c3;
+                in.lin_z2 += fz * dW1 * c3;
+            }
+        }
+    }
+}
+
 // Two-dimensional node tables (eq (20)-(21) with tensor Gauss-Hermite nodes):
 // node (l0, l1) of layer n+j sits at x + drift j dt + vol sqrt(2 j dt) (a_l0, a_l1),
 // i.e. s0 = (drift0 j dt + vol00 dW0)/dx0 (vol lower triangular) and
@@ -487,6 +579,20 @@ bsde_status build_instance2(const bsde_problem &p, Instance2 &in)
         }
     }
     in.h0 = p.k_y * in.dt * gy[0];
+    in.bspline = !in.f32 && !bicubic;
+    if (in.bspline) {
+        // one plane element per grid point; the widest node spread and the
+        // columns next to the ends of axis 1 that a node's correction reaches
+        build_instance2b(p, in, a, w, gy, gz, m1min, m1max);
+        in.pad0 = in.pad0r = in.pad1 = in.pad1r = 0;
+        in.npad0 = in.n0;
+        in.npad1 = in.n1;
+        in.plane = (size_t)in.n0 * in.n1;
+        const int tiles = in.n0 * ((in.n1 + bsde::kTile2B - 1) / bsde::kTile2B);
+        in.nwaves = tiles * bsde::kGroups2B;
+        in.reach = std::max({-m0min, m0max + 1, -m1min, m1max + 1});
+        return BSDE_OK;
+    }
     // ghosts: node reach plus the overhang of the last tile (kTile2R rows,
     // kTile2C columns)
     in.pad0 = std::max(0, -m0min) + 1;
@@ -499,6 +605,7 @@ bsde_status build_instance2(const bsde_problem &p, Instance2 &in)
     const int tiles = ((in.n0 + bsde::kTile2R - 1) / bsde::kTile2R) *
                       ((in.n1 + bsde::kTile2C - 1) / bsde::kTile2C);
     in.nwaves = tiles * bsde::kWaves2;
+    in.reach = std::max({in.pad0 - 1, in.pad1 - 1, in.pad0r - bsde::kTile2R - 1});
     return BSDE_OK;
 }
 
@@ -506,6 +613,8 @@ bsde::Sweep2Args sweep2_args(const Instance2 &in, char *ws, bool stats)
 {
     bsde::Sweep2Args a{};
     a.ring = ws + in.ring_off;
+    a.planes = in.planes();
+    a.vstep = in.bspline ? 1 : 4;
     a.plane = in.plane;
     a.n0 = in.n0;
     a.n1 = in.n1;
@@ -527,6 +636,19 @@ bsde::Sweep2Args sweep2_args(const Instance2 &in, char *ws, bool stats)
     a.zform = in.pb.z_form;
     a.interp = in.pb.interp;
     a.half = (in.win + 1) / 2;
+    if (in.bspline) {
+        a.rowsb = in.d_rowsb;
+        a.nodesb = in.d_nodesb;
+        a.corr_l = in.d_corr_l;
+        a.corr_r = in.d_corr_r;
+        a.nl = in.nl;
+        a.nr = in.nr;
+        a.lds_wave = (int)bsde::sweep2b_wave_lds(in.spread);
+        a.lin_y = in.lin_y;
+        a.lin_z1 = in.lin_z1;
+        a.lin_z2 = in.lin_z2;
+        a.tmp = reinterpret_cast<double *>(ws + in.tmp_off);
+    }
     a.fin = reinterpret_cast<double *>(ws + in.fin_off);
     if (stats) {
         unsigned long long *sum = reinterpret_cast<unsigned long long *>(ws + in.stat_off);
@@ -1019,6 +1141,7 @@ bsde_status enqueue_solve2(const bsde_plan_s &pl, char *ws, const bsde_io *io, b
         a.n = N - K;
         // the derivative planes of a layer: tensor spline or finite differences
         auto interp_layer = [&](int slot) {
+            if (in.bspline) return bsde::launch_coef2d(a, slot, s);
             return in.pb.interp == BSDE_INTERP_BICUBIC_FD
                        ? bsde::launch_fd2d(in.f32, a, slot, in.dx0, in.dx1, s)
                        : bsde::launch_spline2d(in.f32, a, slot, f, s);
@@ -1028,7 +1151,7 @@ bsde_status enqueue_solve2(const bsde_plan_s &pl, char *ws, const bsde_io *io, b
         for (int n = N - K; n >= in.pb.n_stop; --n) {
             a.n = n;
             if (tm) HIP_OK(tm->mark(tm->sweep, s));
-            HIP_OK(bsde::launch_sweep2d(in.f32, a, s));
+            HIP_OK(in.bspline ? bsde::launch_sweep2b(a, s) : bsde::launch_sweep2d(in.f32, a, s));
             if (tm) HIP_OK(tm->mark(tm->sweep, s));
             if (n > in.pb.n_stop) {
                 if (tm) HIP_OK(tm->mark(tm->spline, s));
@@ -1271,7 +1394,11 @@ bsde_status plan_2d(const bsde_problem *pb, int batch, bsde_plan_t *out)
         toff[b] = tbytes;
         tbytes += align_up(in.rows.size() * sizeof(bsde::Node2Row), 256) +
                   align_up(in.nodes.size() * sizeof(bsde::Node2), 256) +
-                  align_up(in.m1.size() * sizeof(int), 256);
+                  align_up(in.m1.size() * sizeof(int), 256) +
+                  align_up(in.rowsb.size() * sizeof(bsde::Row2B), 256) +
+                  align_up(in.nodesb.size() * sizeof(bsde::Node2B), 256) +
+                  align_up(in.corr_l.size() * sizeof(double4), 256) +
+                  align_up(in.corr_r.size() * sizeof(double4), 256);
     }
     const size_t desc_off = tbytes;
     tbytes += align_up((size_t)batch * sizeof(bsde::InstDesc), 256);
@@ -1295,15 +1422,34 @@ bsde_status plan_2d(const bsde_problem *pb, int batch, bsde_plan_t *out)
         in.d_nodes =
             static_cast<const bsde::Node2 *>(put(in.nodes.data(), in.nodes.size() * sizeof(bsde::Node2)));
         in.d_m1 = static_cast<const int *>(put(in.m1.data(), in.m1.size() * sizeof(int)));
+        if (in.bspline) {
+            in.d_rowsb = static_cast<const bsde::Row2B *>(
+                put(in.rowsb.data(), in.rowsb.size() * sizeof(bsde::Row2B)));
+            in.d_nodesb = static_cast<const bsde::Node2B *>(
+                put(in.nodesb.data(), in.nodesb.size() * sizeof(bsde::Node2B)));
+            in.d_corr_l = static_cast<const double4 *>(
+                put(in.corr_l.data(), in.corr_l.size() * sizeof(double4)));
+            in.d_corr_r = static_cast<const double4 *>(
+                put(in.corr_r.data(), in.corr_r.size() * sizeof(double4)));
+            const size_t lds = bsde::kGroups2B * bsde::sweep2b_wave_lds(in.spread);
+            if (lds > 65536 && bsde::set_sweep2b_lds_limit(lds) != hipSuccess) {
+                bsde_plan_destroy(pl);
+                return BSDE_EDEVICE;
+            }
+        }
     }
-    // workspace: rings (12 planes of doubles per layer, or 15 of floats in the
-    // FP32 form), final layers, statistics
+    // workspace: rings (6 planes of doubles per layer in the B-spline form, 12
+    // with the bicubic, or 15 of floats in the FP32 form), final layers, statistics
     size_t off = 0;
     for (Instance2 &in : pl->inst2) {
         in.ring_off = off;
-        off += align_up((in.f32 ? (size_t)15 * sizeof(float) : (size_t)12 * sizeof(double)) *
-                            (in.K + 1) * in.plane,
+        off += align_up((size_t)in.planes() * (in.f32 ? sizeof(float) : sizeof(double)) * (in.K + 1) *
+                            in.plane,
                         256);
+        if (in.bspline) {  // between the two passes of the spline
+            in.tmp_off = off;
+            off += align_up((size_t)3 * sizeof(double) * in.plane, 256);
+        }
     }
     for (Instance2 &in : pl->inst2) {
         in.fin_off = off;
@@ -1449,8 +1595,7 @@ bsde_status bsde_problem_info(const bsde_problem *pb, bsde_problem_info_t *info)
         r.stability_ratio =
             std::max(std::hypot(pb->vol[0][0], pb->vol[0][1]) / dx0,
                      std::hypot(pb->vol[1][0], pb->vol[1][1]) / dx1) * std::sqrt(2.0 * dt);
-        r.node_reach = r.supported ? in.pad0 - 1 : 0;
-        if (r.supported) r.node_reach = std::max({r.node_reach, in.pad1 - 1, in.pad0r - bsde::kTile2R - 1});
+        r.node_reach = r.supported ? in.reach : 0;
     }
     r.stable = beyond_stability_limit(r.stability_ratio) ? 0 : 1;
     *info = r;
@@ -1888,7 +2033,7 @@ bsde_status bsde_profile_kernels(bsde_plan_t plan, void *ws, const bsde_io *io, 
         kt->path = 2;
         kt->points_per_lane = 1;
         kt->node_groups = 1;
-        kt->blocks = in.nwaves / bsde::kWaves2;
+        kt->blocks = in.nwaves / (in.bspline ? bsde::kGroups2B : bsde::kWaves2);
         kt->lds_bytes = 0;
         return BSDE_OK;
     }

@@ -63,6 +63,34 @@ struct SplineFilter {
 };
 constexpr int kMinLine = kPcrTaps / 2 + 2;  // 33: one reflection covers the filter's reach
 
+// FP64 form with the natural spline: a layer is kept by the coefficients of
+// its tensor product of cubic B-splines, one double per function and point, so
+// a ring slot is 6 planes of n0 x n1 doubles (the values of y, z1, z2, then
+// their coefficients) and the sweep reads 4 x 4 coefficients where the form
+// above reads 2 x 2 points of 4 planes.
+constexpr int kTile2B = 256;   // grid columns of a block (one grid row), four per lane
+constexpr int kGroups2B = 4;   // wavefronts of a block: they share the (j, l0) node rows
+constexpr int kPlanes2B = 6;
+
+// Per (j, l0): the node row's axis-0 cell and B-spline weights, and the row's
+// weights of eq (20).  u = p0 y + p1 z1 + p2 z2 is the linear driver's value
+// without its constant.
+struct alignas(16) Row2B {
+    int m0, m1lo, m1hi, extra;  // extra: the y expectation pass (pass 2)
+    double b[4];
+    double H;    // Y  += H E[u]
+    double Gu;   // Z1 += E[C z1 + Gu u + Gy y]
+    double Gy;
+    double C;    // Z2 += E[C z2]  (and the node's dW1 terms)
+    double ey;   // Y  += ey E[y]  (pass 2)
+    double pad;
+};
+// Per (j, l0, l1): axis-1 B-spline weights times the quadrature weight, and the
+// weights of E[u dW1] (Z2) and E[y dW1] (Z2, pass 2).
+struct alignas(16) Node2B {
+    double w0, w1, w2, w3, gu, gy, pad0, pad1;
+};
+
 // The truncated PCR of the (1, 4, 1) system as line filters, constants of
 // the system evaluated at compile time: c[k + 31] acts on the odd extension
 // of the second differences, d[k + 32] on the values (the second difference
@@ -70,6 +98,8 @@ constexpr int kMinLine = kPcrTaps / 2 + 2;  // 33: one reflection covers the fil
 struct SplineTaps {
     double c[kPcrTaps];
     double d[kPcrTaps + 2];
+    double inv_b;            // M = 6/dx^2 inv_b sum d v
+    double e[kPcrTaps + 2];  // B-spline coefficients: v - dx^2/6 M = sum e v
 };
 __host__ __device__ constexpr SplineTaps spline_taps()
 {
@@ -98,11 +128,14 @@ __host__ __device__ constexpr SplineTaps spline_taps()
         const double cp = (m + 1 >= -H && m + 1 <= H) ? cur[m + 1 + H] : 0.0;
         t.d[m + H + 1] = cm - 2.0 * c0 + cp;
     }
+    t.inv_b = 1.0 / bv;
+    for (int k = 0; k < T + 2; ++k) t.e[k] = (k == H + 1 ? 1.0 : 0.0) - t.inv_b * t.d[k];
     return t;
 }
 
 struct Sweep2Args {
-    char *ring;             // K+1 slots of kPlanes2<E> planes of E (double or float)
+    char *ring;             // K+1 slots of `planes` planes of E (double or float)
+    int planes, vstep;      // planes per slot; plane of function f's values: vstep f
     size_t plane;
     int n0, n1, npad1, pad0, pad1;
     int K, Ky, L, n, n_stop;
@@ -116,24 +149,35 @@ struct Sweep2Args {
     int zform;              // first term of the z equation: 0 E[z^{n+1}], 1 E[y^{n+1} dW]/dt
     int interp;             // bsde_interp: the natural spline or the bicubic
     int half;               // LDS window columns of one parity: ceil(widest window / 2)
+    // B-spline form: node rows, nodes, and the corrections of the columns next
+    // to the ends of axis 1 (nl and nr columns a node row, sums of weights)
+    const Row2B *rowsb;
+    const Node2B *nodesb;
+    const double4 *corr_l, *corr_r;
+    int nl, nr, lds_wave;   // lds_wave: LDS bytes of a wavefront
+    double lin_y, lin_z1, lin_z2;  // the driver's constant term
+    double *tmp;            // three planes between the two spline passes
     double *fin;            // layer n_stop: y, z1, z2 planes of n0*n1
     unsigned int *st_iter_max;
     unsigned long long *st_iter_sum, *st_nonconv;
 };
 
-// Planes of a ring slot and the typed address of plane p of slot `slot`.
-template <typename E>
-constexpr int kPlanes2 = std::is_same<E, float>::value ? 15 : 12;
+// The typed address of plane p of slot `slot`.
 template <typename E>
 __host__ __device__ inline E *plane2(const Sweep2Args &a, int slot, int p)
 {
-    return reinterpret_cast<E *>(a.ring) + (size_t)(kPlanes2<E> * slot + p) * a.plane;
+    return reinterpret_cast<E *>(a.ring) + (size_t)(a.planes * slot + p) * a.plane;
 }
 
 // The launchers take the element type of the ring planes: f32 = the FP32
 // form (float planes, residual planes), else double.
 size_t sweep2d_lds(int half);  // dynamic LDS of the sweep kernel
 hipError_t launch_sweep2d(bool f32, const Sweep2Args &a, hipStream_t s);
+// B-spline form: the step, and the coefficients of the layer in slot `slot`
+size_t sweep2b_wave_lds(int spread);  // LDS bytes of a wavefront, widest node spread
+hipError_t set_sweep2b_lds_limit(size_t bytes);
+hipError_t launch_sweep2b(const Sweep2Args &a, hipStream_t s);
+hipError_t launch_coef2d(const Sweep2Args &a, int slot, hipStream_t s);
 // splines and ghosts of the layer in slot `slot`
 hipError_t launch_spline2d(bool f32, const Sweep2Args &a, int slot, const SplineFilter &f,
                            hipStream_t s);

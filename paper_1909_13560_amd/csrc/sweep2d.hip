@@ -159,6 +159,44 @@ __device__ inline void store_fed_back2(float *val, float *res, size_t o, double 
     res[o] = (float)(t - (double)q);
 }
 
+// Picard iteration of the implicit y equation at one point, from y; a fixed
+// number of iterations ends early where an iterate repeats one of the two
+// before it, with the value that the last iteration would give.
+__device__ inline double picard2(const Sweep2Args &a, double y, double Yc, double z1, double z2,
+                                 unsigned int &it, bool &conv)
+{
+    it = 0;
+    conv = true;
+    const unsigned int itmax = (unsigned int)a.picard_max;
+    if (a.picard_tol > 0.0) {
+        conv = false;
+        while (it < itmax) {
+            const double yn = fma(a.h0, f_linear2(a.drv, y, z1, z2), Yc);
+            ++it;
+            const double dy = fabs(yn - y);
+            y = yn;
+            if (dy <= a.picard_tol * fmax(1.0, fabs(y))) {
+                conv = true;
+                break;
+            }
+        }
+    } else {
+        double y2 = y;
+        while (it < itmax) {
+            const double yn = fma(a.h0, f_linear2(a.drv, y, z1, z2), Yc);
+            ++it;
+            if (yn == y || yn == y2) {
+                if (yn == y || ((itmax - it) & 1u) == 0) y = yn;
+                it = itmax;
+                break;
+            }
+            y2 = y;
+            y = yn;
+        }
+    }
+    return y;
+}
+
 // One time step: layer n from layers n+1..n+K.  Block = kTile2R x kTile2C points.
 // Dynamic LDS: (U, V) of 3 functions x kTile2R rows x 2 a.half columns.  E: the
 // element type of the ring planes; the arithmetic is double in both forms.
@@ -238,23 +276,9 @@ sweep2d(const Sweep2Args a)
         const bool valid = i0 < a.n0 && i1 < a.n1;
         const size_t o = pidx(a, min(i0, a.n0 - 1), min(i1, a.n1 - 1));
         double y = prev[o];
-        int it = 0;
-        bool conv = true;
-        if (a.picard_tol > 0.0) {
-            conv = false;
-            while (it < a.picard_max) {
-                const double yn = fma(a.h0, f_linear2(a.drv, y, Z1[k], Z2[k]), Y[k]);
-                ++it;
-                const double dy = fabs(yn - y);
-                y = yn;
-                if (dy <= a.picard_tol * fmax(1.0, fabs(y))) {
-                    conv = true;
-                    break;
-                }
-            }
-        } else {
-            for (; it < a.picard_max; ++it) y = fma(a.h0, f_linear2(a.drv, y, Z1[k], Z2[k]), Y[k]);
-        }
+        unsigned int it;
+        bool conv;
+        y = picard2(a, y, Y[k], Z1[k], Z2[k], it, conv);
         if (valid) {
             if constexpr (std::is_same<E, float>::value) {
                 // residuals of y^{n+K_y} (y recurrence) and of z^{n+1} (z recurrence)
@@ -275,7 +299,7 @@ sweep2d(const Sweep2Args a)
                 a.fin[np + kk] = Z1[k];
                 a.fin[2 * np + kk] = Z2[k];
             }
-            it_max = max(it_max, (unsigned int)it);
+            it_max = max(it_max, it);
             it_sum += it;
             nonconv += conv ? 0u : 1u;
         }
@@ -334,6 +358,10 @@ __device__ inline double spline_line(const E *v, long stride, int n, int i,
 }
 
 constexpr int kRun = 16;  // consecutive outputs per thread of the line passes
+// The axis-0 passes take four: 17 loads per output (mostly L2 hits) instead of
+// 5, but four times the threads, which is what covers the loads' latency
+// (387 x 387: 49 -> 11 us in FP64, 35 -> 9 us for the FP32 form's filter).
+constexpr int kRunCols = 4;
 
 // Outputs i0 .. i0 + kRun - 1 (those < n) of the natural spline of one line
 // of n >= kMinLine values: M_i = s6 sum_k d[k] v~_{i-32+k}.  Each value is
@@ -342,7 +370,7 @@ constexpr int kRun = 16;  // consecutive outputs per thread of the line passes
 // v~_{-j} = 2 v_0 - v_j and v~_{n-1+j} = 2 v_{n-1} - v_{n-1-j}: their second
 // differences are then the odd extension the natural end conditions call
 // for, so the values form holds at every point; M_0 = M_{n-1} = 0.
-template <typename E>
+template <int kRun, typename E>
 __device__ inline void line_run(const E *v, long stride, int n, int i0, double s6, E *out,
                                 long ostride)
 {
@@ -383,7 +411,7 @@ __device__ inline void line_run(const E *v, long stride, int n, int i0, double s
 }
 
 // The same outputs for lines shorter than kMinLine, one at a time.
-template <typename E>
+template <int kRun, typename E>
 __device__ inline void line_run_short(const E *v, long stride, int n, int i0,
                                       const SplineFilter &F, double s6, E *out, long ostride)
 {
@@ -396,7 +424,7 @@ __device__ inline void line_run_short(const E *v, long stride, int n, int i0,
 // M_xx of field blockIdx.y (y, z1, z2): lines along axis 0.  Thread t:
 // column t % n1 (adjacent lanes read adjacent columns), rows from
 // kRun * (t / n1).
-template <typename E>
+template <int kRun, typename E>
 __global__ void __launch_bounds__(256) spline2d_cols(const Sweep2Args a, int slot,
                                                      const SplineFilter F)
 {
@@ -405,9 +433,9 @@ __global__ void __launch_bounds__(256) spline2d_cols(const Sweep2Args a, int slo
     const int i1 = (int)(t % a.n1), i0 = (int)(t / a.n1) * kRun;
     E *col = plane2<E>(a, slot, 4 * blockIdx.y) + pidx(a, 0, i1);
     if (a.n0 >= kMinLine)
-        line_run(col, a.npad1, a.n0, i0, F.s6[0], col + a.plane, a.npad1);
+        line_run<kRun>(col, a.npad1, a.n0, i0, F.s6[0], col + a.plane, a.npad1);
     else
-        line_run_short(col, a.npad1, a.n0, i0, F, F.s6[0], col + a.plane, a.npad1);
+        line_run_short<kRun>(col, a.npad1, a.n0, i0, F, F.s6[0], col + a.plane, a.npad1);
 }
 
 // Lines along axis 1 of field blockIdx.y / 2: the values give M_yy
@@ -425,9 +453,9 @@ __global__ void __launch_bounds__(256) spline2d_rows(const Sweep2Args a, int slo
     const E *src = row + (size_t)g * a.plane;
     E *dst = row + (size_t)(2 + g) * a.plane;
     if (a.n1 >= kMinLine)
-        line_run(src, 1, a.n1, i1, F.s6[1], dst, 1);
+        line_run<kRun>(src, 1, a.n1, i1, F.s6[1], dst, 1);
     else
-        line_run_short(src, 1, a.n1, i1, F, F.s6[1], dst, 1);
+        line_run_short<kRun>(src, 1, a.n1, i1, F, F.s6[1], dst, 1);
 }
 
 // Lines along axis 1 of at least kMinLine points, through LDS: a block
@@ -577,7 +605,7 @@ __global__ void __launch_bounds__(256) scatter2d(const Sweep2Args a, const doubl
         if constexpr (std::is_same<E, float>::value) {  // value and its rounding residual
             store_fed_back2(base + 4 * f * a.plane, base + (12 + f) * a.plane, o, v[f], 0.0f);
         } else {
-            base[4 * f * a.plane + o] = v[f];
+            base[(size_t)a.vstep * f * a.plane + o] = v[f];
         }
     }
 }
@@ -600,6 +628,552 @@ __global__ void __launch_bounds__(256) gather2d(const Sweep2Args a, double *__re
 }
 
 // ---------------------------------------------------------------------------
+// B-spline form (FP64, natural spline).
+//
+// A layer's tensor spline is S = sum_ab b_a(phi0) b_b(phi1) c(p-1+a, q-1+b).
+// For one axis-0 node l0 the four source rows combine into one row of
+// coefficients per function; with the linear driver the functions that the
+// sums of eq (20) need are linear in them, so a column of the window holds
+//   s0 = u = p0 y + p1 z1 + p2 z2,  s1 = C z1 + Gu u + Gy y,  s2 = C z2
+// and a node l1 costs, per point, t = sum_b w_b s0 (Y += H t, Z2 += gu t),
+// Z1 += sum w_b s1, Z2 += sum w_b s2: 14 operations, against 20 with values
+// and second derivatives of y, z1, z2 and the driver per node.  The layer
+// j = K_y (and z form E[y dW]/dt at j = 1) adds a pass over y alone.
+//
+// One wavefront works by itself: it stages the window of its 256 columns (four
+// per lane: a node reads 7 coefficients for 4 points) and runs the row's
+// nodes without any block barrier, so the wavefronts of a CU drift apart and
+// one stages while others compute.  The block's four wavefronts take every
+// fourth node row of the same tile and add their sums in LDS at the end
+// (classes 0+2, 1+3).  Bound: FP64 issue and LDS reads about equally (42 B per
+// node and point).
+//
+// Cells outside the grid: along axis 0 the row's weights (uniform) become
+// those of the end row; beyond the natural end the coefficient continues as
+// 2 c(0) - c(1), folded into the weights of the first rows.  Along axis 1 the
+// window continues the end column's coefficient as a constant, which is the
+// clamped evaluation except in the two cells next to the end, whose error is
+// (c(1) - c(0)) b_3 outside and (c(1) - c(0)) b_0 inside: per node two columns
+// of the tile's row, summed over a row's nodes on the host (corr_l, corr_r).
+// ---------------------------------------------------------------------------
+namespace {
+
+__device__ inline Node2B load_node2b(const Node2B *p)
+{
+    Node2B n{};
+    n.w0 = const_load(&p->w0);
+    n.w1 = const_load(&p->w1);
+    n.w2 = const_load(&p->w2);
+    n.w3 = const_load(&p->w3);
+    n.gu = const_load(&p->gu);
+    n.gy = const_load(&p->gy);
+    return n;
+}
+
+__device__ inline int slot4(int e) { return e + (e >> 2); }  // a pad slot per four columns
+
+// seven consecutive columns from the lane's first at an offset res mod 4
+template <int B, typename V>
+__device__ inline void fetch7(const V *p, V (&r)[7])
+{
+#pragma unroll
+    for (int q = 0; q < 7; ++q) r[q] = p[q + ((B + q) >> 2)];
+}
+template <typename V>
+__device__ inline void fetch7(const V *p, int res, V (&r)[7])
+{
+    switch (res & 3) {
+    case 0: fetch7<0>(p, r); asm volatile("; pattern 0"); break;
+    case 1: fetch7<1>(p, r); asm volatile("; pattern 1"); break;
+    case 2: fetch7<2>(p, r); asm volatile("; pattern 2"); break;
+    default: fetch7<3>(p, r); asm volatile("; pattern 3"); break;
+    }
+}
+
+// order the wavefront's own LDS writes and reads
+__device__ inline void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int kEdge2B = 4;  // columns 0, 1, n1 - 2, n1 - 1 kept beside the window
+
+}  // namespace
+
+size_t sweep2b_wave_lds(int spread)
+{
+    const int w = kTile2B + spread + 3;
+    const int slots = w + w / 4 + 2;
+    const size_t stage = (size_t)slots * (sizeof(double2) + sizeof(double)) + kEdge2B * 3 * sizeof(double);
+    const size_t part = (size_t)kTile2B * 3 * sizeof(double);
+    return (std::max(stage, part) + 15) / 16 * 16;
+}
+
+__global__ void __launch_bounds__(64 * kGroups2B) __attribute__((amdgpu_waves_per_eu(3)))
+sweep2b(const Sweep2Args a)
+{
+    extern __shared__ double2 smem2b[];
+    const int tiles1 = (a.n1 + kTile2B - 1) / kTile2B;
+    const int idx = xcd_tile(blockIdx.x, gridDim.x);
+    const int i0 = idx / tiles1, c0 = (idx % tiles1) * kTile2B;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int grp = __builtin_amdgcn_readfirstlane(tid >> 6);
+    char *mine = reinterpret_cast<char *>(smem2b) + (size_t)grp * a.lds_wave;
+    const int S = a.K + 1, n0 = a.n0, n1 = a.n1;
+    double Y[4], Z1[4], Z2[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) Y[k] = Z1[k] = Z2[k] = 0.0;
+    const int col = c0 + lane * 4;  // the lane's first column
+    const bool near_l = c0 < a.nl, near_r = c0 + kTile2B > n1 - a.nr;
+    const int nrows = a.K * a.L;
+    // the row ahead: its first window columns (kPre per lane) are loaded while
+    // the nodes of the row before are evaluated
+    constexpr int kPre = 1;
+    int nslot = a.n % S, njc = 0, nl0 = grp;  // layer and l0 of the row ahead
+    const double *nq0 = nullptr;
+    int nw0 = 0;
+    double pf[kPre][12];
+    auto load_column = [&](const double *q0, int q, double (&r)[12]) {
+        // scalar row bases and one 32-bit column offset (a row is below 4 GiB)
+        const unsigned o = (unsigned)q * 8u;
+        const size_t st = (size_t)n1 * 8;
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            const char *v = reinterpret_cast<const char *>(q0 + (size_t)f * a.plane);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) r[4 * f + k] = *reinterpret_cast<const double *>(v + k * st + o);
+        }
+    };
+    auto column = [&](int w0, int e) { return min(max(w0 + e, 0), n1 - 1); };
+    auto ahead = [&](int rowi) {  // loads for row rowi
+        while (nl0 >= a.L || njc == 0) {  // rows are ordered by layer
+            if (njc != 0) nl0 -= a.L;
+            ++njc;
+            nslot = nslot + 1 == S ? 0 : nslot + 1;
+        }
+        nl0 += kGroups2B;
+        const Row2B *rp = a.rowsb + rowi;
+        const int r0 = min(max(i0 + const_load(&rp->m0) - 1, 0), n0 - 4);
+        nq0 = plane2<double>(a, nslot, 3) + (size_t)r0 * n1;
+        nw0 = c0 + const_load(&rp->m1lo) - 1;
+#pragma unroll
+        for (int u = 0; u < kPre; ++u) load_column(nq0, column(nw0, lane + 64 * u), pf[u]);
+    };
+    if (grp < nrows) ahead(grp);
+    for (int rowi = grp; rowi < nrows; rowi += kGroups2B) {
+        const Row2B *rp = a.rowsb + rowi;
+        const int m0 = const_load(&rp->m0), m1lo = const_load(&rp->m1lo), m1hi = const_load(&rp->m1hi);
+        const bool extra = const_load(&rp->extra) != 0;
+        const int W = kTile2B + (m1hi - m1lo) + 3;
+        const int slots = W + (W >> 2) + 2;
+        double2 *wa = reinterpret_cast<double2 *>(mine);      // (s0, s1)
+        double *wb = reinterpret_cast<double *>(wa + slots);  // s2, then y in pass 2
+        double *we = wb + slots;                              // end columns: s0, s1, s2 each
+        const int mv = a.m1[(size_t)rowi * a.L + min(lane, a.L - 1)] - m1lo;
+        // axis-0 weights on four rows r0 .. r0 + 3 inside the grid
+        double b0 = const_load(&rp->b[0]), b1 = const_load(&rp->b[1]), b2 = const_load(&rp->b[2]),
+               b3 = const_load(&rp->b[3]);
+        // (the loads take the rows min(max(p - 1, 0), n0 - 4) ..)
+        const int p = i0 + m0;
+        if (p < 0) {  // the value at the first row
+            b0 = 1.0;
+            b1 = b2 = b3 = 0.0;
+        } else if (p > n0 - 2) {  // the value at the last row
+            b3 = 1.0;
+            b0 = b1 = b2 = 0.0;
+        } else {
+            if (p == 0) {  // c(-1) = 2 c(0) - c(1)
+                const double x = b0;
+                b0 = fma(2.0, x, b1);
+                b1 = b2 - x;
+                b2 = b3;
+                b3 = 0.0;
+            }
+            if (p == n0 - 2) {  // c(n0) = 2 c(n0 - 1) - c(n0 - 2); rows shift down by one
+                const double x = b3;
+                b3 = fma(2.0, x, b2);
+                b2 = b1 - x;
+                b1 = b0;
+                b0 = 0.0;
+            }
+        }
+        const double *q0 = nq0;
+        const int w0 = nw0;  // window column 0
+        const double H = const_load(&rp->H), Gu = const_load(&rp->Gu), Gy = const_load(&rp->Gy),
+                     C = const_load(&rp->C), ey = const_load(&rp->ey);
+        const double p0 = a.drv.p0, p1 = a.drv.p1, p2 = a.drv.p2;
+        auto combine = [&](const double *r) { return fma(b3, r[3], fma(b0, r[0], fma(b2, r[2], b1 * r[1]))); };
+        auto put = [&](int e, const double (&r)[12]) {
+            const double y = combine(r), z1 = combine(r + 4), z2 = combine(r + 8);
+            const double u = fma(p0, y, fma(p1, z1, p2 * z2));
+            const double s1 = fma(C, z1, fma(Gu, u, Gy * y)), s2 = C * z2;
+            if (e < W) {
+                wa[slot4(e)] = make_double2(u, s1);
+                wb[slot4(e)] = s2;
+            } else if (e < W + kEdge2B) {  // the end columns
+                we[3 * (e - W)] = u;
+                we[3 * (e - W) + 1] = s1;
+                we[3 * (e - W) + 2] = s2;
+            }
+        };
+        // element e of the staging: window column, then the four end columns
+        auto staged = [&](int e) {
+            const int x = min(e - W, kEdge2B - 1);
+            return x < 0 ? column(w0, e) : x < 2 ? x : n1 - 4 + x;
+        };
+        wave_lds_fence();  // the last row's reads are done
+#pragma unroll
+        for (int u = 0; u < kPre; ++u) put(lane + 64 * u, pf[u]);
+#pragma unroll 1
+        for (int e = lane + 64 * kPre; e - lane < W + kEdge2B; e += 128) {
+            double r[2][12];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) load_column(q0, staged(e + 64 * u), r[u]);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) put(e + 64 * u, r[u]);
+        }
+        wave_lds_fence();
+        // corrections of the lane's columns: of the left end where the tile is
+        // near both (the right one's then follow after the nodes)
+        const double4 *ct = near_l ? a.corr_l + (size_t)rowi * a.nl : a.corr_r + (size_t)rowi * a.nr;
+        const int cn = near_l ? a.nl : a.nr;
+        double2 kc[4];
+        if (near_l || near_r) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int c = near_l ? col + k : n1 - 1 - (col + k);
+                const double2 v = *reinterpret_cast<const double2 *>(ct + min(max(c, 0), cn - 1));
+                kc[k] = c >= 0 && c < cn ? v : make_double2(0.0, 0.0);
+            }
+        }
+        if (rowi + kGroups2B < nrows) ahead(rowi + kGroups2B);
+        const double2 *la = wa + slot4(lane * 4);
+        const double *lb = wb + slot4(lane * 4);
+        const Node2B *nodes = a.nodesb + (size_t)rowi * a.L;
+#pragma unroll 1
+        for (int l = 0; l < a.L; ++l) {
+            const Node2B nd = load_node2b(nodes + l);
+            const int off = __builtin_amdgcn_readlane(mv, l), so = off + (off >> 2);
+            double2 ra[7];
+            double rb[7];
+            // (the comments keep the four patterns apart: merged into one, every
+            // read would compute its address and lose its alignment)
+            switch (off & 3) {
+            case 0:
+                fetch7<0>(la + so, ra);
+                fetch7<0>(lb + so, rb);
+                asm volatile("; pattern 0");
+                break;
+            case 1:
+                fetch7<1>(la + so, ra);
+                fetch7<1>(lb + so, rb);
+                asm volatile("; pattern 1");
+                break;
+            case 2:
+                fetch7<2>(la + so, ra);
+                fetch7<2>(lb + so, rb);
+                asm volatile("; pattern 2");
+                break;
+            default:
+                fetch7<3>(la + so, ra);
+                fetch7<3>(lb + so, rb);
+                asm volatile("; pattern 3");
+                break;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double t = fma(nd.w3, ra[k + 3].x,
+                                     fma(nd.w0, ra[k].x, fma(nd.w2, ra[k + 2].x, nd.w1 * ra[k + 1].x)));
+                Y[k] = fma(H, t, Y[k]);
+                Z1[k] = fma(nd.w0, ra[k].y, Z1[k]);
+                Z1[k] = fma(nd.w1, ra[k + 1].y, Z1[k]);
+                Z1[k] = fma(nd.w2, ra[k + 2].y, Z1[k]);
+                Z1[k] = fma(nd.w3, ra[k + 3].y, Z1[k]);
+                double z = fma(nd.gu, t, Z2[k]);
+                z = fma(nd.w0, rb[k], z);
+                z = fma(nd.w1, rb[k + 1], z);
+                z = fma(nd.w2, rb[k + 2], z);
+                Z2[k] = fma(nd.w3, rb[k + 3], z);
+            }
+        }
+        // corrections next to the ends of axis 1: x the sum of the weights, y
+        // of the weights times gu
+        auto correct = [&](const double2 (&c)[4], int i, int o) {  // end columns i (inner), o (outer)
+            const double e0 = we[3 * i] - we[3 * o], e1 = we[3 * i + 1] - we[3 * o + 1],
+                         e2 = we[3 * i + 2] - we[3 * o + 2];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                Y[k] = fma(-H * c[k].x, e0, Y[k]);
+                Z1[k] = fma(-c[k].x, e1, Z1[k]);
+                Z2[k] = fma(-c[k].y, e0, fma(-c[k].x, e2, Z2[k]));
+            }
+        };
+        if (near_l || near_r) correct(kc, near_l ? 1 : 2, near_l ? 0 : 3);
+        if (near_l && near_r) {
+            double2 k2[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int d = n1 - 1 - (col + k);
+                const double2 v = *reinterpret_cast<const double2 *>(a.corr_r + (size_t)rowi * a.nr +
+                                                                     min(max(d, 0), a.nr - 1));
+                k2[k] = d >= 0 && d < a.nr ? v : make_double2(0.0, 0.0);
+            }
+            correct(k2, 2, 3);
+        }
+        if (extra) {  // pass 2: the expectation of y
+            wave_lds_fence();
+#pragma unroll 1
+            for (int e = lane; e - lane < W + kEdge2B; e += 256) {
+                double r[4][4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const unsigned o = (unsigned)staged(e + 64 * u) * 8u;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        r[u][k] = *reinterpret_cast<const double *>(reinterpret_cast<const char *>(q0) +
+                                                                    k * (size_t)n1 * 8 + o);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int x = e + 64 * u;
+                    const double y = combine(r[u]);
+                    if (x < W)
+                        wb[slot4(x)] = y;
+                    else if (x < W + kEdge2B)
+                        we[x - W] = y;
+                }
+            }
+            wave_lds_fence();
+#pragma unroll 1
+            for (int l = 0; l < a.L; ++l) {
+                const Node2B nd = load_node2b(nodes + l);
+                const int off = __builtin_amdgcn_readlane(mv, l), so = off + (off >> 2);
+                double rb[7];
+                fetch7(lb + so, off, rb);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const double t = fma(nd.w3, rb[k + 3],
+                                         fma(nd.w0, rb[k], fma(nd.w2, rb[k + 2], nd.w1 * rb[k + 1])));
+                    Y[k] = fma(ey, t, Y[k]);
+                    Z2[k] = fma(nd.gy, t, Z2[k]);
+                }
+            }
+            // x the sum of the weights, z of the weights times gy
+            auto correct_y = [&](const double4 *t, int n, bool left) {
+                const double e0 = left ? we[1] - we[0] : we[2] - we[3];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int c = left ? col + k : n1 - 1 - (col + k);
+                    const double4 v = t[(size_t)rowi * n + min(max(c, 0), n - 1)];
+                    const bool in = c >= 0 && c < n;
+                    Y[k] = fma(in ? -ey * v.x : 0.0, e0, Y[k]);
+                    Z2[k] = fma(in ? -v.z : 0.0, e0, Z2[k]);
+                }
+            };
+            if (near_l) correct_y(a.corr_l, a.nl, true);
+            if (near_r) correct_y(a.corr_r, a.nr, false);
+        }
+    }
+    // the groups' sums meet in LDS (each over its own window); thread t
+    // finishes column t of the tile
+    wave_lds_fence();
+    double *part = reinterpret_cast<double *>(mine);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        part[lane * 4 + k] = Y[k];
+        part[kTile2B + lane * 4 + k] = Z1[k];
+        part[2 * kTile2B + lane * 4 + k] = Z2[k];
+    }
+    __syncthreads();
+    double v[3];
+#pragma unroll
+    for (int f = 0; f < 3; ++f) {
+        double g[kGroups2B];
+#pragma unroll
+        for (int k = 0; k < kGroups2B; ++k)
+            g[k] = reinterpret_cast<const double *>(reinterpret_cast<const char *>(smem2b) +
+                                                    (size_t)k * a.lds_wave)[f * kTile2B + tid];
+        v[f] = (g[0] + g[2]) + (g[1] + g[3]);
+    }
+    const double Yc = v[0] + a.lin_y, z1 = v[1] + a.lin_z1, z2 = v[2] + a.lin_z2;
+    const int i1 = c0 + tid;
+    const bool valid = i1 < n1;
+    const size_t o = (size_t)i0 * n1 + min(i1, n1 - 1);
+    double y = plane2<double>(a, (a.n + 1) % S, 0)[o];
+    unsigned int it = 0;
+    bool conv = true;
+    y = picard2(a, y, Yc, z1, z2, it, conv);
+    if (valid) {
+        double *out = plane2<double>(a, a.n % S, 0);
+        out[o] = y;
+        out[o + a.plane] = z1;
+        out[o + 2 * a.plane] = z2;
+        if (a.n == a.n_stop) {
+            const size_t np = (size_t)n0 * n1;
+            a.fin[o] = y;
+            a.fin[np + o] = z1;
+            a.fin[2 * np + o] = z2;
+        }
+    }
+    if (a.st_iter_max) {
+        const unsigned int itm = wave_max_u32(valid ? it : 0u), its = wave_sum_u32(valid ? it : 0u);
+        const unsigned int nc = wave_sum_u32(valid && !conv ? 1u : 0u);
+        if (lane == 0) {
+            const int w = idx * kGroups2B + grp;
+            a.st_iter_max[w] = max(a.st_iter_max[w], itm);
+            a.st_iter_sum[w] += its;
+            a.st_nonconv[w] += nc;
+        }
+    }
+}
+
+// Coefficients of a layer: the values filtered along axis 0 into the tmp
+// planes, these along axis 1 into the coefficient planes.  A thread computes
+// kRunCols (axis 0) or kRun consecutive outputs of one line and streams its inputs once, as
+// spline2d_cols; the taps give v - dx^2/6 M directly, and both end values of a
+// line are their own coefficients (M = 0 there).
+namespace {
+// lines shorter than the filter's one-reflection reach: point by point
+__device__ inline double coef_line(const double *v, long stride, int n, int i)
+{
+    constexpr SplineTaps T = spline_taps();
+    const double x = v[(long)i * stride];
+    if (i == 0 || i == n - 1) return x;
+    double acc = 0.0;
+    for (int k = 0; k < kPcrTaps; ++k) acc = fma(T.c[k], rt_line(v, stride, n, i + k - 31), acc);
+    return fma(-T.inv_b, acc, x);
+}
+}  // namespace
+
+__global__ void __launch_bounds__(256) coef2d_cols(const Sweep2Args a, int slot)
+{
+    constexpr SplineTaps T = spline_taps();
+    constexpr int H = kPcrTaps / 2 + 1;
+    const long t = blockIdx.x * 256L + threadIdx.x;
+    const int n = a.n0, st = a.n1;
+    if (t >= (long)st * ((n + kRunCols - 1) / kRunCols)) return;
+    const int i1 = (int)(t % st), j0 = (int)(t / st) * kRunCols;
+    const double *v = plane2<double>(a, slot, blockIdx.y) + i1;
+    double *out = a.tmp + (size_t)blockIdx.y * a.plane + i1;
+    if (n < kMinLine) {
+        for (int i = j0; i < min(j0 + kRunCols, n); ++i) out[(long)i * st] = coef_line(v, st, n, i);
+        return;
+    }
+    double acc[kRunCols];
+#pragma unroll
+    for (int r = 0; r < kRunCols; ++r) acc[r] = 0.0;
+    const double v0 = v[0], vn = v[(long)(n - 1) * st];
+    if (j0 >= H && j0 + kRunCols - 1 + H <= n - 1) {  // clear of both ends
+        const double *p = v + (long)(j0 - H) * st;
+#pragma unroll
+        for (int m = 0; m < kRunCols + 2 * H; ++m) {
+            const double x = p[(long)m * st];
+#pragma unroll
+            for (int r = 0; r < kRunCols; ++r)
+                if (m - r >= 0 && m - r <= 2 * H) acc[r] = fma(T.e[m - r], x, acc[r]);
+        }
+    } else {
+#pragma unroll
+        for (int m = 0; m < kRunCols + 2 * H; ++m) {
+            const int k = j0 - H + m;
+            const int kk = min(max(k < 0 ? -k : (k > n - 1 ? 2 * (n - 1) - k : k), 0), n - 1);
+            const double y = v[(long)kk * st];
+            const double x = k < 0 ? 2.0 * v0 - y : (k > n - 1 ? 2.0 * vn - y : y);
+#pragma unroll
+            for (int r = 0; r < kRunCols; ++r)
+                if (m - r >= 0 && m - r <= 2 * H) acc[r] = fma(T.e[m - r], x, acc[r]);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kRunCols; ++r) {
+        const int i = j0 + r;
+        if (i < n) out[(long)i * st] = i == 0 ? v0 : i == n - 1 ? vn : acc[r];
+    }
+}
+
+__global__ void __launch_bounds__(256) coef2d_rows(const Sweep2Args a, int slot)
+{
+    constexpr SplineTaps T = spline_taps();
+    constexpr int H = kPcrTaps / 2 + 1;
+    __shared__ double sm[kRowTile * kRowStride];
+    const int n = a.n1, tiles1 = (n + kRowCols - 1) / kRowCols;
+    const int r0 = (int)(blockIdx.x / tiles1) * kRowTile, c0 = (int)(blockIdx.x % tiles1) * kRowCols;
+    const double *src = a.tmp + (size_t)blockIdx.y * a.plane;
+    double *dst = plane2<double>(a, slot, 3 + blockIdx.y);
+    const bool short_line = n < kMinLine;
+    if (!short_line) {
+        for (int e = threadIdx.x; e < kRowTile * kRowIn; e += 256) {
+            const int rr = e / kRowIn, cc = e - rr * kRowIn;
+            const int i0 = r0 + rr;
+            if (i0 >= a.n0) continue;
+            const double *v = src + (size_t)i0 * n;
+            const int k = c0 - H + cc;
+            const int kk = min(max(k < 0 ? -k : (k > n - 1 ? 2 * (n - 1) - k : k), 0), n - 1);
+            const double y = v[kk];
+            sm[rr * kRowStride + cc] = k < 0 ? 2.0 * v[0] - y : (k > n - 1 ? 2.0 * v[n - 1] - y : y);
+        }
+    }
+    __syncthreads();
+    const int r = threadIdx.x % kRowTile, q = threadIdx.x / kRowTile;
+    const int i0 = r0 + r, j0 = c0 + q * kRun;
+    double acc[kRun];
+    if (!short_line) {
+        const double *w = sm + r * kRowStride + q * kRun;
+#pragma unroll
+        for (int u = 0; u < kRun; ++u) acc[u] = 0.0;
+#pragma unroll
+        for (int m = 0; m < kRun + 2 * H; ++m) {
+            const double x = w[m];
+#pragma unroll
+            for (int u = 0; u < kRun; ++u)
+                if (m - u >= 0 && m - u <= 2 * H) acc[u] = fma(T.e[m - u], x, acc[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kRun; ++u)
+            if (j0 + u == 0 || j0 + u == n - 1) acc[u] = w[u + H];
+    } else {
+        const double *v = src + (size_t)min(i0, a.n0 - 1) * n;
+#pragma unroll
+        for (int u = 0; u < kRun; ++u) acc[u] = j0 + u < n ? coef_line(v, 1, n, j0 + u) : 0.0;
+    }
+    // outputs through LDS, so that the stores are whole lines
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kRun; ++u) sm[r * kRowStride + q * kRun + u] = acc[u];
+    __syncthreads();
+    for (int e = threadIdx.x; e < kRowTile * kRowCols; e += 256) {
+        const int rr = e / kRowCols, cc = e - rr * kRowCols;
+        if (r0 + rr < a.n0 && c0 + cc < n) dst[(size_t)(r0 + rr) * n + c0 + cc] = sm[rr * kRowStride + cc];
+    }
+}
+
+hipError_t set_sweep2b_lds_limit(size_t bytes)
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep2b),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+hipError_t launch_sweep2b(const Sweep2Args &a, hipStream_t s)
+{
+    const int tiles = a.n0 * ((a.n1 + kTile2B - 1) / kTile2B);
+    hipLaunchKernelGGL(sweep2b, dim3(tiles), dim3(64 * kGroups2B), (size_t)kGroups2B * a.lds_wave, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_coef2d(const Sweep2Args &a, int slot, hipStream_t s)
+{
+    const long tc = (long)a.n1 * ((a.n0 + kRunCols - 1) / kRunCols);
+    hipLaunchKernelGGL(coef2d_cols, dim3((unsigned)((tc + 255) / 256), 3), dim3(256), 0, s, a, slot);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const long tiles = (long)((a.n0 + kRowTile - 1) / kRowTile) * ((a.n1 + kRowCols - 1) / kRowCols);
+    hipLaunchKernelGGL(coef2d_rows, dim3((unsigned)tiles, 3), dim3(256), 0, s, a, slot);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
 size_t sweep2d_lds(int half) { return (size_t)3 * kTile2R * 2 * half * sizeof(double2); }
@@ -619,7 +1193,7 @@ __global__ void __launch_bounds__(256) export2d(const Sweep2Args a, double *__re
     const size_t o = pidx(a, (int)(i / a.n1), (int)(i % a.n1));
     double v[3];
     for (int f = 0; f < 3; ++f) {
-        v[f] = base[(size_t)(4 * f) * a.plane + o];
+        v[f] = base[(size_t)(a.vstep * f) * a.plane + o];
         if constexpr (std::is_same<E, float>::value) v[f] += (double)base[(size_t)(12 + f) * a.plane + o];
     }
     ly[r * np + i] = v[0];
@@ -649,8 +1223,8 @@ hipError_t launch_ghosts2d_t(const Sweep2Args &a, int slot, hipStream_t s)
 template <typename E>
 hipError_t launch_spline2d_t(const Sweep2Args &a, int slot, const SplineFilter &f, hipStream_t s)
 {
-    const long tc = (long)a.n1 * ((a.n0 + kRun - 1) / kRun);
-    hipLaunchKernelGGL(spline2d_cols<E>, dim3((unsigned)((tc + 255) / 256), 3), dim3(256), 0, s, a,
+    const long tc = (long)a.n1 * ((a.n0 + kRunCols - 1) / kRunCols);
+    hipLaunchKernelGGL((spline2d_cols<kRunCols, E>), dim3((unsigned)((tc + 255) / 256), 3), dim3(256), 0, s, a,
                        slot, f);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
