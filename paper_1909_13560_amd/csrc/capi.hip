@@ -61,6 +61,13 @@ struct Instance {
     bsde::GaussBand band[bsde::kMaxOrder + 1];  // per layer j (exact)
     int toep_off[bsde::kMaxOrder + 1] = {};       // band j in the device table
     const double *toep_w = nullptr;
+    // exact expectations on B-spline coefficients: bands and end corrections
+    std::vector<double> ex_band;
+    std::vector<double2> ex_corr;
+    int ex_boff[bsde::kMaxOrder + 1] = {}, ex_loff[bsde::kMaxOrder + 1] = {}, ex_roff[bsde::kMaxOrder + 1] = {};
+    int ex_nl[bsde::kMaxOrder + 1] = {}, ex_nr[bsde::kMaxOrder + 1] = {};
+    const double *d_ex_band = nullptr;
+    const double2 *d_ex_corr = nullptr;
     const bsde::NodeRecB *d_recb = nullptr;
     int2 *d_addr = nullptr;  // fused sweep: node addresses of the bound shape
     int steps;  // layers computed: N - K - n_stop + 1
@@ -389,6 +396,24 @@ bool build_instance(const bsde_problem &p, Instance &in)
                 return false;
             in.m_min = std::min(in.m_min, b.klo);
             in.m_max = std::max(in.m_max, b.klo + (int)b.ev.size() - 1);
+            in.ex_boff[j] = (int)in.ex_band.size();
+            in.ex_band.insert(in.ex_band.end(), b.ec.begin(), b.ec.end());
+            in.ex_band.insert(in.ex_band.end(), b.wc.begin(), b.wc.end());
+            const int cells = (int)b.i0.size();
+            auto piece = [&](const std::vector<double> &v, int cell) {  // cell relative to the point
+                const int k = cell - b.klo;
+                return k >= 0 && k < cells ? v[k] : 0.0;
+            };
+            in.ex_nl[j] = std::min(std::max(0, -b.klo) + 1, in.nx);
+            in.ex_nr[j] = std::min(std::max(0, b.klo + cells) + 2, in.nx);
+            in.ex_loff[j] = (int)in.ex_corr.size();
+            for (int i = 0; i < in.ex_nl[j]; ++i)
+                in.ex_corr.push_back(make_double2(piece(b.i3, -1 - i) + piece(b.i0, -i),
+                                                  piece(b.j3, -1 - i) + piece(b.j0, -i)));
+            in.ex_roff[j] = (int)in.ex_corr.size();
+            for (int i = 0; i < in.ex_nr[j]; ++i)
+                in.ex_corr.push_back(make_double2(piece(b.i0, i) + piece(b.i3, i - 1),
+                                                  piece(b.j0, i) + piece(b.j3, i - 1)));
         }
     }
     in.pad_l = std::max(0, -in.m_min) + 1;
@@ -900,15 +925,77 @@ int toeplitz_splits(const std::vector<Instance> &all, const std::vector<int> &me
     return (int)std::max(1L, std::min<long>({want, 16L, (long)chunks}));
 }
 
-SweepConfig toeplitz_config(const std::vector<Instance> &all, const std::vector<int> &members)
+// Windows, bands and LDS layout of a block of the exact-expectation sweep on
+// B-spline coefficients.
+struct ExactLds {
+    int lo[bsde::kMaxOrder + 1], W[bsde::kMaxOrder + 1], shift[bsde::kMaxOrder + 1], steps[bsde::kMaxOrder + 1];
+    int win[bsde::kMaxOrder + 1], band[bsde::kMaxOrder + 1], d, a, edge, part;
+    size_t total;
+};
+
+ExactLds exact_layout(const Instance &in, int G)
 {
+    ExactLds l{};
+    constexpr int T = bsde::kExactTile;
+    size_t off = 0;
+    for (int j = 1; j <= in.K; ++j) {
+        const int nb = (int)in.band[j].ec.size();
+        const int klo = in.band[j].klo - 1;  // first coefficient of the band
+        l.steps[j] = (nb + 7 + 3) / 4;
+        l.lo[j] = klo;
+        int hi = klo + 4 * l.steps[j] + T - 8;  // one past the last record a step reads
+        if (j == 1) {  // layer n+1's window holds the tile itself
+            while (l.lo[j] > -1) l.lo[j] -= 8;  // and the point before it
+            hi = std::max(hi, T);
+        }
+        l.shift[j] = klo - l.lo[j];
+        l.W[j] = hi - l.lo[j];
+        l.win[j] = (int)off;
+        off += (size_t)(l.W[j] + l.W[j] / 8 + 1) * 16;
+    }
+    for (int j = 1; j <= in.K; ++j) {
+        l.band[j] = (int)off;
+        off += align_up((size_t)2 * (4 * l.steps[j] + 8) * sizeof(double), 16);
+    }
+    l.d = (int)off;
+    off += (size_t)(l.W[1] + 2 * bsde::kHalo + 2 + bsde::kFirOver) * 16;
+    l.a = (int)off;
+    off += (size_t)(l.W[1] + 48 + bsde::kFirOver) * 16;
+    l.edge = (int)off;
+    off += (size_t)4 * in.K * 16;
+    l.part = (int)off;
+    off += (size_t)4 * G * T * 16;
+    l.total = off;
+    return l;
+}
+
+// Exact expectations: on B-spline coefficients where the windows and bands of
+// every member fit in LDS (W = 1; stability ratios up to about 40 at K = 4),
+// with a second group of four wavefronts where a tile has more than one chunk
+// of 256 taps; else the chunked sweep on values and second derivatives.
+SweepConfig toeplitz_config(const std::vector<Instance> &all, const std::vector<int> &members, size_t max_lds)
+{
+    int G = 1;
+    size_t lds = 0;
+    for (int b : members) {
+        const Instance &in = all[b];
+        int c = 0;
+        for (int j = 1; j <= in.K; ++j) {
+            if ((long)in.band[j].ec.size() > (long)(max_lds / 16)) c = 1 << 20;
+            c += bsde::toeplitz_chunks((int)in.band[j].ev.size());
+        }
+        if (c > 1) G = 2;
+        lds = c >= (1 << 20) ? max_lds + 1 : std::max(lds, exact_layout(in, 2).total);
+        if (lds > max_lds) break;
+    }
+    if (lds <= max_lds) return SweepConfig{PATH_TOEPLITZ, 1, G, lds, 1};
     return SweepConfig{PATH_TOEPLITZ, 1, toeplitz_splits(all, members), bsde::toeplitz_lds_bytes()};
 }
 
 SweepConfig default_config(const std::vector<Instance> &all, const Group &g, size_t max_lds)
 {
     if (group_gathers(all, g.members)) return SweepConfig{PATH_GATHER, 1, 1, 0};
-    if (group_exact(all, g.members)) return toeplitz_config(all, g.members);
+    if (group_exact(all, g.members)) return toeplitz_config(all, g.members, max_lds);
     const char *env = std::getenv("BSDE_SWEEP");
     if (env) {
         int P = 0, G = 1, W = 4;
@@ -930,7 +1017,9 @@ SweepConfig default_config(const std::vector<Instance> &all, const Group &g, siz
 
 int sweep_tiles(const Instance &in, const SweepConfig &c)
 {
-    const int T = c.path == PATH_FUSED ? 64 * c.P * c.W : kBlock * c.P;
+    const int T = c.path == PATH_FUSED                     ? 64 * c.P * c.W
+                  : c.path == PATH_TOEPLITZ && c.W == 1 ? bsde::kExactTile
+                                                        : kBlock * c.P;
     return (in.nx + T - 1) / T;
 }
 int tiles_of(const Instance &in, int T) { return (in.nx + T - 1) / T; }
@@ -941,7 +1030,9 @@ bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
 {
     if (c.path == PATH_FUSED && c.lds > 65536)
         HIP_OK(bsde::set_fused_lds_limit(c.P, c.W, c.G, g.f32, g.driver, c.lds));
-    if (c.path == PATH_TOEPLITZ && c.lds > 65536) HIP_OK(bsde::set_toeplitz_lds_limit());
+    const bool exact_b = c.path == PATH_TOEPLITZ && c.W == 1;  // on B-spline coefficients
+    if (exact_b && c.lds > 65536) HIP_OK(bsde::set_exact_lds_limit(c.G, c.lds));
+    if (c.path == PATH_TOEPLITZ && !exact_b && c.lds > 65536) HIP_OK(bsde::set_toeplitz_lds_limit());
     g.cfg = c;
     g.tile_prefix.assign(g.members.size() + 1, 0);
     g.spline_prefix.assign(g.members.size() + 1, 0);
@@ -954,7 +1045,41 @@ bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
         d.spline_base = g.spline_prefix[k];
         d.spline_tiles = spline_tiles(in);
         d.a.ntiles = sweep_tiles(in, c);
-        d.coef = c.path == PATH_FUSED && !in.f32 ? 1 : 0;
+        d.coef = (c.path == PATH_FUSED && !in.f32) || exact_b ? 1 : 0;
+        if (exact_b) {
+            const ExactLds l = exact_layout(in, c.G);
+            bsde::ExactHot &h = d.ex;
+            h.ring_off = d.ring_off;
+            h.band = in.d_ex_band;
+            h.corr = in.d_ex_corr;
+            h.nx = in.nx;
+            h.npad = in.npad;
+            h.pad_l = in.pad_l;
+            h.K = in.K;
+            h.n0 = d.n0;
+            h.n0_mod = d.n0 % (in.K + 1);
+            h.mod_magic = (65536 + in.K) / (in.K + 1);
+            h.tile_base = d.tile_base;
+            h.ntiles = d.a.ntiles;
+            h.lds_d = l.d;
+            h.lds_a = l.a;
+            h.lds_edge = l.edge;
+            h.lds_part = l.part;
+            for (int j = 1; j <= in.K; ++j) {
+                h.lo[j] = l.lo[j];
+                h.W[j] = l.W[j];
+                h.shift[j] = l.shift[j];
+                h.steps[j] = l.steps[j];
+                h.lds_win[j] = l.win[j];
+                h.lds_band[j] = l.band[j];
+                h.nb[j] = (int)in.band[j].ec.size();
+                h.boff[j] = in.ex_boff[j];
+                h.nl[j] = in.ex_nl[j];
+                h.nr[j] = in.ex_nr[j];
+                h.loff[j] = in.ex_loff[j];
+                h.roff[j] = in.ex_roff[j];
+            }
+        }
         if (c.path == PATH_FUSED) {
             const FusedLds l = fused_layout(in, c.P, c.W, c.G);
             const std::vector<int2> addr = fused_addresses(in, l, c.P);
@@ -1035,7 +1160,7 @@ bsde::StepArgs step_args(const bsde_plan_s &pl, const Group &g, char *ws, int s,
     a.s = s;
     a.s_mod = s % 420;
     a.stats = stats ? 1 : 0;
-    a.part = (g.cfg.path == PATH_TOEPLITZ || g.cfg.path == PATH_DIRECT) && g.cfg.G > 1
+    a.part = ((g.cfg.path == PATH_TOEPLITZ && g.cfg.W != 1) || g.cfg.path == PATH_DIRECT) && g.cfg.G > 1
                  ? reinterpret_cast<double *>(ws + g.part_off)
                  : nullptr;
     a.dsplit = g.cfg.path == PATH_DIRECT ? g.cfg.G : 1;
@@ -1060,13 +1185,15 @@ bsde_status enqueue_step(const bsde_plan_s &pl, const Group &g, char *ws, int s,
         if (c.path == PATH_GATHER)
             HIP_OK(bsde::launch_sweep_gather(g.f32, g.driver, a, blocks, st));
         else if (c.path == PATH_TOEPLITZ)
-            HIP_OK(bsde::launch_sweep_toeplitz(a, blocks, c.G, st));
+            HIP_OK(c.W == 1 ? bsde::launch_sweep_exact(a, blocks, c.G, c.lds, st)
+                            : bsde::launch_sweep_toeplitz(a, blocks, c.G, st));
         else
             HIP_OK(bsde::launch_sweep_direct(c.P, g.f32, g.driver, a, blocks, c.lds, st));
         if (tm) HIP_OK(tm->mark(tm->sweep, st));
         // natural spline of the new layer (the fused kernel does this in-kernel,
-        // and so does the split Toeplitz sweep's finishing kernel)
-        if (c.path == PATH_TOEPLITZ && c.G > 1) return BSDE_OK;
+        // and so do the Toeplitz sweep on coefficients and the split one's
+        // finishing kernel)
+        if (c.path == PATH_TOEPLITZ && (c.W == 1 || c.G > 1)) return BSDE_OK;
         if (tm) HIP_OK(tm->mark(tm->spline, st));
         HIP_OK(bsde::launch_spline(g.f32, step_args(pl, g, ws, s, false, true), 1,
                                    g.spline_prefix[act], st));
@@ -1095,8 +1222,8 @@ bsde_status enqueue_init(const bsde_plan_s &pl, char *ws, const bsde_io *io, hip
     for (const Group &g : pl.groups) {
         int kmax = 0;
         for (int b : g.members) kmax = std::max(kmax, pl.inst[b].K);
-        // fused FP64 groups keep a layer's spline by its B-spline coefficients
-        const bool coef = g.cfg.path == PATH_FUSED && !g.f32;
+        // groups that keep a layer's spline by its B-spline coefficients
+        const bool coef = pl.desc[g.members[0]].coef != 0;
         for (int r = 0; r < kmax; ++r) {
             const bsde::StepArgs a = step_args(pl, g, ws, r, false, true);
             HIP_OK(coef ? bsde::launch_coef(a, g.spline_prefix.back(), s)
@@ -1670,6 +1797,7 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         one.members = {b};
         own[b] = default_config(pl->inst, one, pl->max_lds);
         if (own[b].path == PATH_FUSED) fits[b] = fitting_shapes(pl->inst, b, pl->max_lds);
+        if (own[b].path == PATH_TOEPLITZ) fits[b] = own[b].W;
         int gi = -1;
         for (size_t k = 0; k < pl->groups.size(); ++k) {
             const Group &g = pl->groups[k];
@@ -1709,7 +1837,8 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         size_t nbw = 0;
         tbytes += align_up(kl * sizeof(int2), 256);
         for (int j = 1; j <= in.K; ++j) nbw += 4 * in.band[j].ev.size();
-        tbytes += align_up(nbw * sizeof(double), 256);
+        tbytes += align_up(nbw * sizeof(double), 256) + align_up(in.ex_band.size() * sizeof(double), 256) +
+                  align_up(in.ex_corr.size() * sizeof(double2), 256);
         tbytes += align_up(in.ctab.size() * sizeof(double), 256);
     }
     const size_t desc_off = tbytes;
@@ -1790,6 +1919,8 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
             bw.insert(bw.end(), bd.wm.begin(), bd.wm.end());
         }
         in.toep_w = static_cast<const double *>(put(bw.data(), bw.size() * sizeof(double)));
+        in.d_ex_band = static_cast<const double *>(put(in.ex_band.data(), in.ex_band.size() * sizeof(double)));
+        in.d_ex_corr = static_cast<const double2 *>(put(in.ex_corr.data(), in.ex_corr.size() * sizeof(double2)));
         if (!in.ctab.empty())
             in.d_ctab = static_cast<const double *>(put(in.ctab.data(), in.ctab.size() * sizeof(double)));
     }
@@ -1824,6 +1955,7 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
     // and split
     for (Group &g : pl->groups) {
         if (!group_exact(pl->inst, g.members)) continue;
+        if (toeplitz_config(pl->inst, g.members, pl->max_lds).W == 1) continue;
         const int S = toeplitz_splits(pl->inst, g.members);
         if (S == 1) continue;
         size_t tiles = 0;
@@ -2078,7 +2210,7 @@ bsde_status bsde_autotune(bsde_plan_t plan, void *ws, const bsde_io *io, void *s
         else
             for (const Shape &q : kShapes64) consider(q);
         if (group_gathers(plan->inst, g.members)) cand.assign(1, SweepConfig{PATH_GATHER, 1, 1, 0});
-        if (group_exact(plan->inst, g.members)) cand.assign(1, toeplitz_config(plan->inst, g.members));
+        if (group_exact(plan->inst, g.members)) cand.assign(1, toeplitz_config(plan->inst, g.members, plan->max_lds));
         if (cand.empty()) {
             cand.push_back(direct_config(plan->inst, g.members, g.f32, 1));
             cand.push_back(direct_config(plan->inst, g.members, g.f32, 2));

@@ -190,6 +190,24 @@ struct alignas(64) FusedHot {
     int mod_magic;               // ceil(2^16 / (K + 1))
 };
 
+// The same for the exact-expectation sweep on B-spline coefficients.
+struct alignas(64) ExactHot {
+    size_t ring_off;
+    const double *band;      // per layer ec, wc (nb[j] weights each) at boff[j]
+    const double2 *corr;     // per layer the end corrections (E, E[. dW]) of nl[j] points at loff[j]
+                             // (from the left end) and of nr[j] at roff[j] (from the right end)
+    int nx, npad, pad_l, K;
+    int n0, n0_mod, mod_magic, tile_base;
+    int ntiles, lds_d, lds_a, lds_edge;
+    int lds_part;
+    int lo[kMaxOrder + 1], W[kMaxOrder + 1];       // window of layer j: records t0 + lo .. + W - 1
+    int shift[kMaxOrder + 1], steps[kMaxOrder + 1];  // band start in the window (a multiple of 8), 4-tap steps
+    int nb[kMaxOrder + 1], boff[kMaxOrder + 1];
+    int lds_win[kMaxOrder + 1], lds_band[kMaxOrder + 1];
+    int nl[kMaxOrder + 1], nr[kMaxOrder + 1], loff[kMaxOrder + 1], roff[kMaxOrder + 1];
+};
+constexpr int kExactTile = 64;  // points of a block of that sweep
+
 // One instance of a (batched) solve as the kernels see it: its SweepArgs
 // with the workspace parts given as byte offsets, bound to the workspace
 // address at launch.  The kernels of one launch serve a group of instances
@@ -197,6 +215,7 @@ struct alignas(64) FusedHot {
 // instance after instance.
 struct alignas(64) InstDesc {
     FusedHot hot;         // fused sweep
+    ExactHot ex;          // exact-expectation sweep
     SweepArgs a;          // ring, fin_*, st_* unset; n unset
     size_t ring_off;      // ring of K+1 slots
     size_t fin_off;       // layer n_stop: n_x doubles of y, then of z

@@ -47,6 +47,10 @@ size_t toeplitz_lds_bytes();
 int toeplitz_chunks(int nb);  // band chunks of a layer whose band has nb taps
 hipError_t launch_sweep_toeplitz(const StepArgs &a, int tiles, int S, hipStream_t s);
 hipError_t set_toeplitz_lds_limit();
+// the same on B-spline coefficients, windows and bands of all layers in LDS:
+// kExactTile points per tile, G groups of four wavefronts share the bands
+hipError_t launch_sweep_exact(const StepArgs &a, int tiles, int G, size_t lds, hipStream_t s);
+hipError_t set_exact_lds_limit(int G, size_t lds);
 // mode 0: initial layer s of every instance; mode 1: layer n0 - s (direct path)
 hipError_t launch_spline(bool f32, const StepArgs &a, int mode, int blocks, hipStream_t s);
 // B-spline coefficients of initial layer s of every instance (FP64 fused groups)

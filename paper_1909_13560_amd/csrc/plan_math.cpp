@@ -199,9 +199,12 @@ bool gaussian_spline_band(double m0, double rho, double h, double dx, GaussBand 
     out.em.assign(nb, 0.0);
     out.wv.assign(nb, 0.0);
     out.wm.assign(nb, 0.0);
+    out.ec.assign(nb + 2, 0.0);  // coefficients dlo - 1 .. dhi + 2
+    out.wc.assign(nb + 2, 0.0);
+    for (std::vector<double> *v : {&out.i0, &out.i3, &out.j0, &out.j3}) v->assign(dhi - dlo + 1, 0.0);
     const double inv_sqrt_2pi = 0.39894228040143267794, dx26 = dx * dx / 6.0;
     for (int dd = dlo; dd <= dhi; ++dd) {
-        double I[4] = {0, 0, 0, 0}, J[4] = {0, 0, 0, 0};
+        double I[4] = {0, 0, 0, 0}, J[4] = {0, 0, 0, 0}, P[4] = {0, 0, 0, 0}, Q[4] = {0, 0, 0, 0};
         for (int q = 0; q < nsub; ++q)
             for (int g = 0; g < kGl; ++g) {
                 const double th = (q + gx[g]) / nsub;
@@ -213,6 +216,13 @@ bool gaussian_spline_band(double m0, double rho, double h, double dx, GaussBand 
                     I[k] += dens * b[k];
                     J[k] += dens * b[k] * h * xi;
                 }
+                // the cubic B-spline's pieces on the cell
+                const double bs[4] = {u * u * u / 6.0, 2.0 / 3.0 - 0.5 * th * th * (2.0 - th),
+                                      2.0 / 3.0 - 0.5 * u * u * (2.0 - u), th * th * th / 6.0};
+                for (int k = 0; k < 4; ++k) {
+                    P[k] += dens * bs[k];
+                    Q[k] += dens * bs[k] * h * xi;
+                }
             }
         const int k0 = dd - dlo;  // left record of the cell; the right one is k0 + 1
         out.ev[k0] += I[0];
@@ -223,6 +233,14 @@ bool gaussian_spline_band(double m0, double rho, double h, double dx, GaussBand 
         out.wv[k0 + 1] += J[1];
         out.wm[k0] += J[2];
         out.wm[k0 + 1] += J[3];
+        for (int k = 0; k < 4; ++k) {  // cell d reads the coefficients d - 1 .. d + 2
+            out.ec[k0 + k] += P[k];
+            out.wc[k0 + k] += Q[k];
+        }
+        out.i0[k0] = P[0];
+        out.i3[k0] = P[3];
+        out.j0[k0] = Q[0];
+        out.j3[k0] = Q[3];
     }
     return true;
 }

@@ -28,9 +28,18 @@ bool gauss_legendre01(int n, double *x, double *w);
 // value and M = 0 (so the mass outside the truncated domain goes to the
 // boundary values).  Cells more than 9 rho + 1 from m0 are left out (mass
 // below 1e-18).
+// The same operator on the spline's B-spline coefficients c (values v = (c_- +
+// 4 c + c_+) / 6):
+//   E[v(X)] = sum_k ec[k] c_{i+klo-1+k},  E[v(X) h xi] = sum_k wc[k] c_{i+klo-1+k},
+// k = 0 .. nb+1.  i0, i3 (and j0, j3 for the dW-weighted form) are the shares of
+// the first and the last cubic piece of the basis function on cell klo + d: with
+// coefficients continued as constants beyond the grid, the clamped expectation
+// at grid point i is the sum above less (c_1 - c_0) (i3 on cell -1 + i0 on cell
+// 0) and (c_{n-2} - c_{n-1}) (i0 on cell n-1 + i3 on cell n-2).
 struct GaussBand {
     int klo = 0;
     std::vector<double> ev, em, wv, wm;
+    std::vector<double> ec, wc, i0, i3, j0, j3;
 };
 bool gaussian_spline_band(double m0, double rho, double h, double dx, GaussBand &out);
 

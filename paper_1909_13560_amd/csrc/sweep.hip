@@ -275,6 +275,44 @@ __global__ void __launch_bounds__(kBlock) spline_layer(const StepArgs s, int mod
     }
 }
 
+// B-spline coefficients of the initial layers of the instances of a group
+// (layer n0 + 1 + s), with their ghost records.
+__global__ void __launch_bounds__(kBlock) coef_layer(const StepArgs s)
+{
+    constexpr int W = kSplineTile + 2;  // records t0 - 1 .. t0 + kSplineTile
+    __shared__ double2 D[W + 2 * kHalo + 2 + kFirOver], A[W + 48 + kFirOver];
+    const int idx = xcd_tile(blockIdx.x, gridDim.x);
+    const InstDesc &d = block_desc(s, idx);
+    const SweepArgs a = bind_instance(d, s.ws, 0, false);
+    if (s.s >= a.K) return;
+    const int tile = idx - d.spline_base, t0 = tile * kSplineTile, nx = a.nx, tid = threadIdx.x;
+    const Slot<false> g = ring_slot<false>(a, d.n0 + 1 + s.s);
+    const double2 end0 = layer_value(g, 0), end1 = layer_value(g, nx - 1);
+    for (int e = tid; e < W + 2 * kHalo + 2; e += kBlock) {
+        const int k = t0 - 2 - kHalo + e;
+        D[e] = reflected_value(nx, k, layer_value(g, reflected_index(nx, k)), end0, end1);
+    }
+    __syncthreads();
+    fir_pass_a<kBlock, 3>(W, D, A);
+    __syncthreads();
+    const double inv_b = a.pcr.inv_b;
+    fir_pass_b<kBlock, 2>(W, A, [&](int e, double wy, double wz) {
+        const int k = t0 - 1 + e;
+        const bool own = (k >= t0 && k < min(t0 + kSplineTile, nx)) || k == -1 ||
+                         (k == nx && tile == d.spline_tiles - 1);
+        const double2 v = D[e + kHalo + 1];
+        if (own) g.set_der(k, fma(-inv_b, wy, v.x), fma(-inv_b, wz, v.y));
+    });
+    if (tile == 0) {
+        const double2 e0 = g.val(0);
+        for (int k = -2 - tid; k >= -a.pad_l; k -= kBlock) g.set_der(k, e0.x, e0.y);
+    }
+    if (tile == d.spline_tiles - 1) {
+        const double2 e1 = g.val(nx - 1);
+        for (int k = nx + 1 + tid; k < nx + a.pad_r; k += kBlock) g.set_der(k, e1.x, e1.y);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Input / output / statistics kernels
 // ---------------------------------------------------------------------------

@@ -27,6 +27,7 @@
 // adds them in a fixed order (deterministic), finishes the points and builds
 // the new layer's spline.
 #include "device_common.h"
+#include "fused.h"
 #include "kernels.h"
 
 namespace bsde {
@@ -402,6 +403,255 @@ __global__ void __launch_bounds__(256) toeplitz_finish(const StepArgs s, int S)
             g.set_der(a.nx + k, 0.0, 0.0);
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// The same operator on B-spline coefficients, one launch per step.  The spline
+// of a layer is one coefficient pair (c_y, c_z) per point, so the four bands
+// above become two (expectation and dW-weighted) and the products halve.  A
+// block takes 64 points: the 16 x 16 product's rows are the two bands at 8
+// consecutive points, its columns 8 groups of 8 points of c_y and of c_z, so
+// one instruction per four taps gives E[y], E[z], E[y dW] and E[z dW] of the
+// tile, and a 16384-point grid fills the chip without splitting a band over
+// blocks.  Row r = 4 i + lane / 16 (the accumulator layout) holds band i / 2 at
+// point 2 (lane / 16) + i % 2 of the group.  The block stages every layer's
+// window and band in LDS, builds layer n+1's coefficients as the fused sweep
+// does, and its wavefronts take every (4 G)-th step of a layer's band.
+// Coefficients beyond the grid continue as constants; the expectations of the
+// points within reach of an end are corrected in the finish (GaussBand).
+// Per step on 16384 points, R = 16, K = 4: 23.4 -> 11.6 us (two launches -> one);
+// the matrix products need 2.4 us of it, the loads, the spline's passes and the
+// launch the rest.
+// ---------------------------------------------------------------------------
+template <int G>
+__global__ void __launch_bounds__(256 * G) sweep_exact(const StepArgs s)
+{
+    constexpr int T = kExactTile, NT = 256 * G, NW = 4 * G;
+    constexpr int kU = 2;
+    extern __shared__ char smem_exact[];
+    char *smem = smem_exact;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int idx = xcd_tile(blockIdx.x, gridDim.x);
+    const InstDesc &d = block_desc(s, idx);
+    const ExactHot h = d.ex;
+    asm volatile("" ::"s"(h.nx), "s"(h.npad), "s"(h.lo[1]), "s"(h.W[kMaxOrder]), "s"(h.lds_win[1]),
+                 "s"(h.lds_band[kMaxOrder]), "s"(h.boff[1]));
+    const int K = h.K, nx = h.nx, tile = idx - h.tile_base, t0 = tile * T;
+    double2 *D = reinterpret_cast<double2 *>(smem + h.lds_d);
+    double2 *A = reinterpret_cast<double2 *>(smem + h.lds_a);
+    double2 *edge = reinterpret_cast<double2 *>(smem + h.lds_edge);  // per layer c_0, c_1, c_{n-2}, c_{n-1}
+    const int KP = K + 1, q0 = (int)((unsigned)(s.s_mod * h.mod_magic) >> 16);
+    int nmod = h.n0_mod - (s.s_mod - q0 * KP);
+    if (nmod < 0) nmod += KP;
+    char *ring = s.ws + h.ring_off;
+    auto slot = [&](int j) {
+        const int r = nmod + j >= KP ? nmod + j - KP : nmod + j;
+        char *base = ring + (size_t)r * ((size_t)2 * h.npad * sizeof(double2));
+        return Slot<false>{base, base + (size_t)h.npad * sizeof(double2), h.pad_l};
+    };
+    auto slot8 = [](int e) { return e + (e >> 3); };  // a pad slot per eight records
+    const Slot<false> g1 = slot(1);
+    const int W1 = h.W[1], r1 = t0 + h.lo[1], WS = W1 + 2 * kHalo + 2, s0 = r1 - kHalo - 1;
+    const bool ends = s0 < 0 || s0 + WS > nx;
+    double2 raw[kU], pre[kMaxOrder - 1][kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+        const int e = tid + u * NT;
+        if (e < WS) raw[u] = layer_value(g1, ends ? reflected_index(nx, s0 + e) : s0 + e);
+    }
+    const double2 end0 = layer_value(g1, 0), end1 = layer_value(g1, nx - 1);
+#pragma unroll
+    for (int jj = 0; jj < kMaxOrder - 1; ++jj) {
+        const int j = jj + 2;
+        if (j <= K) {
+            const Slot<false> g = slot(j);
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int e = tid + u * NT;
+                if (e < h.W[j]) pre[jj][u] = g.der(min(max(t0 + h.lo[j] + e, 0), nx - 1));
+            }
+        }
+    }
+    double2 ev;  // end coefficients of the layers n+2 .. n+K
+    if (tid >= 4 && tid < 4 * K) {
+        const int k = tid & 3;
+        ev = slot(1 + (tid >> 2)).der(k < 2 ? k : nx - 4 + k);
+    }
+    warm_scalar(&d, sizeof(InstDesc), wave, NW);
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+        const int e = tid + u * NT;
+        if (e < WS) D[e] = ends ? reflected_value(nx, s0 + e, raw[u], end0, end1) : raw[u];
+    }
+    for (int e = tid + kU * NT; e < WS; e += NT) {
+        const double2 v = layer_value(g1, ends ? reflected_index(nx, s0 + e) : s0 + e);
+        D[e] = ends ? reflected_value(nx, s0 + e, v, end0, end1) : v;
+    }
+    __syncthreads();
+    fir_pass_a<NT, 1>(W1, D, A);
+    // the bands, with seven zeros before (the rows' shifts) and zeros up to the
+    // last step's taps
+#pragma unroll
+    for (int jj = 0; jj < kMaxOrder; ++jj) {
+        const int j = jj + 1;
+        if (j <= K) {
+            const int len = 4 * h.steps[j] + 8, nb = h.nb[j];
+            double *w = reinterpret_cast<double *>(smem + h.lds_band[j]);
+            const double *src = h.band + h.boff[j];
+            for (int e = tid; e < 2 * len; e += NT) {
+                const int b = e >= len ? 1 : 0, k = e - b * len - 7;
+                w[e] = k >= 0 && k < nb ? src[b * nb + k] : 0.0;
+            }
+        }
+    }
+    __syncthreads();
+    double2 *w1 = reinterpret_cast<double2 *>(smem + h.lds_win[1]);
+    {
+        const double inv_b = const_load(&d.a.pcr.inv_b);
+        fir_pass_b<NT, 1>(W1, A, [&](int e, double wy, double wz) {
+            const double2 v = D[e + kHalo + 1];
+            const int k = r1 + e;
+            double2 c = make_double2(fma(-inv_b, wy, v.x), fma(-inv_b, wz, v.y));
+            if (k < 0) c = end0;
+            if (k >= nx) c = end1;
+            w1[slot8(e)] = c;
+        });
+    }
+#pragma unroll
+    for (int jj = 0; jj < kMaxOrder - 1; ++jj) {
+        const int j = jj + 2;
+        if (j <= K) {
+            const Slot<false> g = slot(j);
+            double2 *w = reinterpret_cast<double2 *>(smem + h.lds_win[j]);
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int e = tid + u * NT;
+                if (e < h.W[j]) w[slot8(e)] = pre[jj][u];
+            }
+            for (int e = tid + kU * NT; e < h.W[j]; e += NT)
+                w[slot8(e)] = g.der(min(max(t0 + h.lo[j] + e, 0), nx - 1));
+        }
+    }
+    if (tid >= 4 && tid < 4 * K) edge[tid] = ev;
+    __syncthreads();
+    // layer n+1's coefficients: the tile's to HBM, the end ones for the
+    // corrections (blocks within reach of an end hold them in their window)
+    for (int k = t0 + tid; k < min(t0 + T, nx); k += NT) {
+        const double2 c = w1[slot8(k - r1)];
+        g1.set_der(k, c.x, c.y);
+    }
+    if (tid < 4) {
+        const int k = tid < 2 ? tid : nx - 4 + tid;
+        if (k >= r1 && k < r1 + W1) edge[tid] = w1[slot8(k - r1)];
+    }
+    // the banded products
+    const int lr = lane & 15, lk = lane >> 4, f = lr & 1;
+    const int aband = lr >> 3, apt = 2 * (lr & 3) + ((lr >> 2) & 1);  // row lr: band, point
+    double Y[2] = {0.0, 0.0}, Z[2] = {0.0, 0.0};
+#pragma unroll 1
+    for (int j = K; j >= 1; --j) {
+        const ExactHot &x = d.ex;
+        const int steps = const_load(&x.steps[j]), len = 4 * steps + 8, sh = const_load(&x.shift[j]);
+        const double *bw = reinterpret_cast<const double *>(smem + const_load(&x.lds_band[j])) +
+                           aband * len + 7 - apt + lk;
+        const double *rec = reinterpret_cast<const double *>(smem + const_load(&x.lds_win[j])) +
+                            2 * (sh + (sh >> 3) + 9 * (lr >> 1) + lk) + f;
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+        for (int q = wave; q < steps; q += NW)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(bw[4 * q], rec[2 * (4 * q + (q >> 1))], acc, 0, 0, 0);
+        // this lane: E at points 2 lk, 2 lk + 1 of its group in acc[0], acc[1],
+        // E[. dW] in acc[2], acc[3], of y (f = 0) or z (f = 1)
+        const ToepTable &t = d.a.toep;
+        const double ye = f ? const_load(&t.cy_ez[j]) : const_load(&t.cy_ey[j]);
+        const double ze = f ? const_load(&t.cz_ez[j]) : 0.0;
+        const double zw = f ? const_load(&t.cz_wz[j]) : const_load(&t.cz_wy[j]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            Y[i] = fma(ye, acc[i], Y[i]);
+            Z[i] = fma(ze, acc[i], fma(zw, acc[2 + i], Z[i]));
+        }
+    }
+    double2 *part = reinterpret_cast<double2 *>(smem + h.lds_part);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double y = Y[i] + __shfl_xor(Y[i], 1, 64), z = Z[i] + __shfl_xor(Z[i], 1, 64);
+        if (f == 0) part[wave * T + 8 * (lr >> 1) + 2 * lk + i] = make_double2(y, z);
+    }
+    __syncthreads();
+    if (tid >= T) return;
+    const int i = t0 + tid;
+    const bool valid = i < nx;
+    double Yc = 0.0, Zc = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const double2 v = part[w * T + tid];
+        Yc += v.x;
+        Zc += v.y;
+    }
+    const SweepArgs &r = d.a;
+    for (int j = 1; j <= K; ++j) {
+        const ToepTable &t = r.toep;
+        const int nl = const_load(&d.ex.nl[j]), nr = const_load(&d.ex.nr[j]);
+        Yc += const_load(&t.cy_1[j]);
+        auto correct = [&](const double2 &k, const double2 &in, const double2 &out) {
+            const double ey = in.x - out.x, ez = in.y - out.y;
+            Yc -= k.x * (const_load(&t.cy_ey[j]) * ey + const_load(&t.cy_ez[j]) * ez);
+            Zc -= k.x * const_load(&t.cz_ez[j]) * ez +
+                  k.y * (const_load(&t.cz_wy[j]) * ey + const_load(&t.cz_wz[j]) * ez);
+        };
+        const double2 *e = edge + 4 * (j - 1);
+        if (i < nl) correct(h.corr[const_load(&d.ex.loff[j]) + i], e[1], e[0]);
+        const int q = nx - 1 - i;
+        if (q >= 0 && q < nr) correct(h.corr[const_load(&d.ex.roff[j]) + q], e[2], e[3]);
+    }
+    SweepArgs fa{};
+    fa.drv.p0 = const_load(&r.drv.p0);
+    fa.drv.p1 = const_load(&r.drv.p1);
+    fa.drv.p3 = const_load(&r.drv.p3);
+    fa.h0 = const_load(&r.h0);
+    fa.picard_max = const_load(&r.picard_max);
+    fa.picard_tol = const_load(&r.picard_tol);
+    const Driver<BSDE_DRIVER_LINEAR, double> f0(fa.drv, 0.0);
+    unsigned int it = 0;
+    bool conv = true;
+    if (valid) {
+        const double y = picard_solve(fa, f0, D[i - s0].x, Yc, Zc, it, conv);
+        slot(0).set_val(i, y, Zc);
+        if (h.n0 - s.s == const_load(&r.n_stop)) {
+            double *fin_y = reinterpret_cast<double *>(s.ws + const_load(&d.fin_off));
+            fin_y[i] = y;
+            fin_y[nx + i] = Zc;
+        }
+    }
+    if (s.stats) {
+        const unsigned int itm = wave_max_u32(it), its = wave_sum_u32(it), nc = wave_sum_u32(conv ? 0u : 1u);
+        if (lane == 0) {
+            const int w = t0 >> 6, nw = const_load(&d.nwaves);
+            unsigned long long *sum = reinterpret_cast<unsigned long long *>(s.ws + const_load(&d.stat_off));
+            unsigned int *mx = reinterpret_cast<unsigned int *>(sum + 2 * nw);
+            mx[w] = max(mx[w], itm);
+            sum[w] += its;
+            sum[nw + w] += nc;
+        }
+    }
+}
+
+hipError_t launch_sweep_exact(const StepArgs &a, int tiles, int G, size_t lds, hipStream_t s)
+{
+    if (G == 1)
+        hipLaunchKernelGGL(sweep_exact<1>, dim3(tiles), dim3(256), lds, s, a);
+    else
+        hipLaunchKernelGGL(sweep_exact<2>, dim3(tiles), dim3(512), lds, s, a);
+    return hipGetLastError();
+}
+
+hipError_t set_exact_lds_limit(int G, size_t lds)
+{
+    return hipFuncSetAttribute(G == 1 ? reinterpret_cast<const void *>(&sweep_exact<1>)
+                                      : reinterpret_cast<const void *>(&sweep_exact<2>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
 hipError_t launch_sweep_toeplitz(const StepArgs &a, int tiles, int S, hipStream_t s)
