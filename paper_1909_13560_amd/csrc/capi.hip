@@ -55,6 +55,7 @@ struct Instance {
     double R;
     bool f32;
     bool gather;  // state-dependent forward coefficients: nodes located per point
+    bool located = false;  // of these, with node windows that the fused sweep can stage (FP64)
     bool exact;   // exact Gaussian expectations (banded Toeplitz operators)
     std::vector<double> ctab;          // tabulated forward coefficients (host copy)
     const double *d_ctab = nullptr;    // and on the device
@@ -295,6 +296,48 @@ bool supported_2d(const bsde_problem &p)
            (p.interp == BSDE_INTERP_SPLINE || (p.n_x[0] >= 5 && p.n_x[1] >= 5));
 }
 
+// Window bounds of every layer for state-dependent coefficients: the nodes of
+// grid point i sit (a(t, x_i) j dt + b(t, x_i) dW) / dx cells away with b > 0,
+// so the extremes over the grid (and the table's rows) of the outermost
+// nodes, one cell wider for rounding.  gh: Gauss-Hermite nodes.  Bounds far
+// beyond any LDS window leave the instance to the kernel that reads HBM.
+void located_windows(const bsde_problem &p, Instance &in, const double *gh)
+{
+    double glo = gh[0], ghi = gh[0];
+    for (int l = 1; l < p.L; ++l) {
+        glo = std::min(glo, gh[l]);
+        ghi = std::max(ghi, gh[l]);
+    }
+    std::vector<int> lo(in.K + 1, 0), hi(in.K + 1, 0);
+    for (int j = 1; j <= in.K; ++j) {
+        const double t = j * in.dt / in.dx, sq = std::sqrt(2.0 * j * in.dt) / in.dx;
+        double mn = 1e300, mx = -1e300;
+        auto point = [&](double a, double b) {
+            mn = std::min(mn, std::min(a * t + b * sq * glo, a * t + b * sq * ghi));
+            mx = std::max(mx, std::max(a * t + b * sq * glo, a * t + b * sq * ghi));
+        };
+        if (p.tab_steps > 0) {
+            for (int r = 0; r < p.tab_steps; ++r) {
+                const double *ta = p.coef_tab + (size_t)2 * r * in.nx, *tb = ta + in.nx;
+                for (int i = 0; i < in.nx; ++i) point(ta[i], tb[i]);
+            }
+        } else {  // affine: the extremes lie at the grid's ends
+            for (double x : {p.x_min[0], p.x_max[0]})
+                point(p.drift[0] + p.drift_x * x, p.vol[0][0] + p.vol_x * x);
+        }
+        if (!(mn > -4000.0) || !(mx < 4000.0)) return;
+        lo[j] = std::min((int)std::floor(mn) - 1, 0);
+        hi[j] = std::max((int)std::floor(mx) + 1, 0);
+    }
+    in.located = true;
+    in.win_lo = lo;
+    in.win_hi = hi;
+    for (int j = 1; j <= in.K; ++j) {
+        in.m_min = std::min(in.m_min, lo[j]);
+        in.m_max = std::max(in.m_max, hi[j]);
+    }
+}
+
 // Node tables of eq (20)-(21) on the uniform grid (Section 3.2): the node
 // x_i + drift j dt + vol sqrt(2 j dt) a_l sits s = (drift j dt + vol sqrt(2 j dt) a_l)/dx
 // cells from x_i, independent of i; s = m + phi with integer m.  The weights
@@ -385,6 +428,7 @@ bool build_instance(const bsde_problem &p, Instance &in)
         in.m_max = std::max(in.m_max, hi);
     }
     in.h0 = p.k_y * in.dt * gy[0];
+    if (in.gather && !in.f32 && p.z_form == BSDE_ZFORM_EZ) located_windows(p, in, a);
     if (in.exact) {
         // exact Gaussian expectations: the band of every layer; the ghosts
         // cover the band and the Toeplitz kernel's window overhang
@@ -734,7 +778,7 @@ SweepConfig fused_config(const std::vector<Instance> &all, const std::vector<int
     for (int b : members) {
         const Instance &in = all[b];
         // the fused kernel serves the E[z] form of the z equation only
-        if (in.gather || in.exact || in.pb.z_form != BSDE_ZFORM_EZ || in.pb.L > 64) return c;
+        if ((in.gather && !in.located) || in.exact || in.pb.z_form != BSDE_ZFORM_EZ || in.pb.L > 64) return c;
         // node offsets beyond any window that could fit (and int arithmetic)
         if ((long)in.m_max - in.m_min > (long)(max_lds / 16)) return c;
         // FP32 form: wider reaches stay on the direct kernel (its sums, in
@@ -773,7 +817,9 @@ std::vector<int2> fused_addresses(const Instance &in, const FusedLds &lds, int P
             const int m = in.m[(j - 1) * L + l], off = m - in.win_lo[j];
             const int slot = P % 2 == 0 ? off + off / P : off;
             const int at = in.f32 ? (j - 1) * L + l : fused_position(in.K, L, j, l);
-            v[at] = make_int2((lds.win[j] + 16 * slot) | (off % P), m * 16 + j);
+            // (located nodes: the address of the record of the tile's first point)
+            v[at] = in.located ? make_int2(lds.win[j] - 16 * (in.win_lo[j] - 1), j)
+                               : make_int2((lds.win[j] + 16 * slot) | (off % P), m * 16 + j);
         }
     return v;
 }
@@ -992,9 +1038,30 @@ SweepConfig toeplitz_config(const std::vector<Instance> &all, const std::vector<
     return SweepConfig{PATH_TOEPLITZ, 1, toeplitz_splits(all, members), bsde::toeplitz_lds_bytes()};
 }
 
+constexpr size_t kLocatedLds = 131072;
+
+// State-dependent coefficients: in the fused sweep (W = 1) where every member
+// is double precision and a block's windows take at most 128 KB of LDS, else
+// from HBM/L2.  Measured (bid-ask, K = 4, L = 16, N = 128; fused against HBM/L2
+// per solve): 59 KB 0.83 ms, 100 KB 0.96 against 4.38 ms and 139 KB 1.13 against
+// 4.35 ms on 2001 points; on 60000 points 3.14 against 4.14 and 3.63 against
+// 4.21 ms.  The widest windows keep the kernel whose separate spline launches
+// show in the launch counts of bsde_profile_kernels.
+SweepConfig gather_config(const std::vector<Instance> &all, const std::vector<int> &members, size_t max_lds)
+{
+    bool ok = true;
+    for (int b : members) ok = ok && all[b].located;
+    if (ok) {
+        SweepConfig c = fused_config(all, members, 1, 1, 8, max_lds);
+        c.path = PATH_GATHER;
+        if (c.lds && c.lds <= kLocatedLds) return c;
+    }
+    return SweepConfig{PATH_GATHER, 1, 1, 0};
+}
+
 SweepConfig default_config(const std::vector<Instance> &all, const Group &g, size_t max_lds)
 {
-    if (group_gathers(all, g.members)) return SweepConfig{PATH_GATHER, 1, 1, 0};
+    if (group_gathers(all, g.members)) return gather_config(all, g.members, max_lds);
     if (group_exact(all, g.members)) return toeplitz_config(all, g.members, max_lds);
     const char *env = std::getenv("BSDE_SWEEP");
     if (env) {
@@ -1017,9 +1084,10 @@ SweepConfig default_config(const std::vector<Instance> &all, const Group &g, siz
 
 int sweep_tiles(const Instance &in, const SweepConfig &c)
 {
-    const int T = c.path == PATH_FUSED                     ? 64 * c.P * c.W
+    const bool located = c.path == PATH_GATHER && c.W == 1;
+    const int T = c.path == PATH_FUSED || located ? 64 * c.P * c.W
                   : c.path == PATH_TOEPLITZ && c.W == 1 ? bsde::kExactTile
-                                                        : kBlock * c.P;
+                                                         : kBlock * c.P;
     return (in.nx + T - 1) / T;
 }
 int tiles_of(const Instance &in, int T) { return (in.nx + T - 1) / T; }
@@ -1031,6 +1099,8 @@ bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
     if (c.path == PATH_FUSED && c.lds > 65536)
         HIP_OK(bsde::set_fused_lds_limit(c.P, c.W, c.G, g.f32, g.driver, c.lds));
     const bool exact_b = c.path == PATH_TOEPLITZ && c.W == 1;  // on B-spline coefficients
+    const bool located = c.path == PATH_GATHER && c.W == 1;    // in the fused sweep
+    if (located && c.lds > 65536) HIP_OK(bsde::set_located_lds_limit(g.driver, c.lds));
     if (exact_b && c.lds > 65536) HIP_OK(bsde::set_exact_lds_limit(c.G, c.lds));
     if (c.path == PATH_TOEPLITZ && !exact_b && c.lds > 65536) HIP_OK(bsde::set_toeplitz_lds_limit());
     g.cfg = c;
@@ -1045,7 +1115,7 @@ bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
         d.spline_base = g.spline_prefix[k];
         d.spline_tiles = spline_tiles(in);
         d.a.ntiles = sweep_tiles(in, c);
-        d.coef = (c.path == PATH_FUSED && !in.f32) || exact_b ? 1 : 0;
+        d.coef = (c.path == PATH_FUSED && !in.f32) || exact_b || located ? 1 : 0;
         if (exact_b) {
             const ExactLds l = exact_layout(in, c.G);
             bsde::ExactHot &h = d.ex;
@@ -1080,7 +1150,7 @@ bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
                 h.roff[j] = in.ex_roff[j];
             }
         }
-        if (c.path == PATH_FUSED) {
+        if (c.path == PATH_FUSED || located) {
             const FusedLds l = fused_layout(in, c.P, c.W, c.G);
             const std::vector<int2> addr = fused_addresses(in, l, c.P);
             HIP_OK(hipMemcpy(in.d_addr, addr.data(), addr.size() * sizeof(int2), hipMemcpyHostToDevice));
@@ -1183,7 +1253,8 @@ bsde_status enqueue_step(const bsde_plan_s &pl, const Group &g, char *ws, int s,
         if (tm) HIP_OK(tm->mark(tm->sweep, st));
     } else {
         if (c.path == PATH_GATHER)
-            HIP_OK(bsde::launch_sweep_gather(g.f32, g.driver, a, blocks, st));
+            HIP_OK(c.W == 1 ? bsde::launch_sweep_located(g.driver, a, blocks, c.lds, st)
+                            : bsde::launch_sweep_gather(g.f32, g.driver, a, blocks, st));
         else if (c.path == PATH_TOEPLITZ)
             HIP_OK(c.W == 1 ? bsde::launch_sweep_exact(a, blocks, c.G, c.lds, st)
                             : bsde::launch_sweep_toeplitz(a, blocks, c.G, st));
@@ -1194,6 +1265,7 @@ bsde_status enqueue_step(const bsde_plan_s &pl, const Group &g, char *ws, int s,
         // and so do the Toeplitz sweep on coefficients and the split one's
         // finishing kernel)
         if (c.path == PATH_TOEPLITZ && (c.W == 1 || c.G > 1)) return BSDE_OK;
+        if (c.path == PATH_GATHER && c.W == 1) return BSDE_OK;
         if (tm) HIP_OK(tm->mark(tm->spline, st));
         HIP_OK(bsde::launch_spline(g.f32, step_args(pl, g, ws, s, false, true), 1,
                                    g.spline_prefix[act], st));
@@ -1797,7 +1869,7 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         one.members = {b};
         own[b] = default_config(pl->inst, one, pl->max_lds);
         if (own[b].path == PATH_FUSED) fits[b] = fitting_shapes(pl->inst, b, pl->max_lds);
-        if (own[b].path == PATH_TOEPLITZ) fits[b] = own[b].W;
+        if (own[b].path == PATH_TOEPLITZ || own[b].path == PATH_GATHER) fits[b] = own[b].W;
         int gi = -1;
         for (size_t k = 0; k < pl->groups.size(); ++k) {
             const Group &g = pl->groups[k];
@@ -1889,6 +1961,10 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
             rb.b1 = 2.0 / 3.0 - 0.5 * ph * ph * (2.0 - ph);
             rb.b2 = 2.0 / 3.0 - 0.5 * u * u * (2.0 - u);
             rb.b3 = ph * ph * ph / 6.0;
+            if (in.located) {  // located nodes: the increments in cells
+                rb.b0 = in.dw[k] / in.dx;
+                rb.b1 = j * in.dt / in.dx;
+            }
             if (in.pb.driver == BSDE_DRIVER_LINEAR) {
                 rb.w0 = in.cfy[k] * in.pb.p[0] + cy;
                 rb.w1 = in.cfy[k] * in.pb.p[1];
@@ -2209,7 +2285,7 @@ bsde_status bsde_autotune(bsde_plan_t plan, void *ws, const bsde_io *io, void *s
             for (const Shape &q : kShapes32) consider(q);
         else
             for (const Shape &q : kShapes64) consider(q);
-        if (group_gathers(plan->inst, g.members)) cand.assign(1, SweepConfig{PATH_GATHER, 1, 1, 0});
+        if (group_gathers(plan->inst, g.members)) cand.assign(1, gather_config(plan->inst, g.members, plan->max_lds));
         if (group_exact(plan->inst, g.members)) cand.assign(1, toeplitz_config(plan->inst, g.members, plan->max_lds));
         if (cand.empty()) {
             cand.push_back(direct_config(plan->inst, g.members, g.f32, 1));

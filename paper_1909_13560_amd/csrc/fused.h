@@ -393,6 +393,68 @@ __device__ inline void class_nodes(const char *lane, const double2 *edge, const 
     }
 }
 
+// The nodes of one class for state-dependent coefficients (one point per
+// lane): the node of (j, l) sits s = i + (a(x_i) j dt + b(x_i) dW_l) / dx cells
+// along the grid, so each lane locates its cell, forms the B-spline weights at
+// its fraction and reads its four records.  Clamping s to the grid gives the
+// boundary value beyond the ends: the natural spline ends at its end values.
+// recs: b0 = dW / dx, b1 = j dt / dx; av.x: LDS address of the record of grid
+// point t0; base: the block's LDS.
+template <int DRV>
+__device__ inline void gather_nodes(const char *base, const NodeRecB *recs, int cnt, const int2 &av,
+                                    const SweepArgs &a, const double *drv, double pos, double ax, double bx,
+                                    int t0, int nx, double &Y, double &Z)
+{
+    const Driver<DRV, double> f = make_driver<DRV, double>(a, drv);
+    const double top = nx - 1.0;
+    auto fetch = [&](int k, const NodeRecB &c, double2 (&r)[4], double &ph) {
+        const double s = fmin(fmax(fma(bx, c.b0, fma(ax, c.b1, pos)), 0.0), top);
+        const int p = min((int)s, nx - 2);
+        ph = s - p;
+        const double2 *q =
+            reinterpret_cast<const double2 *>(base + __builtin_amdgcn_readlane(av.x, k) + 16 * (p - 1 - t0));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = q[i];
+    };
+    auto node = [&](int k, const NodeRecB &c, const double2 (&r)[4], double ph) {
+        const double u = 1.0 - ph, p2 = ph * ph, u2 = u * u;
+        const double b0 = u2 * u * (1.0 / 6.0), b3 = p2 * ph * (1.0 / 6.0);
+        const double b1 = fma(-0.5 * p2, 2.0 - ph, 2.0 / 3.0), b2 = fma(-0.5 * u2, 1.0 + ph, 2.0 / 3.0);
+        const double yh = fma(b3, r[3].x, fma(b0, r[0].x, fma(b2, r[2].x, b1 * r[1].x)));
+        const double zh = fma(b3, r[3].y, fma(b0, r[0].y, fma(b2, r[2].y, b1 * r[1].y)));
+        if constexpr (DRV == BSDE_DRIVER_LINEAR) {
+            Y = fma(c.w0, yh, fma(c.w1, zh, Y));
+            Z = fma(c.w2, yh, fma(c.w3, zh, Z));
+        } else {
+            const Driver<DRV, double> fj =
+                DRV == BSDE_DRIVER_EXP
+                    ? make_driver<DRV, double>(a, drv + 3 * (__builtin_amdgcn_readlane(av.y, k) & 15))
+                    : f;
+            const double fh = fj(yh, zh);
+            Y = fma(c.w0, fh, fma(c.w3, yh, Y));
+            Z = fma(c.w1, fh, fma(c.w2, zh, Z));
+        }
+    };
+    int k = 0;
+#pragma unroll 1
+    for (; k + 1 < cnt; k += 2) {
+        const NodeRecB ca = load_node(recs + k), cb = load_node(recs + k + 1);
+        double2 ra[4], rb[4];
+        double pa, pb;
+        fetch(k, ca, ra, pa);
+        fetch(k + 1, cb, rb, pb);
+        node(k, ca, ra, pa);
+        node(k + 1, cb, rb, pb);
+    }
+    if (k < cnt) {
+        const NodeRecB ca = load_node(recs + k);
+        double2 ra[4];
+        double pa;
+        fetch(k, ca, ra, pa);
+        node(k, ca, ra, pa);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // The sweep kernel.  Sums: the FP64 form adds the nodes of class l mod 8 over
 // the layers K, ..., 2, 1 in each of eight classes; the classes k and k + 4,
@@ -407,9 +469,11 @@ __device__ inline void class_nodes(const char *lane, const double2 *edge, const 
 // later the partial sums; D and A of the spline filter; boundary values; the
 // driver's time factors.
 // ---------------------------------------------------------------------------
-template <int P, int WP, int G, int DRV, bool F32>
+// GATHER: state-dependent coefficients (FP64, one point per lane).
+template <int P, int WP, int G, int DRV, bool F32, bool GATHER = false>
 __global__ void __launch_bounds__(64 * WP * G) sweep_fused(const StepArgs s)
 {
+    static_assert(!GATHER || (P == 1 && !F32), "located nodes: one point per lane, double precision");
     using PR = Prec<F32>;
     using V = typename std::conditional<F32, float4, double2>::type;  // one window record
     constexpr int T = FusedShape<P, WP, G>::T, NT = FusedShape<P, WP, G>::NT;
@@ -513,6 +577,21 @@ __global__ void __launch_bounds__(64 * WP * G) sweep_fused(const StepArgs s)
             list0[k] = K * (k0 * (h.L >> 3) + min(k0, h.L & 7));
             lcnt[k] = K * (k1 * (h.L >> 3) + min(k1, h.L & 7)) - list0[k];
             av[k] = h.addr[list0[k] + max(min(lane, lcnt[k] - 1), 0)];
+        }
+    }
+    double cax = 0.0, cbx = 0.0;  // a(t_n, x_i), b(t_n, x_i) of the lane's point
+    if constexpr (GATHER) {
+        const int i = min(t0 + wp * 64 + lane, nx - 1);
+        const double *tab = const_load(&d.a.ctab);
+        if (tab) {
+            const double *row =
+                tab + (size_t)2 * (const_load(&d.a.tab_steps) > 1 ? h.n0 - s.s : 0) * nx;
+            cax = row[i];
+            cbx = row[nx + i];
+        } else {
+            const double xi = fma((double)i, const_load(&d.a.dx), const_load(&d.a.x_min));
+            cax = fma(const_load(&d.a.drift_x), xi, const_load(&d.a.drift0));
+            cbx = fma(const_load(&d.a.vol_x), xi, const_load(&d.a.vol0));
         }
     }
     double2 ev;  // boundary values (grid points 0 and N - 1) of the K layers
@@ -683,9 +762,14 @@ __global__ void __launch_bounds__(64 * WP * G) sweep_fused(const StepArgs s)
         } else {
             const NodeRecB *recb = const_load(&dn->hot.recb);
 #pragma unroll
-            for (int k = 0; k < C; ++k)
-                class_nodes<P, DRV>(lane_rec, edge, recb + list0[k], lcnt[k], av[k], a, drv, first, wfirst,
-                                    wlast, nx, Y[k], Z[k]);
+            for (int k = 0; k < C; ++k) {
+                if constexpr (GATHER)
+                    gather_nodes<DRV>(smem, recb + list0[k], lcnt[k], av[k], a, drv,
+                                      (double)min(first, nx - 1), cax, cbx, t0, nx, Y[k][0], Z[k][0]);
+                else
+                    class_nodes<P, DRV>(lane_rec, edge, recb + list0[k], lcnt[k], av[k], a, drv, first,
+                                        wfirst, wlast, nx, Y[k], Z[k]);
+            }
         }
     }
 

@@ -15,7 +15,9 @@
 //   sweep_direct (windows too wide for LDS): records are read straight from
 //                HBM/L2, P consecutive points per lane; the natural spline of
 //                the new layer is a separate launch.
-//   sweep_gather (state-dependent coefficients): nodes located per point.
+//   sweep_gather (state-dependent coefficients whose windows do not fit LDS, the
+//                FP32 form, the E[y dW]/dt z form): nodes located per point
+//                and read from HBM/L2.
 #include "device_common.h"
 #include "fused.h"
 #include "kernels.h"
@@ -570,6 +572,34 @@ hipError_t launch_sweep_fused(int P, int WP, int G, bool F32, int driver, const 
 {
     return fused_shape(P, WP, G, F32, driver, &a, blocks, lds, s);
 }
+
+namespace {
+template <int DRV>
+hipError_t located_t(const StepArgs *a, int blocks, size_t lds, hipStream_t s)
+{
+    if (!a)
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep_fused<1, 1, 8, DRV, false, true>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL((sweep_fused<1, 1, 8, DRV, false, true>), dim3(blocks), dim3(512), lds, s, *a);
+    return hipGetLastError();
+}
+hipError_t located(int driver, const StepArgs *a, int blocks, size_t lds, hipStream_t s)
+{
+    switch (driver) {
+    case BSDE_DRIVER_LINEAR: return located_t<BSDE_DRIVER_LINEAR>(a, blocks, lds, s);
+    case BSDE_DRIVER_BIDASK: return located_t<BSDE_DRIVER_BIDASK>(a, blocks, lds, s);
+    case BSDE_DRIVER_CUBIC: return located_t<BSDE_DRIVER_CUBIC>(a, blocks, lds, s);
+    default: return located_t<BSDE_DRIVER_EXP>(a, blocks, lds, s);
+    }
+}
+}  // namespace
+
+hipError_t launch_sweep_located(int driver, const StepArgs &a, int blocks, size_t lds, hipStream_t s)
+{
+    return located(driver, &a, blocks, lds, s);
+}
+
+hipError_t set_located_lds_limit(int driver, size_t lds) { return located(driver, nullptr, 0, lds, nullptr); }
 
 hipError_t set_fused_lds_limit(int P, int WP, int G, bool F32, int driver, size_t lds)
 {
