@@ -1365,7 +1365,7 @@ bsde_status enqueue_solve2(const bsde_plan_s &pl, char *ws, const bsde_io *io, b
             if (in.bspline) return bsde::launch_coef2d(a, slot, s);
             return in.pb.interp == BSDE_INTERP_BICUBIC_FD
                        ? bsde::launch_fd2d(in.f32, a, slot, in.dx0, in.dx1, s)
-                       : bsde::launch_spline2d(in.f32, a, slot, f, s);
+                       : bsde::launch_spline2d(a, slot, f, s);
         };
         HIP_OK(bsde::launch_scatter2d(in.f32, a, io[b].init_y, io[b].init_z, s));
         for (int r = 0; r < K; ++r) HIP_OK(interp_layer((N - K + 1 + r) % (K + 1)));

@@ -179,8 +179,7 @@ hipError_t set_sweep2b_lds_limit(size_t bytes);
 hipError_t launch_sweep2b(const Sweep2Args &a, hipStream_t s);
 hipError_t launch_coef2d(const Sweep2Args &a, int slot, hipStream_t s);
 // splines and ghosts of the layer in slot `slot`
-hipError_t launch_spline2d(bool f32, const Sweep2Args &a, int slot, const SplineFilter &f,
-                           hipStream_t s);
+hipError_t launch_spline2d(const Sweep2Args &a, int slot, const SplineFilter &f, hipStream_t s);
 // the paper's bicubic interpolation: derivatives by fourth-order finite
 // differences (into the three derivative planes) and ghosts of slot `slot`
 hipError_t launch_fd2d(bool f32, const Sweep2Args &a, int slot, double dx0, double dx1,

@@ -197,6 +197,64 @@ __device__ inline double picard2(const Sweep2Args &a, double y, double Yc, doubl
     return y;
 }
 
+// The implicit y equation by Picard iteration from y^{n+1} and the stores, per
+// point of the lane (row i0, columns t1 + c + k); idx: the tile, tid: the thread.
+template <typename E>
+__device__ inline void finish2d(const Sweep2Args &a, int idx, int tid, int i0, int t1, int c,
+                                const double (&Y)[kCols2], const double (&Z1)[kCols2],
+                                const double (&Z2)[kCols2])
+{
+    const int S = a.K + 1;
+    const E *prev = plane2<E>(a, (a.n + 1) % S, 0);
+    E *out = plane2<E>(a, a.n % S, 0);
+    unsigned int it_max = 0, it_sum = 0, nonconv = 0;
+#pragma unroll
+    for (int k = 0; k < kCols2; ++k) {
+        const int i1 = t1 + c + k;
+        const bool valid = i0 < a.n0 && i1 < a.n1;
+        const size_t o = pidx(a, min(i0, a.n0 - 1), min(i1, a.n1 - 1));
+        double y = prev[o];
+        unsigned int it;
+        bool conv;
+        y = picard2(a, y, Y[k], Z1[k], Z2[k], it, conv);
+        if (valid) {
+            if constexpr (std::is_same<E, float>::value) {
+                // residuals of y^{n+K_y} (y recurrence) and of z^{n+1} (z recurrence)
+                const float *ry = plane2<float>(a, (a.n + a.Ky) % S, 12);
+                const float *rz = plane2<float>(a, (a.n + 1) % S, 13);
+                float *res = plane2<float>(a, a.n % S, 12);
+                store_fed_back2(out, res, o, y, ry[o]);
+                store_fed_back2(out + 4 * a.plane, res + a.plane, o, Z1[k], rz[o]);
+                store_fed_back2(out + 8 * a.plane, res + 2 * a.plane, o, Z2[k], rz[o + a.plane]);
+            } else {
+                out[o] = y;
+                out[o + 4 * a.plane] = Z1[k];
+                out[o + 8 * a.plane] = Z2[k];
+            }
+            if (a.n == a.n_stop) {
+                const size_t np = (size_t)a.n0 * a.n1, kk = (size_t)i0 * a.n1 + i1;
+                a.fin[kk] = y;
+                a.fin[np + kk] = Z1[k];
+                a.fin[2 * np + kk] = Z2[k];
+            }
+            it_max = max(it_max, it);
+            it_sum += it;
+            nonconv += conv ? 0u : 1u;
+        }
+    }
+    if (a.st_iter_max) {
+        it_max = wave_max_u32(it_max);
+        it_sum = wave_sum_u32(it_sum);
+        nonconv = wave_sum_u32(nonconv);
+        if ((tid & 63) == 0) {
+            const int w = idx * kWaves2 + tid / 64;
+            a.st_iter_max[w] = max(a.st_iter_max[w], it_max);
+            a.st_iter_sum[w] += it_sum;
+            a.st_nonconv[w] += nonconv;
+        }
+    }
+}
+
 // One time step: layer n from layers n+1..n+K.  Block = kTile2R x kTile2C points.
 // Dynamic LDS: (U, V) of 3 functions x kTile2R rows x 2 a.half columns.  E: the
 // element type of the ring planes; the arithmetic is double in both forms.
@@ -265,61 +323,106 @@ sweep2d(const Sweep2Args a)
             __syncthreads();
         }
     }
-    // implicit y equation by Picard iteration from y^{n+1}, per point of the lane
-    const E *prev = plane2<E>(a, (a.n + 1) % S, 0);
-    E *out = plane2<E>(a, a.n % S, 0);
-    const int i0 = t0 + r;
-    unsigned int it_max = 0, it_sum = 0, nonconv = 0;
+    finish2d<E>(a, idx, tid, t0 + r, t1, c, Y, Z1, Z2);
+}
+
+// The same step for grids of few tiles, which leave a CU one or two blocks to
+// cover the staging's latency with: the raw planes of the next node row are
+// loaded into registers before the nodes of this one, and two windows in LDS
+// take turns, so a row costs one barrier and no exposed load.  Wavefronts whose
+// columns all lie beyond the grid stage and then wait.  Same operations in the
+// same order, same results.  Time of a whole step (sweep, derivative passes),
+// L = 8, K = 3, with sweep2d and with this kernel: FP32 spline 129 x 129
+// 133 -> 101 us, 387 x 387 150 -> 139 us; FP64 bicubic 250 x 250 150 -> 114 us,
+// but 387 x 387 171 -> 249 us: 256 registers leave room for one block a CU.
+constexpr int kPre2 = (kWin2 + kThreads2 - 1) / kThreads2;  // window columns per thread
+template <typename E>
+__global__ void __launch_bounds__(kThreads2) sweep2d_ahead(const Sweep2Args a)
+{
+    static_assert(kTile2R == 1, "one grid row per tile");
+    extern __shared__ double2 uv[];
+    const int tiles1 = (a.n1 + kTile2C - 1) / kTile2C;
+    const int idx = xcd_tile(blockIdx.x, gridDim.x);
+    const int i0 = idx / tiles1, t1 = (idx % tiles1) * kTile2C;
+    const int tid = threadIdx.x, c = tid * kCols2;
+    const int cols = min(kTile2C, (a.n1 - t1 + 127) & ~127);  // columns of wavefronts in the grid
+    const bool idle = t1 + (tid & ~63) * kCols2 >= a.n1;  // wavefront beyond the grid
+    const int S = a.K + 1, nrows = a.K * a.L, wsize = 6 * a.half;
+    double Y[kCols2], Z1[kCols2], Z2[kCols2];
 #pragma unroll
-    for (int k = 0; k < kCols2; ++k) {
-        const int i1 = t1 + c + k;
-        const bool valid = i0 < a.n0 && i1 < a.n1;
-        const size_t o = pidx(a, min(i0, a.n0 - 1), min(i1, a.n1 - 1));
-        double y = prev[o];
-        unsigned int it;
-        bool conv;
-        y = picard2(a, y, Y[k], Z1[k], Z2[k], it, conv);
-        if (valid) {
-            if constexpr (std::is_same<E, float>::value) {
-                // residuals of y^{n+K_y} (y recurrence) and of z^{n+1} (z recurrence)
-                const float *ry = plane2<float>(a, (a.n + a.Ky) % S, 12);
-                const float *rz = plane2<float>(a, (a.n + 1) % S, 13);
-                float *res = plane2<float>(a, a.n % S, 12);
-                store_fed_back2(out, res, o, y, ry[o]);
-                store_fed_back2(out + 4 * a.plane, res + a.plane, o, Z1[k], rz[o]);
-                store_fed_back2(out + 8 * a.plane, res + 2 * a.plane, o, Z2[k], rz[o + a.plane]);
-            } else {
-                out[o] = y;
-                out[o + 4 * a.plane] = Z1[k];
-                out[o + 8 * a.plane] = Z2[k];
+    for (int k = 0; k < kCols2; ++k) Y[k] = Z1[k] = Z2[k] = 0.0;
+    E raw[kPre2][24];  // planes of the three functions at cells p and p + 1
+    int mvn = 0;
+    auto ahead = [&](int rowi, int j) {
+        const Node2Row *row = a.rows + rowi;
+        const int m0 = const_load(&row->m0), m1lo = const_load(&row->m1lo), m1hi = const_load(&row->m1hi);
+        mvn = a.m1[(size_t)rowi * a.L + min(tid & 63, a.L - 1)];
+        const E *slot = plane2<E>(a, (a.n + j) % S, 0);
+        const int W = cols + m1hi - m1lo + 2;
+#pragma unroll
+        for (int u = 0; u < kPre2; ++u) {
+            const int e = tid + u * kThreads2;
+            if (e < W) {
+                const unsigned o = (unsigned)pidx(a, i0 + m0, t1 + m1lo + e);
+#pragma unroll
+                for (int q = 0; q < 12; ++q) {
+                    const E *v = slot + (size_t)q * a.plane;
+                    raw[u][2 * q] = v[o];
+                    raw[u][2 * q + 1] = v[o + (unsigned)a.npad1];
+                }
             }
-            if (a.n == a.n_stop) {
-                const size_t np = (size_t)a.n0 * a.n1, kk = (size_t)i0 * a.n1 + i1;
-                a.fin[kk] = y;
-                a.fin[np + kk] = Z1[k];
-                a.fin[2 * np + kk] = Z2[k];
+        }
+    };
+    ahead(0, 1);
+    int buf = 0;
+    for (int j = 1; j <= a.K; ++j) {
+        for (int l0 = 0; l0 < a.L; ++l0, buf ^= 1) {
+            const int rowi = (j - 1) * a.L + l0;
+            const Node2Row *row = a.rows + rowi;
+            const int m1lo = const_load(&row->m1lo), m1hi = const_load(&row->m1hi);
+            const int p = i0 + const_load(&row->m0);
+            const bool in = p >= 0 && p < a.n0 - 1;
+            const double B0 = in ? const_load(&row->B0) : 0.0, C0 = in ? const_load(&row->C0) : 0.0,
+                         D0 = in ? const_load(&row->D0) : 0.0;
+            const int W = cols + m1hi - m1lo + 2;
+            const int mv = mvn;
+            double2 *win = uv + buf * wsize;
+#pragma unroll
+            for (int u = 0; u < kPre2; ++u) {
+                const int e = tid + u * kThreads2;
+                if (e < W) {
+#pragma unroll
+                    for (int f = 0; f < 3; ++f) {  // v, Mxx, Myy, Mxxyy at cells p and p + 1
+                        const E *q = raw[u] + 8 * f;
+                        const double v0 = q[0], y0 = q[4];
+                        const double U = fma(B0, (double)q[1] - v0,
+                                             fma(C0, (double)q[2], fma(D0, (double)q[3], v0)));
+                        const double V = fma(B0, (double)q[5] - y0,
+                                             fma(C0, (double)q[6], fma(D0, (double)q[7], y0)));
+                        win[uv_index(a.half, f, 0, e)] = make_double2(U, V);
+                    }
+                }
             }
-            it_max = max(it_max, it);
-            it_sum += it;
-            nonconv += conv ? 0u : 1u;
+            __syncthreads();
+            if (rowi + 1 < nrows) ahead(rowi + 1, l0 + 1 < a.L ? j : j + 1);
+            if (idle) continue;
+            const Node2 *ntab = a.nodes + (size_t)rowi * a.L;
+            const int nf = (j == a.Ky ? 1 : 0) | (j == 1 && a.zform ? 2 : 0);
+            const bool clamp = a.interp == BSDE_INTERP_BICUBIC_FD &&
+                               (t1 + m1lo < 0 || t1 + kTile2C + m1hi > a.n1 - 1);
+            const double2 *uvl = win + uv_index(a.half, 0, 0, c);
+            if (clamp)
+                row_nodes_nf<true>(nf, a, uvl, ntab, mv, m1lo, t1 + c, Y, Z1, Z2);
+            else
+                row_nodes_nf<false>(nf, a, uvl, ntab, mv, m1lo, t1 + c, Y, Z1, Z2);
         }
     }
-    if (a.st_iter_max) {
-        it_max = wave_max_u32(it_max);
-        it_sum = wave_sum_u32(it_sum);
-        nonconv = wave_sum_u32(nonconv);
-        if ((tid & 63) == 0) {
-            const int w = idx * kWaves2 + tid / 64;
-            a.st_iter_max[w] = max(a.st_iter_max[w], it_max);
-            a.st_iter_sum[w] += it_sum;
-            a.st_nonconv[w] += nonconv;
-        }
-    }
+    finish2d<E>(a, idx, tid, i0, t1, c, Y, Z1, Z2);
 }
 
 // ---------------------------------------------------------------------------
-// Tensor natural spline of a layer: M_xx and M_yy of the values, then M_xxyy
-// as the axis-1 spline of M_xx, then the ghost points.
+// Tensor natural spline of a layer (FP32 planes): M_xx and M_yy of the values,
+// then M_xxyy as the axis-1 spline of M_xx, then the ghost points.
 // ---------------------------------------------------------------------------
 namespace {
 
@@ -341,14 +444,13 @@ __device__ inline double rt_line(const E *v, long stride, int n, int k)
     return sign * ((vp - v0) - (v0 - vm));
 }
 
-template <typename E>
-__device__ inline double spline_line(const E *v, long stride, int n, int i,
+__device__ inline double spline_line(const float *v, long stride, int n, int i,
                                      const SplineFilter &F, double s6)
 {
     if (i == 0 || i == n - 1) return 0.0;
     double acc = 0.0;
     if (i >= 32 && i <= n - 33) {
-        const E *p = v + (long)(i - 32) * stride;
+        const float *p = v + (long)(i - 32) * stride;
 #pragma unroll
         for (int k = 0; k < kPcrTaps + 2; ++k) acc = fma(F.d[k], (double)p[(long)k * stride], acc);
     } else {
@@ -360,7 +462,7 @@ __device__ inline double spline_line(const E *v, long stride, int n, int i,
 constexpr int kRun = 16;  // consecutive outputs per thread of the line passes
 // The axis-0 passes take four: 17 loads per output (mostly L2 hits) instead of
 // 5, but four times the threads, which is what covers the loads' latency
-// (387 x 387: 49 -> 11 us in FP64, 35 -> 9 us for the FP32 form's filter).
+// (387 x 387: 35 -> 9 us).
 constexpr int kRunCols = 4;
 
 // Outputs i0 .. i0 + kRun - 1 (those < n) of the natural spline of one line
@@ -370,8 +472,8 @@ constexpr int kRunCols = 4;
 // v~_{-j} = 2 v_0 - v_j and v~_{n-1+j} = 2 v_{n-1} - v_{n-1-j}: their second
 // differences are then the odd extension the natural end conditions call
 // for, so the values form holds at every point; M_0 = M_{n-1} = 0.
-template <int kRun, typename E>
-__device__ inline void line_run(const E *v, long stride, int n, int i0, double s6, E *out,
+template <int kRun>
+__device__ inline void line_run(const float *v, long stride, int n, int i0, double s6, float *out,
                                 long ostride)
 {
     constexpr SplineTaps T = spline_taps();
@@ -380,7 +482,7 @@ __device__ inline void line_run(const E *v, long stride, int n, int i0, double s
 #pragma unroll
     for (int r = 0; r < kRun; ++r) acc[r] = 0.0;
     if (i0 >= H && i0 + kRun - 1 + H <= n - 1) {  // clear of both ends
-        const E *p = v + (long)(i0 - H) * stride;
+        const float *p = v + (long)(i0 - H) * stride;
 #pragma unroll
         for (int m = 0; m < kRun + 2 * H; ++m) {
             const double x = p[(long)m * stride];
@@ -406,17 +508,17 @@ __device__ inline void line_run(const E *v, long stride, int n, int i0, double s
 #pragma unroll
     for (int r = 0; r < kRun; ++r) {
         const int i = i0 + r;
-        if (i < n) out[(long)i * ostride] = (E)((i == 0 || i == n - 1) ? 0.0 : s6 * acc[r]);
+        if (i < n) out[(long)i * ostride] = (float)((i == 0 || i == n - 1) ? 0.0 : s6 * acc[r]);
     }
 }
 
 // The same outputs for lines shorter than kMinLine, one at a time.
-template <int kRun, typename E>
-__device__ inline void line_run_short(const E *v, long stride, int n, int i0,
-                                      const SplineFilter &F, double s6, E *out, long ostride)
+template <int kRun>
+__device__ inline void line_run_short(const float *v, long stride, int n, int i0,
+                                      const SplineFilter &F, double s6, float *out, long ostride)
 {
     for (int i = i0; i < min(i0 + kRun, n); ++i)
-        out[(long)i * ostride] = (E)spline_line(v, stride, n, i, F, s6);
+        out[(long)i * ostride] = (float)spline_line(v, stride, n, i, F, s6);
 }
 
 }  // namespace
@@ -424,14 +526,14 @@ __device__ inline void line_run_short(const E *v, long stride, int n, int i0,
 // M_xx of field blockIdx.y (y, z1, z2): lines along axis 0.  Thread t:
 // column t % n1 (adjacent lanes read adjacent columns), rows from
 // kRun * (t / n1).
-template <int kRun, typename E>
+template <int kRun>
 __global__ void __launch_bounds__(256) spline2d_cols(const Sweep2Args a, int slot,
                                                      const SplineFilter F)
 {
     const long t = blockIdx.x * 256L + threadIdx.x;
     if (t >= (long)a.n1 * ((a.n0 + kRun - 1) / kRun)) return;
     const int i1 = (int)(t % a.n1), i0 = (int)(t / a.n1) * kRun;
-    E *col = plane2<E>(a, slot, 4 * blockIdx.y) + pidx(a, 0, i1);
+    float *col = plane2<float>(a, slot, 4 * blockIdx.y) + pidx(a, 0, i1);
     if (a.n0 >= kMinLine)
         line_run<kRun>(col, a.npad1, a.n0, i0, F.s6[0], col + a.plane, a.npad1);
     else
@@ -441,7 +543,6 @@ __global__ void __launch_bounds__(256) spline2d_cols(const Sweep2Args a, int slo
 // Lines along axis 1 of field blockIdx.y / 2: the values give M_yy
 // (blockIdx.y even), M_xx gives M_xxyy (odd).  Thread t: row t % n0, columns
 // from kRun * (t / n0), so that a wavefront takes one branch of line_run.
-template <typename E>
 __global__ void __launch_bounds__(256) spline2d_rows(const Sweep2Args a, int slot,
                                                      const SplineFilter F)
 {
@@ -449,9 +550,9 @@ __global__ void __launch_bounds__(256) spline2d_rows(const Sweep2Args a, int slo
     if (t >= (long)a.n0 * ((a.n1 + kRun - 1) / kRun)) return;
     const int i0 = (int)(t % a.n0), i1 = (int)(t / a.n0) * kRun;
     const int f = blockIdx.y >> 1, g = blockIdx.y & 1;
-    E *row = plane2<E>(a, slot, 4 * f) + pidx(a, i0, 0);
-    const E *src = row + (size_t)g * a.plane;
-    E *dst = row + (size_t)(2 + g) * a.plane;
+    float *row = plane2<float>(a, slot, 4 * f) + pidx(a, i0, 0);
+    const float *src = row + (size_t)g * a.plane;
+    float *dst = row + (size_t)(2 + g) * a.plane;
     if (a.n1 >= kMinLine)
         line_run<kRun>(src, 1, a.n1, i1, F.s6[1], dst, 1);
     else
@@ -468,7 +569,6 @@ constexpr int kRowCols = 256 / kRowTile * kRun;  // outputs per row per block
 constexpr int kRowIn = kRowCols + 2 * (kPcrTaps / 2 + 1);  // staged values per row
 constexpr int kRowStride = kRowIn + 1;          // LDS row pitch (odd: fewer bank conflicts)
 
-template <typename E>
 __global__ void __launch_bounds__(256) spline2d_rows_lds(const Sweep2Args a, int slot,
                                                          const SplineFilter F)
 {
@@ -479,14 +579,14 @@ __global__ void __launch_bounds__(256) spline2d_rows_lds(const Sweep2Args a, int
     const int r0 = (int)(blockIdx.x / tiles1) * kRowTile, c0 = (int)(blockIdx.x % tiles1) * kRowCols;
     const int f = blockIdx.y >> 1, g = blockIdx.y & 1;
     const int n = a.n1;
-    E *plane0 = plane2<E>(a, slot, 4 * f);
-    const E *src = plane0 + (size_t)g * a.plane;
-    E *dst = plane0 + (size_t)(2 + g) * a.plane;
+    float *plane0 = plane2<float>(a, slot, 4 * f);
+    const float *src = plane0 + (size_t)g * a.plane;
+    float *dst = plane0 + (size_t)(2 + g) * a.plane;
     for (int e = threadIdx.x; e < kRowTile * kRowIn; e += 256) {
         const int rr = e / kRowIn, cc = e - rr * kRowIn;
         const int i0 = r0 + rr;
         if (i0 >= a.n0) continue;
-        const E *v = src + pidx(a, i0, 0);
+        const float *v = src + pidx(a, i0, 0);
         const int k = c0 - H + cc;
         const int kk = min(max(k < 0 ? -k : (k > n - 1 ? 2 * (n - 1) - k : k), 0), n - 1);
         const double y = v[kk];
@@ -508,12 +608,12 @@ __global__ void __launch_bounds__(256) spline2d_rows_lds(const Sweep2Args a, int
         for (int u = 0; u < kRun; ++u)
             if (m - u >= 0 && m - u <= 2 * H) acc[u] = fma(T.d[m - u], x, acc[u]);
     }
-    E *out = dst + pidx(a, i0, 0);
+    float *out = dst + pidx(a, i0, 0);
     const double s6 = F.s6[1];
 #pragma unroll
     for (int u = 0; u < kRun; ++u) {
         const int i = j0 + u;
-        if (i < n) out[i] = (E)((i == 0 || i == n - 1) ? 0.0 : s6 * acc[u]);
+        if (i < n) out[i] = (float)((i == 0 || i == n - 1) ? 0.0 : s6 * acc[u]);
     }
 }
 
@@ -1207,7 +1307,21 @@ template <typename E>
 hipError_t launch_sweep2d_t(const Sweep2Args &a, hipStream_t s)
 {
     const int tiles = ((a.n0 + kTile2R - 1) / kTile2R) * ((a.n1 + kTile2C - 1) / kTile2C);
-    hipLaunchKernelGGL(sweep2d<E>, dim3(tiles), dim3(kThreads2), sweep2d_lds(a.half), s, a);
+    // The staging runs a row ahead where all blocks are on the chip at once with
+    // the registers that takes (213 of the FP32 planes' loads: two blocks a CU;
+    // 256 of the FP64 planes': one).  See sweep2d_ahead for both sides.
+    constexpr int kAheadTiles = std::is_same<E, float>::value ? 512 : 256;
+    if (tiles <= kAheadTiles) {
+        const size_t lds = 2 * sweep2d_lds(a.half);
+        if (lds > 65536) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep2d_ahead<E>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(sweep2d_ahead<E>, dim3(tiles), dim3(kThreads2), lds, s, a);
+    } else {
+        hipLaunchKernelGGL(sweep2d<E>, dim3(tiles), dim3(kThreads2), sweep2d_lds(a.half), s, a);
+    }
     return hipGetLastError();
 }
 
@@ -1220,27 +1334,30 @@ hipError_t launch_ghosts2d_t(const Sweep2Args &a, int slot, hipStream_t s)
     return hipGetLastError();
 }
 
-template <typename E>
-hipError_t launch_spline2d_t(const Sweep2Args &a, int slot, const SplineFilter &f, hipStream_t s)
+}  // namespace
+
+hipError_t launch_spline2d(const Sweep2Args &a, int slot, const SplineFilter &f, hipStream_t s)
 {
     const long tc = (long)a.n1 * ((a.n0 + kRunCols - 1) / kRunCols);
-    hipLaunchKernelGGL((spline2d_cols<kRunCols, E>), dim3((unsigned)((tc + 255) / 256), 3), dim3(256), 0, s, a,
+    hipLaunchKernelGGL(spline2d_cols<kRunCols>, dim3((unsigned)((tc + 255) / 256), 3), dim3(256), 0, s, a,
                        slot, f);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.n1 >= kMinLine) {
         const long tiles = (long)((a.n0 + kRowTile - 1) / kRowTile) * ((a.n1 + kRowCols - 1) / kRowCols);
-        hipLaunchKernelGGL(spline2d_rows_lds<E>, dim3((unsigned)tiles, 6), dim3(256), 0, s, a, slot,
+        hipLaunchKernelGGL(spline2d_rows_lds, dim3((unsigned)tiles, 6), dim3(256), 0, s, a, slot,
                            f);
     } else {
         const long tr = (long)a.n0 * ((a.n1 + kRun - 1) / kRun);
-        hipLaunchKernelGGL(spline2d_rows<E>, dim3((unsigned)((tr + 255) / 256), 6), dim3(256), 0, s,
+        hipLaunchKernelGGL(spline2d_rows, dim3((unsigned)((tr + 255) / 256), 6), dim3(256), 0, s,
                            a, slot, f);
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_ghosts2d_t<E>(a, slot, s);
+    return launch_ghosts2d_t<float>(a, slot, s);
 }
+
+namespace {
 
 template <typename E>
 hipError_t launch_fd2d_t(const Sweep2Args &a, int slot, double dx0, double dx1, hipStream_t s)
@@ -1271,12 +1388,6 @@ hipError_t launch_scatter2d_t(const Sweep2Args &a, const double *iy, const doubl
 hipError_t launch_sweep2d(bool f32, const Sweep2Args &a, hipStream_t s)
 {
     return f32 ? launch_sweep2d_t<float>(a, s) : launch_sweep2d_t<double>(a, s);
-}
-
-hipError_t launch_spline2d(bool f32, const Sweep2Args &a, int slot, const SplineFilter &f,
-                           hipStream_t s)
-{
-    return f32 ? launch_spline2d_t<float>(a, slot, f, s) : launch_spline2d_t<double>(a, slot, f, s);
 }
 
 hipError_t launch_fd2d(bool f32, const Sweep2Args &a, int slot, double dx0, double dx1,
