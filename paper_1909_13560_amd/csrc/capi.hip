@@ -4,10 +4,13 @@
 // Workspace layout (caller-owned device memory):
 //   per instance: ring of K+1 slots; layer n lives in slot n mod (K+1); a slot
 //                 is two planes of pad_l ghost, n_x grid and pad_r ghost
-//                 elements: (y, z), then (M_y, M_z) (16 bytes each in FP64,
-//                 8 in FP32), so each launch writes whole planes; the FP32
-//                 form adds a third plane, the rounding residuals (e_y, e_z)
-//                 of the stored values (error feedback)
+//                 elements: (y, z), then a spline plane (16 bytes each in
+//                 FP64, 8 in FP32), so each launch writes whole planes.  The
+//                 spline plane holds the B-spline coefficients (c_y, c_z) for
+//                 the fused and the one-launch exact sweep in FP64, the second
+//                 derivatives (M_y, M_z) for the other kernels and the FP32
+//                 form; the FP32 form adds a third plane, the rounding
+//                 residuals (e_y, e_z) of the stored values (error feedback)
 //   per instance: per-wavefront Picard counters (statistics)
 //   totals      : 4 x u64 reduced statistics
 #include <hip/hip_runtime.h>
@@ -297,50 +300,71 @@ bool supported_2d(const bsde_problem &p)
            (p.interp == BSDE_INTERP_SPLINE || (p.n_x[0] >= 5 && p.n_x[1] >= 5));
 }
 
+// Bounds on the drift and the volatility of state-dependent coefficients over
+// runs of a table's rows (its volatilities are positive), or at the grid's ends
+// where they are affine.  One pass over a table, eight extremes at a time: it
+// also serves the widest reach, which took a pass of its own.
+struct CoefBounds {
+    double alo, ahi, blo, bhi;
+};
+std::vector<CoefBounds> coef_bounds(const bsde_problem &p)
+{
+    std::vector<CoefBounds> out;
+    if (p.tab_steps == 0) {
+        for (double x : {p.x_min[0], p.x_max[0]}) {
+            const double ax = p.drift[0] + p.drift_x * x, bx = p.vol[0][0] + p.vol_x * x;
+            out.push_back({ax, ax, std::min(0.0, bx), std::max(0.0, bx)});
+        }
+        return out;
+    }
+    constexpr int kRun = 64, kV = 8;
+    const int nx = p.n_x[0];
+    for (int r = 0; r < p.tab_steps; ++r) {
+        const double *ta = p.coef_tab + (size_t)2 * r * nx, *tb = ta + nx;
+        for (int i0 = 0; i0 < nx; i0 += kRun) {
+            double al[kV], ah[kV], bh[kV];
+            for (int v = 0; v < kV; ++v) {
+                al[v] = ah[v] = ta[i0];
+                bh[v] = tb[i0];
+            }
+            const int i1 = std::min(i0 + kRun, nx);
+            int i = i0;
+            for (; i + kV <= i1; i += kV)
+                for (int v = 0; v < kV; ++v) {
+                    al[v] = ta[i + v] < al[v] ? ta[i + v] : al[v];
+                    ah[v] = ta[i + v] > ah[v] ? ta[i + v] : ah[v];
+                    bh[v] = tb[i + v] > bh[v] ? tb[i + v] : bh[v];
+                }
+            for (; i < i1; ++i) {
+                al[0] = std::min(al[0], ta[i]);
+                ah[0] = std::max(ah[0], ta[i]);
+                bh[0] = std::max(bh[0], tb[i]);
+            }
+            out.push_back({*std::min_element(al, al + kV), *std::max_element(ah, ah + kV), 0.0,
+                           *std::max_element(bh, bh + kV)});
+        }
+    }
+    return out;
+}
+
 // Window bounds of every layer for state-dependent coefficients: the nodes of
 // grid point i sit (a(t, x_i) j dt + b(t, x_i) dW) / dx cells away with b > 0,
 // so the extremes over the grid (and the table's rows) of the outermost
 // nodes, one cell wider for rounding.  gh: Gauss-Hermite nodes.  Bounds far
 // beyond any LDS window leave the instance to the kernel that reads HBM.
-void located_windows(const bsde_problem &p, Instance &in, const double *gh)
+void located_windows(const bsde_problem &p, const std::vector<CoefBounds> &pieces, Instance &in,
+                     const double *gh)
 {
     double glo = gh[0], ghi = gh[0];
     for (int l = 1; l < p.L; ++l) {
         glo = std::min(glo, gh[l]);
         ghi = std::max(ghi, gh[l]);
     }
-    // Pieces with bounds on the drift and the volatility: runs of a table's rows
-    // (its volatilities are positive), or the grid's ends of affine coefficients.
-    // One pass over a table whatever K: 2001 points x 250 rows in 0.4 ms.
-    struct Piece {
-        double alo, ahi, blo, bhi;
-    };
-    std::vector<Piece> pieces;
-    if (p.tab_steps > 0) {
-        constexpr int kRun = 64;
-        for (int r = 0; r < p.tab_steps; ++r) {
-            const double *ta = p.coef_tab + (size_t)2 * r * in.nx, *tb = ta + in.nx;
-            for (int i0 = 0; i0 < in.nx; i0 += kRun) {
-                Piece q{ta[i0], ta[i0], 0.0, tb[i0]};
-                for (int i = i0; i < std::min(i0 + kRun, in.nx); ++i) {
-                    q.alo = ta[i] < q.alo ? ta[i] : q.alo;
-                    q.ahi = ta[i] > q.ahi ? ta[i] : q.ahi;
-                    q.bhi = tb[i] > q.bhi ? tb[i] : q.bhi;
-                }
-                pieces.push_back(q);
-            }
-        }
-    } else {
-        for (double x : {p.x_min[0], p.x_max[0]}) {
-            const double ax = p.drift[0] + p.drift_x * x, bx = p.vol[0][0] + p.vol_x * x;
-            pieces.push_back({ax, ax, std::min(0.0, bx), std::max(0.0, bx)});
-        }
-    }
     std::vector<int> lo(in.K + 1, 0), hi(in.K + 1, 0);
     for (int j = 1; j <= in.K; ++j) {
         const double t = j * in.dt / in.dx, sq = std::sqrt(2.0 * j * in.dt) / in.dx;
         double mn = 1e300, mx = -1e300;
-        for (const Piece &q : pieces) {  // glo <= 0 <= ghi: the abscissae are symmetric
+        for (const CoefBounds &q : pieces) {  // glo <= 0 <= ghi: the abscissae are symmetric
             mn = std::min(mn, q.alo * t + sq * std::min(q.bhi * glo, q.blo * ghi));
             mx = std::max(mx, q.ahi * t + sq * std::max(q.bhi * ghi, q.blo * glo));
         }
@@ -378,12 +402,11 @@ bool build_instance(const bsde_problem &p, Instance &in)
     const double vol = p.vol[0][0];
     // largest Gauss-Hermite spread per cell over the grid (b(x) is affine, or
     // tabulated)
+    const std::vector<CoefBounds> pieces = in.gather ? coef_bounds(p) : std::vector<CoefBounds>();
     double bmax = std::max(vol + p.vol_x * p.x_min[0], vol + p.vol_x * p.x_max[0]);
     if (p.tab_steps > 0) {
         bmax = 0.0;
-        for (int r = 0; r < p.tab_steps; ++r)
-            for (int i = 0; i < in.nx; ++i)
-                bmax = std::max(bmax, p.coef_tab[(size_t)(2 * r + 1) * in.nx + i]);
+        for (const CoefBounds &q : pieces) bmax = std::max(bmax, q.bhi);
         // the plan keeps its own copy of the table
         in.ctab.assign(p.coef_tab, p.coef_tab + (size_t)2 * p.tab_steps * in.nx);
         in.pb.coef_tab = nullptr;
@@ -448,7 +471,7 @@ bool build_instance(const bsde_problem &p, Instance &in)
     }
     in.h0 = p.k_y * in.dt * gy[0];
     const int node_lo = in.m_min, node_hi = in.m_max;
-    if (in.gather && !in.f32 && p.z_form == BSDE_ZFORM_EZ) located_windows(p, in, a);
+    if (in.gather && !in.f32 && p.z_form == BSDE_ZFORM_EZ) located_windows(p, pieces, in, a);
     if (in.exact) {
         // exact Gaussian expectations: the band of every layer; the ghosts
         // cover the band and the Toeplitz kernel's window overhang
@@ -1115,15 +1138,16 @@ int sweep_tiles(const Instance &in, const SweepConfig &c)
 int tiles_of(const Instance &in, int T) { return (in.nx + T - 1) / T; }
 int spline_tiles(const Instance &in) { return (in.nx + bsde::kSplineTile - 1) / bsde::kSplineTile; }
 
-// Bind a kernel shape to a group: tile numbering, descriptors, LDS limit.
+// Bind a kernel shape to a group: tile numbering, descriptors, LDS limit (always
+// the device's: the limit belongs to the kernel, which other plans launch too).
 bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
 {
     if (c.path == PATH_FUSED && c.lds > 65536)
-        HIP_OK(bsde::set_fused_lds_limit(c.P, c.W, c.G, g.f32, g.driver, c.lds));
+        HIP_OK(bsde::set_fused_lds_limit(c.P, c.W, c.G, g.f32, g.driver, pl.max_lds));
     const bool exact_b = c.path == PATH_TOEPLITZ && c.W == 1;  // on B-spline coefficients
     const bool located = c.path == PATH_GATHER && c.W == 1;    // in the fused sweep
-    if (located && c.lds > 65536) HIP_OK(bsde::set_located_lds_limit(g.driver, c.lds));
-    if (exact_b && c.lds > 65536) HIP_OK(bsde::set_exact_lds_limit(c.G, c.lds));
+    if (located && c.lds > 65536) HIP_OK(bsde::set_located_lds_limit(g.driver, pl.max_lds));
+    if (exact_b && c.lds > 65536) HIP_OK(bsde::set_exact_lds_limit(c.G, pl.max_lds));
     if (c.path == PATH_TOEPLITZ && !exact_b && c.lds > 65536) HIP_OK(bsde::set_toeplitz_lds_limit());
     g.cfg = c;
     g.tile_prefix.assign(g.members.size() + 1, 0);
@@ -1603,6 +1627,13 @@ bsde_status plan_2d(const bsde_problem *pb, int batch, bsde_plan_t *out)
         delete pl;
         return BSDE_EDEVICE;
     }
+    int lds_limit = 65536;
+    if (hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock,
+                              pl->device) != hipSuccess) {
+        delete pl;
+        return BSDE_EDEVICE;
+    }
+    pl->max_lds = (size_t)lds_limit;
     {
         const char *g = std::getenv("BSDE_GRAPH");
         pl->use_graphs = !(g && g[0] == '0');
@@ -1652,11 +1683,14 @@ bsde_status plan_2d(const bsde_problem *pb, int batch, bsde_plan_t *out)
                 put(in.corr_l.data(), in.corr_l.size() * sizeof(double4)));
             in.d_corr_r = static_cast<const double4 *>(
                 put(in.corr_r.data(), in.corr_r.size() * sizeof(double4)));
-            const size_t lds = bsde::kGroups2B * bsde::sweep2b_wave_lds(in.spread);
-            if (lds > 65536 && bsde::set_sweep2b_lds_limit(lds) != hipSuccess) {
-                bsde_plan_destroy(pl);
-                return BSDE_EDEVICE;
-            }
+        }
+        // the kernel's limit, which other plans launch too: the device's
+        const size_t lds = in.bspline ? bsde::kGroups2B * bsde::sweep2b_wave_lds(in.spread)
+                                      : 2 * bsde::sweep2d_lds((in.win + 1) / 2);
+        if (lds > 65536 && (in.bspline ? bsde::set_sweep2b_lds_limit(pl->max_lds)
+                                       : bsde::set_sweep2d_lds_limit(in.f32, pl->max_lds)) != hipSuccess) {
+            bsde_plan_destroy(pl);
+            return BSDE_EDEVICE;
         }
     }
     // workspace: rings (6 planes of doubles per layer in the B-spline form, 12

@@ -644,10 +644,10 @@ struct Prec<true> {
 };
 
 // One ring slot (one time layer): planes of npad elements, the values
-// (y, z) and the spline second derivatives (M_y, M_z), each pair a double2
-// (FP64) or float2 (FP32); index k runs from -pad_l to nx + pad_r - 1.  A
-// launch writes whole planes contiguously: the values of layer n and the
-// derivatives of layer n+1.
+// (y, z) and the spline second derivatives (M_y, M_z) -- or, for the FP64
+// kernels on B-spline coefficients, (c_y, c_z) -- each pair a double2 (FP64) or
+// float2 (FP32); index k runs from -pad_l to nx + pad_r - 1.  A launch writes
+// whole planes contiguously: the values of layer n and the spline of layer n+1.
 // The FP32 form has a third plane, the rounding residuals (e_y, e_z) of the
 // stored values: y^n is stored as fl(y^n + e_y^{n+K_y}) and z^n as
 // fl(z^n + e_z^{n+1}) (round to nearest), and the residual of that rounding

@@ -176,6 +176,7 @@ hipError_t launch_sweep2d(bool f32, const Sweep2Args &a, hipStream_t s);
 // B-spline form: the step, and the coefficients of the layer in slot `slot`
 size_t sweep2b_wave_lds(int spread);  // LDS bytes of a wavefront, widest node spread
 hipError_t set_sweep2b_lds_limit(size_t bytes);
+hipError_t set_sweep2d_lds_limit(bool f32, size_t bytes);  // of the kernel that stages ahead
 hipError_t launch_sweep2b(const Sweep2Args &a, hipStream_t s);
 hipError_t launch_coef2d(const Sweep2Args &a, int slot, hipStream_t s);
 // splines and ghosts of the layer in slot `slot`

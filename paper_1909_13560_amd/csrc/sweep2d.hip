@@ -11,6 +11,10 @@
 // s0 depends on the axis-0 Gauss-Hermite index l0 only, so for one l0 the
 // block evaluates (U, V) once per (tile row, window column) into LDS and
 // every node l1 of that row costs one axis-1 evaluation per function.
+//
+// Two forms: sweep2d / sweep2d_ahead on value and derivative planes (the FP32
+// form's spline, the bicubic in both forms), and sweep2b on planes of tensor
+// B-spline coefficients (FP64 natural spline), further down.
 #include "sweep2d.h"
 
 namespace bsde {
@@ -1312,13 +1316,7 @@ hipError_t launch_sweep2d_t(const Sweep2Args &a, hipStream_t s)
     // 256 of the FP64 planes': one).  See sweep2d_ahead for both sides.
     constexpr int kAheadTiles = std::is_same<E, float>::value ? 512 : 256;
     if (tiles <= kAheadTiles) {
-        const size_t lds = 2 * sweep2d_lds(a.half);
-        if (lds > 65536) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep2d_ahead<E>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL(sweep2d_ahead<E>, dim3(tiles), dim3(kThreads2), lds, s, a);
+        hipLaunchKernelGGL(sweep2d_ahead<E>, dim3(tiles), dim3(kThreads2), 2 * sweep2d_lds(a.half), s, a);
     } else {
         hipLaunchKernelGGL(sweep2d<E>, dim3(tiles), dim3(kThreads2), sweep2d_lds(a.half), s, a);
     }
@@ -1384,6 +1382,13 @@ hipError_t launch_scatter2d_t(const Sweep2Args &a, const double *iy, const doubl
 }
 
 }  // namespace
+
+hipError_t set_sweep2d_lds_limit(bool f32, size_t bytes)
+{
+    return hipFuncSetAttribute(f32 ? reinterpret_cast<const void *>(&sweep2d_ahead<float>)
+                                   : reinterpret_cast<const void *>(&sweep2d_ahead<double>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
 
 hipError_t launch_sweep2d(bool f32, const Sweep2Args &a, hipStream_t s)
 {

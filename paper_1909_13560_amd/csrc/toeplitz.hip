@@ -13,6 +13,9 @@
 // is four banded products per layer (E and dW-weighted, of y and of z) and a
 // per-point combination.
 //
+// Bands that fit LDS take sweep_exact (below): on B-spline coefficients, one
+// launch per step.  Wider ones take sweep_toeplitz, described here.
+//
 // A block computes the 256 consecutive points of one tile as a 16 x 16 tile
 // D[r][q] = sum_k A[r][k] B[k][q] of v_mfma_f64_16x16x4f64 products: point
 // base + 16 q + p(r), A[r][k] = w[k - p(r)] (the band, shifted by the row's

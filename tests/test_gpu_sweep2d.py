@@ -16,9 +16,9 @@ pytestmark = pytest.mark.gpu
 
 # rows: 256 and 512 one-column tiles and one more; columns: less than a
 # wavefront's 128, one column into the second wavefront, two 512-column tiles
-# with 3 columns in the last
+# with 3 columns in the last, a node spread whose two windows take over 64 KB
 @pytest.mark.parametrize("n0,n1", [(256, 40), (257, 129), (512, 9), (513, 40), (7, 127), (6, 515),
-                                   (129, 640)])
+                                   (129, 640), (33, 760)])
 @pytest.mark.parametrize("prec,interp", [("fp32_comp", "spline"), ("fp64", "bicubic_fd")])
 def test_tile_counts(lib, orc, n0, n1, prec, interp):
     wl = W.exchange_2d(n_x=max(n0, n1), n_t=6, k=2, L=5, rho=0.4)
