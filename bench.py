@@ -73,15 +73,15 @@ def flops_per_point_step(pb: dict, picard_mean: float) -> float:
 
 def bytes_per_point_step(pb: dict) -> float:
     """Algorithmic HBM bytes of the sweep kernel per point-step (FP64): read
-    layers n+2..n+K whole (y, z and M_y, M_z: 32 B each) and the values of
-    layer n+1 (16 B), write the values of layer n and the second derivatives
-    of layer n+1 (16 B each)."""
+    the spline coefficients of layers n+2..n+K (c_y, c_z: 16 B each) and the
+    values of layer n+1 (16 B), write the values of layer n and the
+    coefficients of layer n+1 (16 B each)."""
     K = max(pb["k_y"], pb["k_z"])
-    return 32.0 * (K - 1) + 16.0 + 32.0
+    return 16.0 * (K - 1) + 16.0 + 32.0
 
 
 # the sources of the 1-D sweep kernel, its launch and its workspace layout
-KERNEL_SOURCES = ["capi.hip", "sweep.hip", "device_common.h", "kernels.h", "plan_math.cpp", "plan_math.h"]
+KERNEL_SOURCES = ["capi.hip", "sweep.hip", "fused.h", "device_common.h", "kernels.h", "plan_math.cpp", "plan_math.h"]
 
 
 def sources_sha1() -> str:
@@ -247,10 +247,10 @@ def flops_per_point_step_2d(pb: dict, picard_mean: float) -> float:
     return K * L * L * per_node + 2 * L * L + 2 * (3 * K + 1) + 2 * K + picard_mean * 8
 
 
-def window_columns_2d(pb: dict, tile_cols: int = 512) -> float:
+def window_columns_2d(pb: dict, tile_cols: int = 256) -> float:
     """Mean over the node rows (j, l0) of the axis-1 window width per tile
-    column of the 2-D sweep: the tile's columns plus the row's node spread
-    along axis 1, plus 2 (as the plan sizes it)."""
+    column of the FP64 2-D sweep: the columns of a wavefront plus the row's
+    node spread along axis 1 and the spline's reach."""
     import numpy as np
 
     K, L = max(pb["k_y"], pb["k_z"]), pb["L"]
@@ -264,23 +264,23 @@ def window_columns_2d(pb: dict, tile_cols: int = 512) -> float:
         for l0 in range(L):
             s1 = (pb["drift"][1] * j * dt + vol[1][0] * sq * a[l0] + vol[1][1] * sq * a) / dx1
             m1 = np.floor(s1)
-            widths.append(tile_cols + (m1.max() - m1.min()) + 2)
+            widths.append(tile_cols + (m1.max() - m1.min()) + 3)
     return float(np.mean(widths)) / tile_cols
 
 
 def flops_per_point_step_2d_executed(pb: dict, picard_mean: float) -> float:
     """FP64 operations the 2-D sweep executes per point and step (axis-split
-    evaluation).  Per node row (j, l0) and window column, the axis-0 terms
-    U = A0 v(p) + B0 v(p+1) + C0 Mxx(p) + D0 Mxx(p+1) and the same V with
-    Myy, Mxxyy for y, z1, z2 (6 sums of 7 flops), over window_columns_2d
-    columns per point; per tensor node the axis-1 combination
-    A1 U(q) + B1 U(q+1) + C1 V(q) + D1 V(q+1) for y, z1, z2 (3 x 7), the
-    driver (6) and the accumulations (10); per layer j = K_y the y expectation
-    (2 per node); the z combination and each Picard iteration (8)."""
+    evaluation on tensor B-spline coefficients).  Per node row (j, l0) and
+    window column, the axis-0 sums of four coefficients of y, z1, z2 (3 x 7)
+    and the three combinations that the linear driver's sums need (11), over
+    window_columns_2d columns per point; per tensor node two weighted sums of
+    four coefficients added (2 x 8), one formed (7) and added twice (4); per
+    node of layer j = K_y the sum of y (9); the z combination and each Picard
+    iteration (8)."""
     K, L = max(pb["k_y"], pb["k_z"]), pb["L"]
-    per_row = 6 * 7 * window_columns_2d(pb)
-    per_node = 3 * 7 + 6 + 10
-    return (K * L * (per_row + L * per_node) + 2 * L * L + 2 * (3 * K + 1) + 2 * K
+    per_row = 32 * window_columns_2d(pb)
+    per_node = 27
+    return (K * L * (per_row + L * per_node) + 9 * L * L + 2 * (3 * K + 1) + 2 * K
             + picard_mean * 8)
 
 
@@ -404,22 +404,25 @@ def time_solves(B, torch, wl, prec="fp64", reps=5, autotune=True, extra=None):
 
 def toeplitz_flops_per_point_step(pb: dict) -> tuple:
     """Algorithmic and executed FP64 operations of the Toeplitz sweep per point
-    and step: per layer j, 8 products per band entry (expectation and
-    dW-weighted, of y and z, from the values and the second derivatives:
-    16 flops), over the band's nb_j entries (executed: nb_j + 15, the 16 x 16
-    tiles' corners); the combination and Picard are left out (under 1%)."""
+    and step: per layer j, 4 products per band entry (expectation and
+    dW-weighted, of y and z, from the spline's coefficients: 8 flops), over the
+    band's nb_j entries.  Executed: nb_j + 7 entries (the corners of 8 points),
+    or, for bands that do not fit LDS, nb_j + 15 entries from the values and
+    the second derivatives (16 flops); the combination and Picard are left out
+    (under 1%)."""
     K = max(pb["k_y"], pb["k_z"])
     dt = pb["T"] / pb["n_t"]
     dx = (pb["x_max"] - pb["x_min"]) / (pb["n_x"] - 1)
-    alg = exe = 0.0
+    bands = []
     for j in range(1, K + 1):
         m0 = pb["drift"] * j * dt / dx
         rho = pb["vol"] * math.sqrt(j * dt) / dx
         reach = 9.0 * rho + 1.0
         nb = math.ceil(m0 + reach) - math.floor(m0 - reach) + 2
-        alg += 16.0 * nb
-        exe += 16.0 * (nb + 15)
-    return alg, exe
+        bands.append(nb)
+    fits = 32 * sum(bands) <= 160 * 1024  # the bands and windows of all layers in LDS
+    exe = sum(8.0 * (nb + 7) if fits else 16.0 * (nb + 15) for nb in bands)
+    return 8.0 * sum(bands), exe
 
 
 def smoothing_study(B, torch, twin, substeps: int = 8):

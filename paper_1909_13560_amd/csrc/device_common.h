@@ -13,7 +13,6 @@ namespace bsde {
 constexpr int kBlock = 256;        // threads per block of every kernel
 constexpr int kPcrRounds = 5;      // PCR strides 1, 2, 4, 8, 16
 constexpr int kHalo = 32;          // > 1 + 2 + 4 + 8 + 16: reach of the truncated PCR
-constexpr int kPcrMaxPerThread = 8;// spline windows of at most kBlock * 8 records
 constexpr int kSplineTile = 512;   // grid points per block of the standalone spline kernel
 constexpr int kSplineSlots = kSplineTile + 2 * kHalo + 24;  // window of a spline tile, with overhang
 

@@ -35,7 +35,7 @@ template <int P, int WP, int G>
 struct FusedShape {
     static constexpr int T = 64 * P * WP;
     static constexpr int NT = 64 * WP * G;
-    static_assert(NT <= 1024 && kFirOver >= 0, "block size");
+    static_assert(NT <= 1024, "block size");
 };
 
 // ---------------------------------------------------------------------------
