@@ -833,8 +833,6 @@ SweepConfig fused_config(const std::vector<Instance> &all, const std::vector<int
             for (int j = 2; j <= in.K; ++j) reach = std::max(reach, in.win_hi[j] - in.win_lo[j] + 1);
             if (reach > 320 || in.win_hi[1] - in.win_lo[1] + 1 > 160) return c;
         }
-        // the FP64 form holds a group's node addresses one per lane
-        if (!in.f32 && G < 4 && in.K * in.pb.L > 64 * G) return c;
         const size_t need = fused_layout(in, P, W, G).total;
         if (need > max_lds) return c;
         lds = std::max(lds, need);

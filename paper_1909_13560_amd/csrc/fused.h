@@ -306,6 +306,19 @@ struct LdsWindow {
     }
 };
 
+// The list of class c (nodes l = c mod 8 of all layers) in the tables, and the
+// address that a lane holds for it.
+static_assert(kMaxOrder * 8 <= 64, "a class's node addresses fit the lanes of a wavefront");
+__device__ inline void class_list(int K, int L, int c, int &start, int &cnt)
+{
+    start = K * (c * (L >> 3) + min(c, L & 7));
+    cnt = K * ((L >> 3) + (c < (L & 7) ? 1 : 0));
+}
+__device__ inline int2 class_address(const int2 *addr, int start, int cnt, int lane)
+{
+    return addr[cnt > 0 ? start + min(lane, cnt - 1) : 0];
+}
+
 // The nodes of one class (FP64 form): cnt consecutive table entries, whose
 // addresses av (FusedHot::addr) the wavefront holds one per lane.  The loop
 // carries little besides the arithmetic: on small grids a SIMD has two
@@ -459,9 +472,9 @@ __device__ inline void gather_nodes(const char *base, const NodeRecB *recs, int 
 // The sweep kernel.  Sums: the FP64 form adds the nodes of class l mod 8 over
 // the layers K, ..., 2, 1 in each of eight classes; the classes k and k + 4,
 // then k and k + 2, then k and k + 1 are added, in registers within a group
-// and in LDS across groups, so every shape that the plan picks by itself
-// gives the same bits (a batch equals its instances solved alone).  One or two
-// groups (on request only) sum their classes in one accumulator.  The FP32
+// and in LDS across groups, so every shape gives the same bits (a batch equals
+// its instances solved alone).  A class has at most 48 nodes, so a wavefront
+// holds the addresses of its list one per lane.  The FP32
 // form adds all nodes in one sequence per point (its results depend on the
 // order at the level of its own rounding), hence one group; more groups, on
 // request, take whole layers.
@@ -565,18 +578,16 @@ __global__ void __launch_bounds__(64 * WP * G) sweep_fused(const StepArgs s)
             res[v] = make_float2(fed_back_residual(gy, h.npad, i).x, fed_back_residual(g1, h.npad, i).y);
         }
     }
-    // FP32: node offsets for LDS.  FP64: the group's node lists (classes k0 ..
-    // k1 - 1 one after the other), their addresses one per lane
+    // FP32: node offsets for LDS.  FP64: the lists of the group's classes and
+    // their addresses, one per lane
     const int mfirst = F32 && tid < K * h.L ? h.m[tid] : 0;
     int list0[C], lcnt[C];
     int2 av[C];
     if constexpr (!F32) {
 #pragma unroll
-        for (int k = 0; k < C; ++k) {
-            const int k0 = G >= 4 ? grp + k * G : grp * 8 / G, k1 = G >= 4 ? k0 + 1 : (grp + 1) * 8 / G;
-            list0[k] = K * (k0 * (h.L >> 3) + min(k0, h.L & 7));
-            lcnt[k] = K * (k1 * (h.L >> 3) + min(k1, h.L & 7)) - list0[k];
-            av[k] = h.addr[list0[k] + max(min(lane, lcnt[k] - 1), 0)];
+        for (int k = 0; k < C; ++k) {  // the group's first class if it takes them one by one
+            class_list(K, h.L, grp + k * G, list0[k], lcnt[k]);
+            av[k] = class_address(h.addr, list0[k], lcnt[k], lane);
         }
     }
     double cax = 0.0, cbx = 0.0;  // a(t_n, x_i), b(t_n, x_i) of the lane's point
@@ -761,8 +772,64 @@ __global__ void __launch_bounds__(64 * WP * G) sweep_fused(const StepArgs s)
             }
         } else {
             const NodeRecB *recb = const_load(&dn->hot.recb);
+            if constexpr (G < 4) {
+                // four or eight classes one after the other: a class and its
+                // partner are added as soon as both are there, in the order of
+                // the other shapes' sums (s: the sums that wait for theirs)
+                constexpr int NC = 8 / G;
+                const int2 *addr = const_load(&dn->hot.addr);
+                double sy[3][P], sz[3][P];
+                int l0 = list0[0], cnt = lcnt[0];
+                int2 an = av[0];
+#pragma unroll 1
+                for (int e = 0; e < NC; ++e) {
+                    const NodeRecB *recs = recb + l0;
+                    const int2 ac = an;
+                    const int n = cnt;
+                    if (e + 1 < NC) {  // the next class's addresses come during this one's nodes
+                        const int r = e + 1;  // its bits reversed
+                        const int c = NC == 8 ? ((r & 1) << 2) | (r & 2) | (r >> 2) : ((r & 1) << 1) | (r >> 1);
+                        class_list(nK, nL, grp + c * G, l0, cnt);
+                        an = class_address(addr, l0, cnt, lane);
+                    }
 #pragma unroll
-            for (int k = 0; k < C; ++k) {
+                    for (int q = 0; q < P; ++q) Y[0][q] = Z[0][q] = 0.0;
+                    class_nodes<P, DRV>(lane_rec, edge, recs, n, ac, a, drv, first, wfirst, wlast, nx, Y[0],
+                                        Z[0]);
+                    auto meet = [&](int d) {
+#pragma unroll
+                        for (int q = 0; q < P; ++q) {
+                            Y[0][q] = sy[d][q] + Y[0][q];
+                            Z[0][q] = sz[d][q] + Z[0][q];
+                        }
+                    };
+                    auto wait = [&](int d) {
+#pragma unroll
+                        for (int q = 0; q < P; ++q) {
+                            sy[d][q] = Y[0][q];
+                            sz[d][q] = Z[0][q];
+                        }
+                    };
+                    if (!(e & 1)) {
+                        wait(0);
+                    } else {
+                        meet(0);
+                        if (!(e & 2)) {
+                            wait(1);
+                        } else {
+                            meet(1);
+                            if (NC == 8) {
+                                if (!(e & 4))
+                                    wait(2);
+                                else
+                                    meet(2);
+                            }
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < (G < 4 ? 0 : C); ++k) {
                 if constexpr (GATHER)
                     gather_nodes<DRV>(smem, recb + list0[k], lcnt[k], av[k], a, drv,
                                       (double)min(first, nx - 1), cax, cbx, t0, nx, Y[k][0], Z[k][0]);
