@@ -491,8 +491,10 @@ bool build_instance(const bsde_problem &p, Instance &in)
                 const int k = cell - b.klo;
                 return k >= 0 && k < cells ? v[k] : 0.0;
             };
-            in.ex_nl[j] = std::min(std::max(0, -b.klo) + 1, in.nx);
-            in.ex_nr[j] = std::min(std::max(0, b.klo + cells) + 2, in.nx);
+            // the points whose first or last piece lies in the band, no others:
+            // the kernel's window holds the end coefficients for these only
+            in.ex_nl[j] = std::min(std::max(0, 1 - b.klo), in.nx);
+            in.ex_nr[j] = std::min(std::max(0, b.klo + cells + 1), in.nx);
             in.ex_loff[j] = (int)in.ex_corr.size();
             for (int i = 0; i < in.ex_nl[j]; ++i)
                 in.ex_corr.push_back(make_double2(piece(b.i3, -1 - i) + piece(b.i0, -i),
