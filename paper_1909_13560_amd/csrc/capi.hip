@@ -369,7 +369,8 @@ void located_windows(const bsde_problem &p, const std::vector<CoefBounds> &piece
             mx = std::max(mx, q.ahi * t + sq * std::max(q.bhi * ghi, q.blo * glo));
         }
         if (!(mn > -4000.0) || !(mx < 4000.0)) return;
-        lo[j] = std::min((int)std::floor(mn) - 1, 0);
+        // (a node clamped to the right end lies in the cell left of the last point)
+        lo[j] = std::min((int)std::floor(mn) - 1, -1);
         hi[j] = std::max((int)std::floor(mx) + 1, 0);
     }
     in.located = true;

@@ -87,12 +87,66 @@ int check_exact_ends()
     return fails;
 }
 
+// State-dependent coefficients in the fused sweep: every record that a node
+// reads (located as the kernel does, clamped to the grid) lies in its layer's
+// window.
+int check_located_windows()
+{
+    const int T = 64;
+    double a[bsde::kMaxL], w[bsde::kMaxL];
+    for (int nx : {4, 5, 63, 64, 65, 66, 129, 193})
+        for (int k : {1, 3})
+            for (int L : {1, 2, 7})
+                for (double R : {0.01, 0.6, 4.0})
+                    for (double cells = -90.0; cells <= 90.0; cells += 7.5)
+                        for (int kind = 0; kind < 2; ++kind) {  // affine, a table of one row
+                            bsde_problem p = problem(nx, k, L, R, cells);
+                            std::vector<double> tab;
+                            if (kind == 0) {
+                                p.vol_x = 0.3 * p.vol[0][0] / nx;
+                                p.drift_x = 0.1 * p.drift[0] / nx;
+                            } else {
+                                tab.resize(2 * nx);
+                                for (int i = 0; i < nx; ++i) {
+                                    tab[i] = p.drift[0] * (1.0 + 0.2 * std::sin(0.7 * i));
+                                    tab[nx + i] = p.vol[0][0] * (1.0 + 0.3 * std::cos(0.4 * i));
+                                }
+                                p.coef_tab = tab.data();
+                                p.tab_steps = 1;
+                                p.drift[0] = 0.0;
+                            }
+                            Instance in;
+                            EXPECT(build_instance(p, in) && in.located, "n_x %d", nx);
+                            bsde::gauss_hermite(L, a, w);
+                            for (int i = 0; i < nx; ++i) {
+                                const double ax = kind ? tab[i] : p.drift[0] + p.drift_x * i;
+                                const double bx = kind ? tab[nx + i] : p.vol[0][0] + p.vol_x * i;
+                                for (int j = 1; j <= k; ++j)
+                                    for (int l = 0; l < L; ++l) {
+                                        const double dw = std::sqrt(2.0 * j * in.dt) * a[l];
+                                        const double s = std::min(
+                                            std::max(std::fma(bx, dw / in.dx,
+                                                              std::fma(ax, j * in.dt / in.dx, (double)i)),
+                                                     0.0),
+                                            nx - 1.0);
+                                        const int cell = std::min((int)s, nx - 2);
+                                        const int e = cell - 1 - (i / T * T + in.win_lo[j] - 1);
+                                        EXPECT(e >= 0 && e + 3 < T + in.win_hi[j] - in.win_lo[j] + 3,
+                                               "n_x %d K %d L %d R %g drift %g kind %d point %d layer %d: record %d",
+                                               nx, k, L, R, cells, kind, i, j, e);
+                                    }
+                            }
+                        }
+    return fails;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "exact_ends") return check_exact_ends() != 0;
+    if (what == "located_windows") return check_located_windows() != 0;
     std::printf("unknown check\n");
     return 2;
 }

@@ -35,3 +35,7 @@ def checks(tmp_path_factory):
 
 def test_exact_end_corrections_stay_in_the_window(checks):
     checks("exact_ends")
+
+
+def test_located_nodes_stay_in_the_window(checks):
+    checks("located_windows")
