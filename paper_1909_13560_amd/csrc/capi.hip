@@ -71,6 +71,7 @@ struct Instance {
     std::vector<double2> ex_corr;
     int ex_boff[bsde::kMaxOrder + 1] = {}, ex_loff[bsde::kMaxOrder + 1] = {}, ex_roff[bsde::kMaxOrder + 1] = {};
     int ex_nl[bsde::kMaxOrder + 1] = {}, ex_nr[bsde::kMaxOrder + 1] = {};
+    int ex_il[bsde::kMaxOrder + 1] = {}, ex_ir[bsde::kMaxOrder + 1] = {};
     const double *d_ex_band = nullptr;
     const double2 *d_ex_corr = nullptr;
     const bsde::NodeRecB *d_recb = nullptr;
@@ -492,16 +493,22 @@ bool build_instance(const bsde_problem &p, Instance &in)
                 const int k = cell - b.klo;
                 return k >= 0 && k < cells ? v[k] : 0.0;
             };
-            // the points whose first or last piece lies in the band, no others:
-            // the kernel's window holds the end coefficients for these only
-            in.ex_nl[j] = std::min(std::max(0, 1 - b.klo), in.nx);
-            in.ex_nr[j] = std::min(std::max(0, b.klo + cells + 1), in.nx);
+            // the points whose first or last piece lies in the band, no others: the
+            // kernel's window holds the end coefficients for these only, and zero
+            // times a non-finite one would be wrong.  Points il .. from the left
+            // end, ir .. from the right one
+            const int lend = std::min(std::max(0, 1 - b.klo), in.nx);
+            const int rend = std::min(std::max(0, b.klo + cells + 1), in.nx);
+            in.ex_il[j] = std::min(std::max(0, -b.klo - cells), lend);
+            in.ex_ir[j] = std::min(std::max(0, b.klo), rend);
+            in.ex_nl[j] = lend - in.ex_il[j];
+            in.ex_nr[j] = rend - in.ex_ir[j];
             in.ex_loff[j] = (int)in.ex_corr.size();
-            for (int i = 0; i < in.ex_nl[j]; ++i)
+            for (int i = in.ex_il[j]; i < lend; ++i)
                 in.ex_corr.push_back(make_double2(piece(b.i3, -1 - i) + piece(b.i0, -i),
                                                   piece(b.j3, -1 - i) + piece(b.j0, -i)));
             in.ex_roff[j] = (int)in.ex_corr.size();
-            for (int i = 0; i < in.ex_nr[j]; ++i)
+            for (int i = in.ex_ir[j]; i < rend; ++i)
                 in.ex_corr.push_back(make_double2(piece(b.i0, i) + piece(b.i3, i - 1),
                                                   piece(b.j0, i) + piece(b.j3, i - 1)));
         }
@@ -1193,6 +1200,8 @@ bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
                 h.boff[j] = in.ex_boff[j];
                 h.nl[j] = in.ex_nl[j];
                 h.nr[j] = in.ex_nr[j];
+                h.il[j] = in.ex_il[j];
+                h.ir[j] = in.ex_ir[j];
                 h.loff[j] = in.ex_loff[j];
                 h.roff[j] = in.ex_roff[j];
             }

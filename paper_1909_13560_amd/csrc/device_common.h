@@ -194,7 +194,8 @@ struct alignas(64) ExactHot {
     size_t ring_off;
     const double *band;      // per layer ec, wc (nb[j] weights each) at boff[j]
     const double2 *corr;     // per layer the end corrections (E, E[. dW]) of nl[j] points at loff[j]
-                             // (from the left end) and of nr[j] at roff[j] (from the right end)
+                             // (il[j], ... from the left end) and of nr[j] at roff[j] (ir[j], ...
+                             // from the right end)
     int nx, npad, pad_l, K;
     int n0, n0_mod, mod_magic, tile_base;
     int ntiles, lds_d, lds_a, lds_edge;
@@ -204,6 +205,7 @@ struct alignas(64) ExactHot {
     int nb[kMaxOrder + 1], boff[kMaxOrder + 1];
     int lds_win[kMaxOrder + 1], lds_band[kMaxOrder + 1];
     int nl[kMaxOrder + 1], nr[kMaxOrder + 1], loff[kMaxOrder + 1], roff[kMaxOrder + 1];
+    int il[kMaxOrder + 1], ir[kMaxOrder + 1];
 };
 constexpr int kExactTile = 64;  // points of a block of that sweep
 

@@ -303,6 +303,7 @@ __global__ void __launch_bounds__(kBlock) coef_layer(const StepArgs s)
         const bool own = (k >= t0 && k < min(t0 + kSplineTile, nx)) || k == -1 ||
                          (k == nx && tile == d.spline_tiles - 1);
         const double2 v = D[e + kHalo + 1];
+        if (k == 0 || k == nx - 1) wy = wz = 0.0;  // an end value is its own coefficient
         if (own) g.set_der(k, fma(-inv_b, wy, v.x), fma(-inv_b, wz, v.y));
     });
     if (tile == 0) {

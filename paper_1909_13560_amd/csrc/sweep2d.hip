@@ -837,12 +837,12 @@ sweep2b(const Sweep2Args a)
     constexpr int kPre = 1;
     int nslot = a.n % S, njc = 0, nl0 = grp;  // layer and l0 of the row ahead
     const double *nq0 = nullptr;
+    size_t nst = 0;  // bytes from one source row to the next
     int nw0 = 0;
     double pf[kPre][12];
-    auto load_column = [&](const double *q0, int q, double (&r)[12]) {
+    auto load_column = [&](const double *q0, size_t st, int q, double (&r)[12]) {
         // scalar row bases and one 32-bit column offset (a row is below 4 GiB)
         const unsigned o = (unsigned)q * 8u;
-        const size_t st = (size_t)n1 * 8;
 #pragma unroll
         for (int f = 0; f < 3; ++f) {
             const char *v = reinterpret_cast<const char *>(q0 + (size_t)f * a.plane);
@@ -859,11 +859,16 @@ sweep2b(const Sweep2Args a)
         }
         nl0 += kGroups2B;
         const Row2B *rp = a.rowsb + rowi;
-        const int r0 = min(max(i0 + const_load(&rp->m0) - 1, 0), n0 - 4);
+        // a cell outside the grid takes the end row's value: all four rows are that
+        // row, so that nothing else, times zero, enters
+        const int p = i0 + const_load(&rp->m0);
+        const bool in = p >= 0 && p <= n0 - 2;
+        const int r0 = in ? min(max(p - 1, 0), n0 - 4) : p < 0 ? 0 : n0 - 1;
+        nst = in ? (size_t)n1 * 8 : 0;
         nq0 = plane2<double>(a, nslot, 3) + (size_t)r0 * n1;
         nw0 = c0 + const_load(&rp->m1lo) - 1;
 #pragma unroll
-        for (int u = 0; u < kPre; ++u) load_column(nq0, column(nw0, lane + 64 * u), pf[u]);
+        for (int u = 0; u < kPre; ++u) load_column(nq0, nst, column(nw0, lane + 64 * u), pf[u]);
     };
     if (grp < nrows) ahead(grp);
     for (int rowi = grp; rowi < nrows; rowi += kGroups2B) {
@@ -881,12 +886,9 @@ sweep2b(const Sweep2Args a)
                b3 = const_load(&rp->b[3]);
         // (the loads take the rows min(max(p - 1, 0), n0 - 4) ..)
         const int p = i0 + m0;
-        if (p < 0) {  // the value at the first row
+        if (p < 0 || p > n0 - 2) {  // the value at the end row
             b0 = 1.0;
             b1 = b2 = b3 = 0.0;
-        } else if (p > n0 - 2) {  // the value at the last row
-            b3 = 1.0;
-            b0 = b1 = b2 = 0.0;
         } else {
             if (p == 0) {  // c(-1) = 2 c(0) - c(1)
                 const double x = b0;
@@ -904,6 +906,7 @@ sweep2b(const Sweep2Args a)
             }
         }
         const double *q0 = nq0;
+        const size_t st = nst;
         const int w0 = nw0;  // window column 0
         const double H = const_load(&rp->H), Gu = const_load(&rp->Gu), Gy = const_load(&rp->Gy),
                      C = const_load(&rp->C), ey = const_load(&rp->ey);
@@ -934,7 +937,7 @@ sweep2b(const Sweep2Args a)
         for (int e = lane + 64 * kPre; e - lane < W + kEdge2B; e += 128) {
             double r[2][12];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) load_column(q0, staged(e + 64 * u), r[u]);
+            for (int u = 0; u < 2; ++u) load_column(q0, st, staged(e + 64 * u), r[u]);
 #pragma unroll
             for (int u = 0; u < 2; ++u) put(e + 64 * u, r[u]);
         }
@@ -1003,16 +1006,19 @@ sweep2b(const Sweep2Args a)
             }
         }
         // corrections next to the ends of axis 1: x the sum of the weights, y
-        // of the weights times gu
+        // of the weights times gu.  Non-finite end values enter the columns that
+        // have a weight only: zero times one would spread it over the tile
         auto correct = [&](const double2 (&c)[4], int i, int o) {  // end columns i (inner), o (outer)
             const double e0 = we[3 * i] - we[3 * o], e1 = we[3 * i + 1] - we[3 * o + 1],
                          e2 = we[3 * i + 2] - we[3 * o + 2];
+            const bool finite = __all(isfinite(fabs(e0) + (fabs(e1) + fabs(e2))));
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                Y[k] = fma(-H * c[k].x, e0, Y[k]);
-                Z1[k] = fma(-c[k].x, e1, Z1[k]);
-                Z2[k] = fma(-c[k].y, e0, fma(-c[k].x, e2, Z2[k]));
-            }
+            for (int k = 0; k < 4; ++k)
+                if (finite || c[k].x != 0.0) {
+                    Y[k] = fma(-H * c[k].x, e0, Y[k]);
+                    Z1[k] = fma(-c[k].x, e1, Z1[k]);
+                    Z2[k] = fma(-c[k].y, e0, fma(-c[k].x, e2, Z2[k]));
+                }
         };
         if (near_l || near_r) correct(kc, near_l ? 1 : 2, near_l ? 0 : 3);
         if (near_l && near_r) {
@@ -1037,7 +1043,7 @@ sweep2b(const Sweep2Args a)
 #pragma unroll
                     for (int k = 0; k < 4; ++k)
                         r[u][k] = *reinterpret_cast<const double *>(reinterpret_cast<const char *>(q0) +
-                                                                    k * (size_t)n1 * 8 + o);
+                                                                    k * st + o);
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
@@ -1071,9 +1077,10 @@ sweep2b(const Sweep2Args a)
                 for (int k = 0; k < 4; ++k) {
                     const int c = left ? col + k : n1 - 1 - (col + k);
                     const double4 v = t[(size_t)rowi * n + min(max(c, 0), n - 1)];
-                    const bool in = c >= 0 && c < n;
-                    Y[k] = fma(in ? -ey * v.x : 0.0, e0, Y[k]);
-                    Z2[k] = fma(in ? -v.z : 0.0, e0, Z2[k]);
+                    if (c >= 0 && c < n && v.x != 0.0) {
+                        Y[k] = fma(-ey * v.x, e0, Y[k]);
+                        Z2[k] = fma(-v.z, e0, Z2[k]);
+                    }
                 }
             };
             if (near_l) correct_y(a.corr_l, a.nl, true);

@@ -516,8 +516,8 @@ __global__ void __launch_bounds__(256 * G) sweep_exact(const StepArgs s)
             const double2 v = D[e + kHalo + 1];
             const int k = r1 + e;
             double2 c = make_double2(fma(-inv_b, wy, v.x), fma(-inv_b, wz, v.y));
-            if (k < 0) c = end0;
-            if (k >= nx) c = end1;
+            if (k <= 0) c = end0;  // (an end value is its own coefficient)
+            if (k >= nx - 1) c = end1;
             w1[slot8(e)] = c;
         });
     }
@@ -605,8 +605,8 @@ __global__ void __launch_bounds__(256 * G) sweep_exact(const StepArgs s)
                   k.y * (const_load(&t.cz_wy[j]) * ey + const_load(&t.cz_wz[j]) * ez);
         };
         const double2 *e = edge + 4 * (j - 1);
-        if (i < nl) correct(h.corr[const_load(&d.ex.loff[j]) + i], e[1], e[0]);
-        const int q = nx - 1 - i;
+        const int p = i - const_load(&d.ex.il[j]), q = nx - 1 - i - const_load(&d.ex.ir[j]);
+        if (p >= 0 && p < nl) correct(h.corr[const_load(&d.ex.loff[j]) + p], e[1], e[0]);
         if (q >= 0 && q < nr) correct(h.corr[const_load(&d.ex.roff[j]) + q], e[2], e[3]);
     }
     SweepArgs fa{};

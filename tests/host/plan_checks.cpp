@@ -47,8 +47,8 @@ bsde_problem problem(int nx, int k, int L, double R, double cells, int n_t = 64)
 
 // Exact expectations on B-spline coefficients: a point that takes the end
 // corrections of layer n+1 finds both end coefficients in its block's window
-// (the kernel keeps only what the window holds), and every point whose basis
-// functions reach over an end takes them.
+// (the kernel keeps only what the window holds), and the points that take
+// them are those whose basis functions reach over an end.
 int check_exact_ends()
 {
     const int T = bsde::kExactTile;
@@ -64,10 +64,11 @@ int check_exact_ends()
                         const ExactLds l = exact_layout(in, G);
                         for (int i = 0; i < nx; ++i) {
                             const int lo = i / T * T + l.lo[1], hi = lo + l.W[1];  // records [lo, hi)
-                            if (i < in.ex_nl[1])
+                            const int pl = i - in.ex_il[1], pr = nx - 1 - i - in.ex_ir[1];
+                            if (pl >= 0 && pl < in.ex_nl[1])
                                 EXPECT(lo <= 0 && 1 < hi, "n_x %d K %d R %g drift %g point %d: left end", nx,
                                        k, R, cells, i);
-                            if (nx - 1 - i < in.ex_nr[1])
+                            if (pr >= 0 && pr < in.ex_nr[1])
                                 EXPECT(lo <= nx - 2 && nx - 1 < hi,
                                        "n_x %d K %d R %g drift %g point %d: right end", nx, k, R, cells, i);
                         }
@@ -79,8 +80,11 @@ int check_exact_ends()
                                 const int q = nx - 1 - i;
                                 const bool left = reached(-1 - i) || reached(-i);
                                 const bool right = reached(q) || reached(q - 1);
-                                EXPECT(!left || i < in.ex_nl[j], "n_x %d layer %d point %d", nx, j, i);
-                                EXPECT(!right || q < in.ex_nr[j], "n_x %d layer %d point %d", nx, j, i);
+                                const int pl = i - in.ex_il[j], pr = q - in.ex_ir[j];
+                                EXPECT(left == (pl >= 0 && pl < in.ex_nl[j]), "n_x %d layer %d point %d", nx,
+                                       j, i);
+                                EXPECT(right == (pr >= 0 && pr < in.ex_nr[j]), "n_x %d layer %d point %d", nx,
+                                       j, i);
                             }
                         }
                     }
