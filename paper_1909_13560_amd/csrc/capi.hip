@@ -377,10 +377,6 @@ void located_windows(const bsde_problem &p, const std::vector<CoefBounds> &piece
     in.located = true;
     in.win_lo = lo;
     in.win_hi = hi;
-    for (int j = 1; j <= in.K; ++j) {
-        in.m_min = std::min(in.m_min, lo[j]);
-        in.m_max = std::max(in.m_max, hi[j]);
-    }
 }
 
 // Node tables of eq (20)-(21) on the uniform grid (Section 3.2): the node
@@ -472,7 +468,6 @@ bool build_instance(const bsde_problem &p, Instance &in)
         in.m_max = std::max(in.m_max, hi);
     }
     in.h0 = p.k_y * in.dt * gy[0];
-    const int node_lo = in.m_min, node_hi = in.m_max;
     if (in.gather && !in.f32 && p.z_form == BSDE_ZFORM_EZ) located_windows(p, pieces, in, a);
     if (in.exact) {
         // exact Gaussian expectations: the band of every layer; the ghosts
@@ -513,8 +508,8 @@ bool build_instance(const bsde_problem &p, Instance &in)
                                                   piece(b.j0, i) + piece(b.j3, i - 1)));
         }
     }
-    // reported: the nodes at the coefficients of the table, not the windows' bounds
-    in.reach = in.located ? std::max(-node_lo, node_hi + 1) : std::max(-in.m_min, in.m_max + 1);
+    in.reach = std::max(-in.m_min, in.m_max + 1);
+    // (located nodes need one ghost either side: their windows' loads are clamped)
     in.pad_l = std::max(0, -in.m_min) + 1;
     // right ghosts cover the overhang of the last tile of any configuration
     in.pad_r = std::max(0, in.m_max) + kBlock * kMaxP + 2 + (in.exact ? 64 : 0);

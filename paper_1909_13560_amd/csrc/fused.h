@@ -537,6 +537,9 @@ __global__ void __launch_bounds__(64 * WP * G) sweep_fused(const StepArgs s)
         return Slot<F32>{base, base + (size_t)h.npad * sizeof(typename PR::E), h.pad_l};
     };
     auto record = [&](const Slot<F32> &g, int k) {
+        // located nodes are clamped to the grid and read one record beyond it at
+        // most; their windows' bounds may lie further out than the ring's ghosts
+        if constexpr (GATHER) k = min(max(k, -1), nx);
         if constexpr (F32) {
             const float2 v = g.val(k), m = g.der(k);
             return make_float4(v.x, v.y, m.x, m.y);

@@ -144,6 +144,27 @@ int check_located_windows()
     return fails;
 }
 
+// The ring of a state-dependent problem: ghosts for its constant part's nodes
+// and no more (the windows of located nodes do not enlarge the workspace).
+int check_located_ghosts()
+{
+    for (int nx : {65, 2001})
+        for (int k : {1, 3, 6})
+            for (double R : {0.6, 9.0, 60.0})
+                for (double slope : {0.001, 0.3, 20.0}) {
+                    bsde_problem p = problem(nx, k, 16, R, 1.5);
+                    p.vol_x = slope * p.vol[0][0] / nx;
+                    Instance in;
+                    EXPECT(build_instance(p, in), "n_x %d", nx);
+                    const int lo = *std::min_element(in.m.begin(), in.m.end());
+                    const int hi = *std::max_element(in.m.begin(), in.m.end());
+                    EXPECT(in.pad_l == std::max(0, -lo) + 1 && in.pad_r == std::max(0, hi) + 1026,
+                           "n_x %d K %d R %g slope %g: %d, %d ghosts for nodes %d..%d", nx, k, R, slope,
+                           in.pad_l, in.pad_r, lo, hi);
+                }
+    return fails;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -151,6 +172,7 @@ int main(int argc, char **argv)
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "exact_ends") return check_exact_ends() != 0;
     if (what == "located_windows") return check_located_windows() != 0;
+    if (what == "located_ghosts") return check_located_ghosts() != 0;
     std::printf("unknown check\n");
     return 2;
 }

@@ -39,3 +39,7 @@ def test_exact_end_corrections_stay_in_the_window(checks):
 
 def test_located_nodes_stay_in_the_window(checks):
     checks("located_windows")
+
+
+def test_located_windows_do_not_enlarge_the_ring(checks):
+    checks("located_ghosts")
