@@ -872,47 +872,61 @@ std::vector<int2> fused_addresses(const Instance &in, const FusedLds &lds, int P
     return v;
 }
 
+// Shapes that the plan and the autotuner choose from (all of them add the nodes
+// in the same order, so they give the same bits), with the time of a step as
+// measured, in us: 256 CUs share the tiles, the first of a CU takes
+//   first + first_node K L + first_kb LDS     and each further one
+//   tile + node K L + kb LDS (+ alone where the LDS leaves room for one block).
+// LDS in KiB.  Fitted to solves of 500 to 1048576 points, K L = 4 to 128 and
+// stability ratios 3 to 180 (max error 7 to 10% in FP64, 8 to 25% in the FP32
+// form).  Where the lines cross, measured a step: 65536 points, K =
+// 4, L = 16: 64-point tiles 14.0 us, 256 10.3, 1024 19.5; 262144: 42.2, 23.3, 21.1.
+// 1048576 points, K = 1, L = 16: four groups a 1024-point tile 38.7 us, two 30.0,
+// where few nodes leave little to share out; K = 4: 74.4 and 82.7.  FP32 form, K
+// L = 16: 256-point tiles 8.0, 512 8.3, 1024 10.7 us on 32768 points, 34.5, 34.3
+// and 39.3 on 1048576.
 struct Shape {
     int P, W, G;
+    double first, first_node, first_kb, tile, node, kb, alone;
 };
-// Shapes that the plan and the autotuner choose from: all of them add the
-// nodes in the same order, so they give the same bits.
-constexpr Shape kShapes64[] = {{1, 1, 8}, {2, 1, 8}, {4, 1, 8}, {4, 4, 4}};
-constexpr Shape kShapes32[] = {{1, 2, 1}, {1, 4, 1}, {1, 8, 1}, {1, 16, 1}};
+constexpr Shape kShapes64[] = {{1, 1, 8, 4.0, 0.032, 0.023, 1.37, 0.0114, 0.0063, 2.75},
+                               {2, 1, 8, 3.9, 0.038, 0.023, 1.49, 0.0196, 0.0061, 2.04},
+                               {4, 1, 8, 4.8, 0.064, 0.021, 1.14, 0.0330, 0.0189, 2.40},
+                               {4, 4, 4, 8.5, 0.178, 0.0, 6.08, 0.169, 0.0041, 0.0},
+                               {4, 4, 2, 6.6, 0.200, 0.033, 0.5, 0.130, 0.0550, 3.20}};
+constexpr Shape kShapes32[] = {{1, 4, 1, 5.5, 0.096, 0.046, 0.73, 0.0338, 0.0216, 0.0},
+                               {1, 8, 1, 5.4, 0.106, 0.035, 1.95, 0.0496, 0.0266, 8.08},
+                               {1, 16, 1, 6.5, 0.161, 0.026, 5.41, 0.183, 0.0209, 0.0}};
+// exp at every node: 30 cycles for 64 points (FP64 and FP32 form)
+constexpr double kExpNode = 0.0125;
 
-// Estimated time of a step of a group (clock cycles of a CU) with a fused
-// shape, summed over four steps spread over the group's length (the set of
-// active instances shrinks).  256 CUs share the active tiles; a tile costs its
-// node loops (`cn` instructions per node and point, 64 lanes a clock) and its
-// window loads, and every round of co-resident blocks the latency of its
-// first loads, spline, barriers and finish: 7000 cycles measured on small
-// grids, 11000 where a CU holds one block, whose phases nothing overlaps.
-// Measured (FP64 bid-ask, K = 4, L = 16): 262144 points 21.4 ms with 1024-point
-// tiles, 24.1 ms with 256; a batch of 48 instances 10.6 against 9.5 ms; 4000
-// points 1.51 ms with 64-point tiles, 2.2 ms with 256.
-double fused_cost(const std::vector<Instance> &all, const std::vector<int> &members, const SweepConfig &c)
+// Estimated time of a step of a group with a fused shape (us), the mean of four
+// steps spread over the group's length (the set of active instances shrinks).
+double fused_cost(const std::vector<Instance> &all, const std::vector<int> &members, const SweepConfig &c,
+                  const Shape &q)
 {
     const int T = 64 * c.P * c.W, NT = 64 * c.W * c.G;
-    const int res = std::max(1, std::min((int)(163840 / c.lds), 2048 / NT));
+    const bool alone = std::min(163840 / c.lds, (size_t)2048 / NT) < 2;
+    const double kb = c.lds / 1024.0;
     int longest = 1;
     for (int b : members) longest = std::max(longest, all[b].steps);
     double cost = 0.0;
     for (int k = 0; k < 4; ++k) {
-        double tiles = 0.0, work = 0.0;
+        double tiles = 0.0, first = 0.0, more = 0.0;  // the latter two: tile by tile
         for (int b : members) {
             const Instance &in = all[b];
             if (in.steps <= (long)longest * k / 4) continue;
-            const double t = (in.nx + T - 1) / T;
-            const double cn = in.f32 ? 23.0 : in.pb.driver == BSDE_DRIVER_EXP ? 55.0 : 18.0;
-            double rec = 0.0;
-            for (int j = 1; j <= in.K; ++j) rec += T + in.win_hi[j] - in.win_lo[j];
+            const double t = (in.nx + T - 1) / T, kl = (double)in.K * in.pb.L;
+            const double ex = in.pb.driver == BSDE_DRIVER_EXP ? kExpNode * T / 64.0 * kl : 0.0;
             tiles += t;
-            work += t * (T * cn * in.K * in.pb.L / 64.0 + rec * 0.5);
+            first += t * (q.first + q.first_node * kl + ex);
+            more += t * (q.tile + q.node * kl + ex);
         }
-        const double per_cu = std::ceil(tiles / 256.0);
-        cost += work / tiles * per_cu + (res == 1 ? 11000.0 : 7000.0) * std::ceil(per_cu / res);
+        first = first / tiles + q.first_kb * kb;
+        more = more / tiles + q.kb * kb + (alone ? q.alone : 0.0);
+        cost += first + (std::ceil(tiles / 256.0) - 1.0) * more;
     }
-    return cost;
+    return cost / 4.0;
 }
 
 // The cheapest fused shape, or lds = 0 if none fits.
@@ -924,7 +938,7 @@ SweepConfig best_fused(const std::vector<Instance> &all, const std::vector<int> 
     auto consider = [&](const Shape &q) {
         const SweepConfig c = fused_config(all, members, q.P, q.W, q.G, max_lds);
         if (!c.lds) return;
-        const double t = fused_cost(all, members, c);
+        const double t = fused_cost(all, members, c, q);
         if (!best.lds || t < cost) {
             best = c;
             cost = t;

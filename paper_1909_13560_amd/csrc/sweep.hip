@@ -523,8 +523,8 @@ hipError_t gather_by_driver(int driver, const StepArgs &a, int blocks, hipStream
 
 #undef BSDE_BY_DRIVER
 
-// The shapes built: X(P, WP, G, forms), forms 1 FP64, 2 FP32, 3 both.  The
-// four-wavefront shapes with one or two groups are for requests (BSDE_SWEEP).
+// The shapes built: X(P, WP, G, forms), forms 1 FP64, 2 FP32, 3 both.  The plan
+// chooses among kShapes64 and kShapes32; the others are for requests (BSDE_SWEEP).
 #define BSDE_FUSED_SHAPES(X) \
     X(1, 4, 1, 3)            \
     X(1, 4, 2, 3)            \

@@ -165,6 +165,58 @@ int check_located_ghosts()
     return fails;
 }
 
+// The shape of a single constant-coefficient solve against the measured times
+// of a step (us) of the shapes it can take: within 6% of the fastest.
+int check_shapes()
+{
+    struct Row {
+        int f32, nx, K, L;
+        double R;
+        std::vector<std::pair<std::vector<int>, double>> us;  // {P, W, G}, time
+    };
+    const std::vector<Row> rows = {
+        {0, 4000, 4, 16, 16, {{{1, 1, 8}, 6.9}, {{4, 1, 8}, 10.3}}},
+        {0, 65536, 1, 4, 8, {{{1, 1, 8}, 8.7}, {{2, 1, 8}, 6.0}, {{4, 1, 8}, 5.8}, {{4, 4, 4}, 8.4}, {{4, 4, 2}, 8.5}}},
+        {0, 65536, 4, 16, 16, {{{1, 1, 8}, 14.0}, {{2, 1, 8}, 10.8}, {{4, 1, 8}, 10.2}, {{4, 4, 4}, 19.6}, {{4, 4, 2}, 21.8}}},
+        {0, 262144, 1, 16, 16, {{{1, 1, 8}, 29.8}, {{2, 1, 8}, 19.5}, {{4, 1, 8}, 14.1}, {{4, 4, 4}, 11.8}, {{4, 4, 2}, 12.0}}},
+        {0, 262144, 2, 8, 8, {{{1, 1, 8}, 30.7}, {{2, 1, 8}, 19.7}, {{4, 1, 8}, 14.9}, {{4, 4, 4}, 12.4}, {{4, 4, 2}, 12.8}}},
+        {0, 262144, 4, 16, 16, {{{1, 1, 8}, 42.1}, {{2, 1, 8}, 29.4}, {{4, 1, 8}, 23.4}, {{4, 4, 4}, 21.2}, {{4, 4, 2}, 23.7}}},
+        {0, 1048576, 1, 4, 8, {{{1, 1, 8}, 95.0}, {{2, 1, 8}, 54.3}, {{4, 1, 8}, 35.9}, {{4, 4, 4}, 29.9}, {{4, 4, 2}, 22.8}}},
+        {0, 1048576, 1, 16, 16, {{{1, 1, 8}, 109.3}, {{2, 1, 8}, 65.6}, {{4, 1, 8}, 43.8}, {{4, 4, 4}, 38.7}, {{4, 4, 2}, 30.0}}},
+        {0, 1048576, 2, 8, 8, {{{1, 1, 8}, 110.9}, {{2, 1, 8}, 65.8}, {{4, 1, 8}, 44.7}, {{4, 4, 4}, 39.8}, {{4, 4, 2}, 32.5}}},
+        {0, 1048576, 2, 16, 16, {{{1, 1, 8}, 122.9}, {{2, 1, 8}, 75.9}, {{4, 1, 8}, 53.4}, {{4, 4, 4}, 49.4}, {{4, 4, 2}, 53.4}}},
+        {0, 1048576, 4, 16, 16, {{{1, 1, 8}, 154.6}, {{2, 1, 8}, 101.8}, {{4, 1, 8}, 77.3}, {{4, 4, 4}, 74.4}, {{4, 4, 2}, 82.7}}},
+        {1, 4000, 4, 16, 16, {{{1, 4, 1}, 13.9}, {{1, 8, 1}, 14.6}, {{1, 16, 1}, 20.0}}},
+        {1, 32768, 1, 16, 16, {{{1, 4, 1}, 8.2}, {{1, 8, 1}, 8.4}, {{1, 16, 1}, 10.7}}},
+        {1, 131072, 4, 16, 16, {{{1, 4, 1}, 16.4}, {{1, 8, 1}, 15.2}, {{1, 16, 1}, 20.5}}},
+        {1, 262144, 4, 16, 16, {{{1, 4, 1}, 26.9}, {{1, 8, 1}, 20.9}, {{1, 16, 1}, 21.2}}},
+        {1, 1048576, 1, 4, 8, {{{1, 4, 1}, 27.3}, {{1, 8, 1}, 27.5}, {{1, 16, 1}, 29.6}}},
+        {1, 1048576, 1, 16, 16, {{{1, 4, 1}, 34.5}, {{1, 8, 1}, 34.3}, {{1, 16, 1}, 39.3}}},
+        {1, 1048576, 2, 8, 8, {{{1, 4, 1}, 35.2}, {{1, 8, 1}, 35.8}, {{1, 16, 1}, 40.5}}},
+        {1, 1048576, 4, 16, 16, {{{1, 4, 1}, 77.6}, {{1, 8, 1}, 65.2}, {{1, 16, 1}, 77.2}}},
+    };
+    for (const Row &r : rows) {
+        bsde_problem p = problem(r.nx, r.K, r.L, r.R, 0.3);
+        p.prec = r.f32 ? BSDE_FP32_COMP : BSDE_FP64;
+        p.driver = BSDE_DRIVER_BIDASK;
+        p.p[3] = 0.2;
+        std::vector<Instance> all(1);
+        EXPECT(build_instance(p, all[0]), "n_x %d", r.nx);
+        Group g;
+        g.f32 = r.f32 != 0;
+        g.members = {0};
+        const SweepConfig c = default_config(all, g, kLds);
+        double best = 1e9, own = 1e9;
+        for (const auto &q : r.us) {
+            best = std::min(best, q.second);
+            if (q.first == std::vector<int>{c.P, c.W, c.G}) own = q.second;
+        }
+        EXPECT(c.path == PATH_FUSED && own <= 1.06 * best, "f32 %d n_x %d K %d L %d: shape %d %d %d, %g against %g us",
+               r.f32, r.nx, r.K, r.L, c.P, c.W, c.G, own, best);
+    }
+    return fails;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -173,6 +225,7 @@ int main(int argc, char **argv)
     if (what == "exact_ends") return check_exact_ends() != 0;
     if (what == "located_windows") return check_located_windows() != 0;
     if (what == "located_ghosts") return check_located_ghosts() != 0;
+    if (what == "shapes") return check_shapes() != 0;
     std::printf("unknown check\n");
     return 2;
 }

@@ -43,3 +43,7 @@ def test_located_nodes_stay_in_the_window(checks):
 
 def test_located_windows_do_not_enlarge_the_ring(checks):
     checks("located_ghosts")
+
+
+def test_shapes_follow_the_measured_times(checks):
+    checks("shapes")
