@@ -876,8 +876,8 @@ std::vector<int2> fused_addresses(const Instance &in, const FusedLds &lds, int P
 // in the same order, so they give the same bits), with the time of a step as
 // measured, in us: 256 CUs share the tiles, the first of a CU takes
 //   first + first_node K L + first_kb LDS     and each further one
-//   tile + node K L + kb LDS (+ alone where the LDS leaves room for one block).
-// LDS in KiB.  Fitted to solves of 500 to 1048576 points, K L = 4 to 128 and
+//   tile + node K L + kb LDS (+ alone + alone_node K L where the LDS leaves room
+// for one block), and both exp K L T / 64 where the driver has an exponential.  LDS in KiB.  Fitted to solves of 500 to 1048576 points, K L = 4 to 128 and
 // stability ratios 3 to 180 (max error 7 to 10% in FP64, 8 to 25% in the FP32
 // form).  Where the lines cross, measured a step: 65536 points, K =
 // 4, L = 16: 64-point tiles 14.0 us, 256 10.3, 1024 19.5; 262144: 42.2, 23.3, 21.1.
@@ -887,18 +887,16 @@ std::vector<int2> fused_addresses(const Instance &in, const FusedLds &lds, int P
 // and 39.3 on 1048576.
 struct Shape {
     int P, W, G;
-    double first, first_node, first_kb, tile, node, kb, alone;
+    double first, first_node, first_kb, tile, node, kb, alone, alone_node, exp;
 };
-constexpr Shape kShapes64[] = {{1, 1, 8, 4.0, 0.032, 0.023, 1.37, 0.0114, 0.0063, 2.75},
-                               {2, 1, 8, 3.9, 0.038, 0.023, 1.49, 0.0196, 0.0061, 2.04},
-                               {4, 1, 8, 4.8, 0.064, 0.021, 1.14, 0.0330, 0.0189, 2.40},
-                               {4, 4, 4, 8.5, 0.178, 0.0, 6.08, 0.169, 0.0041, 0.0},
-                               {4, 4, 2, 6.6, 0.200, 0.033, 0.5, 0.130, 0.0550, 3.20}};
-constexpr Shape kShapes32[] = {{1, 4, 1, 5.5, 0.096, 0.046, 0.73, 0.0338, 0.0216, 0.0},
-                               {1, 8, 1, 5.4, 0.106, 0.035, 1.95, 0.0496, 0.0266, 8.08},
-                               {1, 16, 1, 6.5, 0.161, 0.026, 5.41, 0.183, 0.0209, 0.0}};
-// exp at every node: 30 cycles for 64 points (FP64 and FP32 form)
-constexpr double kExpNode = 0.0125;
+constexpr Shape kShapes64[] = {{1, 1, 8, 4.0, 0.032, 0.023, 1.37, 0.0114, 0.0063, 1.9, 0.0105, 0.0300},
+                               {2, 1, 8, 3.9, 0.038, 0.023, 1.49, 0.0196, 0.0061, 1.4, 0.0105, 0.0220},
+                               {4, 1, 8, 4.8, 0.064, 0.021, 1.14, 0.0330, 0.0189, 2.0, 0.0105, 0.0165},
+                               {4, 4, 4, 8.5, 0.178, 0.0, 6.08, 0.169, 0.0041, 0.0, 0.0, 0.0130},
+                               {4, 4, 2, 6.6, 0.200, 0.033, 0.5, 0.130, 0.0550, 3.20, 0.0, 0.0130}};
+constexpr Shape kShapes32[] = {{1, 4, 1, 5.5, 0.096, 0.046, 0.73, 0.0338, 0.0216, 0.0, 0.0, 0.0125},
+                               {1, 8, 1, 5.4, 0.106, 0.035, 1.95, 0.0496, 0.0266, 8.08, 0.0, 0.0125},
+                               {1, 16, 1, 6.5, 0.161, 0.026, 5.41, 0.183, 0.0209, 0.0, 0.0, 0.0125}};
 
 // Estimated time of a step of a group with a fused shape (us), the mean of four
 // steps spread over the group's length (the set of active instances shrinks).
@@ -917,24 +915,24 @@ double fused_cost(const std::vector<Instance> &all, const std::vector<int> &memb
             const Instance &in = all[b];
             if (in.steps <= (long)longest * k / 4) continue;
             const double t = (in.nx + T - 1) / T, kl = (double)in.K * in.pb.L;
-            const double ex = in.pb.driver == BSDE_DRIVER_EXP ? kExpNode * T / 64.0 * kl : 0.0;
+            const double ex = in.pb.driver == BSDE_DRIVER_EXP ? q.exp * T / 64.0 * kl : 0.0;
             tiles += t;
             first += t * (q.first + q.first_node * kl + ex);
-            more += t * (q.tile + q.node * kl + ex);
+            more += t * (q.tile + q.node * kl + (alone ? q.alone + q.alone_node * kl : 0.0) + ex);
         }
         first = first / tiles + q.first_kb * kb;
-        more = more / tiles + q.kb * kb + (alone ? q.alone : 0.0);
+        more = more / tiles + q.kb * kb;
         cost += first + (std::ceil(tiles / 256.0) - 1.0) * more;
     }
     return cost / 4.0;
 }
 
-// The cheapest fused shape, or lds = 0 if none fits.
+// The cheapest fused shape and its time (us), or lds = 0 if none fits.
 SweepConfig best_fused(const std::vector<Instance> &all, const std::vector<int> &members, bool f32,
-                       size_t max_lds)
+                       size_t max_lds, double &cost)
 {
     SweepConfig best{PATH_FUSED, 1, 1, 0, 4};
-    double cost = 0.0;
+    cost = 0.0;
     auto consider = [&](const Shape &q) {
         const SweepConfig c = fused_config(all, members, q.P, q.W, q.G, max_lds);
         if (!c.lds) return;
@@ -982,6 +980,44 @@ int direct_splits(const std::vector<Instance> &all, const std::vector<int> &memb
     return (int)std::max(1L, std::min<long>({want, 16L, (long)chunks}));
 }
 
+// Time of a step of a group with the direct kernel and its spline launch (us),
+// as measured: n 64-point tiles a CU, three launches where a tile is split over
+// blocks, else two and at least the chain of a tile's loads.  K = 4, L = 16:
+// 14.4 us on 16384 points, 29.4 on 131072 (split), 35.0 on 262144, 118 on 1048576.
+double direct_cost(const std::vector<Instance> &all, const std::vector<int> &members)
+{
+    double tiles = 0.0, node = 0.0, layers = 0.0;  // the latter two: tile by tile
+    for (int b : members) {
+        const Instance &in = all[b];
+        const double t = (in.nx + 63) / 64;
+        tiles += t;
+        layers += t * in.K;
+        node += t * in.K * in.pb.L;
+    }
+    const double n = std::ceil(tiles / 256.0), kl = node / tiles;
+    const double ex = all[members[0]].pb.driver == BSDE_DRIVER_EXP ? 0.011 * kl : 0.0;
+    if (direct_splits(all, members) > 1) return 11.7 + 0.25 * layers / tiles + n * (0.17 + 0.032 * kl + ex);
+    return std::max(9.6 + 0.2 * kl, 7.2 + n * (0.17 + 0.0245 * kl + ex));
+}
+
+// Whether an instance takes the fused sweep: always where it fits in the FP32
+// form (its sums, in another order, are part of the results).  In FP64 where it
+// is the faster on this instance alone: windows so wide that only small tiles
+// fit (one block of 64 points a CU) load more per point than the direct kernel
+// reads.  K = 4, L = 16, stability ratio 105, a step: 6.6 us against 14.4 direct
+// on 16384 points, 10.9 and 11.9 on 32768, 18.9 and 14.9 on 65536, 94 and 36 on
+// 262144; ratio 90 on 262144 points: 38.1 and 35.5.  The rule looks at no other
+// instance of a batch, so that a batch gives the bits of its instances alone; a
+// large batch of small grids with such windows runs faster on the direct kernel
+// (48 of 4000 points, ratio 105: 78 and 44 us a step), which bsde_autotune finds.
+bool takes_fused(const std::vector<Instance> &all, int b, size_t max_lds)
+{
+    double fused = 0.0;
+    const bool f32 = all[b].f32;
+    if (!best_fused(all, {b}, f32, max_lds, fused).lds) return false;
+    return f32 || fused <= direct_cost(all, {b});
+}
+
 // S: blocks per tile (P = 1 only); 0 picks direct_splits.
 SweepConfig direct_config(const std::vector<Instance> &all, const std::vector<int> &members,
                           bool f32, int P, int S = 0)
@@ -997,7 +1033,8 @@ SweepConfig direct_config(const std::vector<Instance> &all, const std::vector<in
 }
 
 // Default shape: the fused kernel in the shape that the cost estimate favours;
-// the direct kernel when no window fits in LDS.  BSDE_SWEEP = "fused:P:G",
+// the direct kernel where that is faster (takes_fused) or no window fits in LDS.
+// BSDE_SWEEP = "fused:P:G",
 // "fused:P:G:W" or "direct:P:S" overrides; bsde_autotune replaces the choice
 // by the fastest measured shape.
 bool group_gathers(const std::vector<Instance> &all, const std::vector<int> &members)
@@ -1137,8 +1174,13 @@ SweepConfig default_config(const std::vector<Instance> &all, const Group &g, siz
         if (std::sscanf(env, "direct:%d:%d", &P, &S) >= 1 && bsde::direct_p_supported(P))
             return direct_config(all, g.members, g.f32, P, S);
     }
-    const SweepConfig cf = best_fused(all, g.members, g.f32, max_lds);
-    if (cf.lds) return cf;
+    bool fused = true;  // the same for every member of a plan's group
+    for (int b : g.members) fused = fused && takes_fused(all, b, max_lds);
+    if (fused) {
+        double t = 0.0;
+        const SweepConfig cf = best_fused(all, g.members, g.f32, max_lds, t);
+        if (cf.lds) return cf;
+    }
     // the direct kernel: split over blocks on a small grid, else two points per lane
     const SweepConfig c1 = direct_config(all, g.members, g.f32, 1);
     return c1.G > 1 ? c1 : direct_config(all, g.members, g.f32, 2);
@@ -2367,7 +2409,12 @@ bsde_status bsde_autotune(bsde_plan_t plan, void *ws, const bsde_io *io, void *s
             for (const Shape &q : kShapes64) consider(q);
         if (group_gathers(plan->inst, g.members)) cand.assign(1, gather_config(plan->inst, g.members, plan->max_lds));
         if (group_exact(plan->inst, g.members)) cand.assign(1, toeplitz_config(plan->inst, g.members, plan->max_lds));
-        if (cand.empty()) {
+        // both kernels where neither is much the faster by estimate (a large batch
+        // of small grids with wide windows is the direct kernel's)
+        double fused_us = 0.0;
+        if (!g.f32 && !cand.empty()) (void)best_fused(plan->inst, g.members, false, plan->max_lds, fused_us);
+        if (cand.empty() || (!g.f32 && cand[0].path == PATH_FUSED &&
+                             direct_cost(plan->inst, g.members) < 1.3 * fused_us)) {
             cand.push_back(direct_config(plan->inst, g.members, g.f32, 1));
             cand.push_back(direct_config(plan->inst, g.members, g.f32, 2));
         }

@@ -217,6 +217,53 @@ int check_shapes()
     return fails;
 }
 
+// Fused or direct, FP64: the faster of the two on a single solve, as measured
+// (cases that differ by more than 5%), whatever else a batch holds.
+int check_fused_or_direct()
+{
+    struct Row {
+        int nx, K, L;
+        double R;
+        int driver, fused;
+    };
+    constexpr int B = BSDE_DRIVER_BIDASK, E = BSDE_DRIVER_EXP;
+    const std::vector<Row> rows = {
+        {4000, 4, 16, 118, B, 1},    {16384, 4, 16, 105, B, 1},  {32768, 4, 16, 105, B, 1},
+        {49152, 4, 16, 105, B, 0},   {65536, 4, 16, 105, B, 0},  {131072, 4, 16, 105, B, 0},
+        {262144, 4, 16, 105, B, 0},  {262144, 4, 16, 90, B, 0},  {524288, 4, 16, 60, B, 0},
+        {65536, 4, 16, 90, B, 1},    {131072, 4, 16, 90, B, 1},  {262144, 4, 16, 30, B, 1},
+        {49152, 4, 32, 60, B, 1},    {65536, 4, 32, 70, B, 0},   {262144, 4, 32, 60, B, 0},
+        {131072, 2, 16, 180, B, 1},  {262144, 2, 16, 130, B, 0}, {262144, 2, 16, 180, B, 0},
+        {262144, 2, 8, 200, B, 0},   {262144, 1, 16, 200, B, 1}, {524288, 1, 4, 400, B, 0},
+        {49152, 6, 16, 60, B, 1},    {98304, 6, 16, 60, B, 0},   {262144, 6, 16, 60, B, 0},
+        {131072, 6, 64, 30, B, 1},   {262144, 6, 64, 30, B, 0},  {262144, 6, 64, 16, B, 1},
+        {1048576, 1, 4, 16, B, 1},   {1048576, 4, 16, 16, B, 1}, {1048576, 6, 16, 16, B, 1},
+        {262144, 1, 4, 3, B, 1},     {1025, 2, 16, 8, B, 1},     {16384, 4, 16, 100, E, 1},
+        {65536, 4, 16, 100, E, 0},   {262144, 4, 16, 60, E, 0},  {262144, 2, 16, 180, E, 0},
+        {262144, 4, 32, 16, E, 1},   {262144, 1, 8, 300, E, 1},  {524288, 6, 64, 30, B, 0},
+    };
+    std::vector<Instance> all(rows.size());
+    for (size_t k = 0; k < rows.size(); ++k) {
+        const Row &r = rows[k];
+        bsde_problem p = problem(r.nx, r.K, r.L, r.R, 0.3);
+        p.driver = r.driver;
+        p.p[3] = 0.2;
+        EXPECT(build_instance(p, all[k]), "n_x %d", r.nx);
+    }
+    for (size_t k = 0; k < rows.size(); ++k) {
+        const Row &r = rows[k];
+        Group one, many;
+        one.members = {(int)k};
+        many.members.assign(64, (int)k);
+        for (const Group &g : {one, many}) {
+            const SweepConfig c = default_config(all, g, kLds);
+            EXPECT((c.path == PATH_FUSED) == (r.fused != 0), "n_x %d K %d L %d ratio %g driver %d, %d instances: path %d",
+                   r.nx, r.K, r.L, r.R, r.driver, (int)g.members.size(), c.path);
+        }
+    }
+    return fails;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -226,6 +273,7 @@ int main(int argc, char **argv)
     if (what == "located_windows") return check_located_windows() != 0;
     if (what == "located_ghosts") return check_located_ghosts() != 0;
     if (what == "shapes") return check_shapes() != 0;
+    if (what == "fused_or_direct") return check_fused_or_direct() != 0;
     std::printf("unknown check\n");
     return 2;
 }

@@ -47,3 +47,7 @@ def test_located_windows_do_not_enlarge_the_ring(checks):
 
 def test_shapes_follow_the_measured_times(checks):
     checks("shapes")
+
+
+def test_fused_or_direct_is_the_faster(checks):
+    checks("fused_or_direct")
