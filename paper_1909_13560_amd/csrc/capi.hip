@@ -1139,22 +1139,81 @@ SweepConfig toeplitz_config(const std::vector<Instance> &all, const std::vector<
 
 constexpr size_t kLocatedLds = 131072;
 
-// State-dependent coefficients: in the fused sweep (W = 1) where every member
-// is double precision and a block's windows take at most 128 KB of LDS, else
-// from HBM/L2.  Measured (bid-ask, K = 4, L = 16, N = 128; fused against HBM/L2
-// per solve): 59 KB 0.83 ms, 100 KB 0.96 against 4.38 ms and 139 KB 1.13 against
-// 4.35 ms on 2001 points; on 60000 points 3.14 against 4.14 and 3.63 against
-// 4.21 ms.  The widest windows keep the kernel whose separate spline launches
+// Shapes of the fused sweep for located nodes and their measured times (as
+// kShapes64; the same bits).  Measured a step at K = 4, L = 16, ratio 16: 7.8 and
+// 15.3 us on 16384 points, 16.3 and 16.1 on 65536, 51 and 34 on 262144.
+constexpr Shape kLocatedShapes[] = {{1, 1, 8, 4.4, 0.034, 0.019, 1.45, 0.0185, 0.010, 2.5, 0.0, 0.0220},
+                                    {1, 4, 1, 5.6, 0.145, 0.030, 1.20, 0.0820, 0.012, 4.2, 0.070, 0.0150}};
+
+SweepConfig located_config(const std::vector<Instance> &all, const std::vector<int> &members, const Shape &q,
+                           size_t max_lds)
+{
+    SweepConfig c = fused_config(all, members, q.P, q.W, q.G, max_lds);
+    c.path = PATH_GATHER;
+    return c;
+}
+
+// The cheaper of them and its time (us), or lds = 0.
+SweepConfig best_located(const std::vector<Instance> &all, const std::vector<int> &members, size_t max_lds,
+                         double &cost)
+{
+    SweepConfig best{PATH_GATHER, 1, 1, 0};
+    cost = 0.0;
+    for (const Shape &q : kLocatedShapes) {
+        const SweepConfig c = located_config(all, members, q, max_lds);
+        if (!c.lds) continue;
+        const double t = fused_cost(all, members, c, q);
+        if (!best.lds || t < cost) {
+            best = c;
+            cost = t;
+        }
+    }
+    return best;
+}
+
+// Time of a step of a group with the kernel that reads HBM/L2, spline launch
+// included (us), as measured: the chain of a point's nodes, and n 64-point tiles
+// a CU once there are more than six.  K = 4, L = 16: 34 us on 65536 points, 62 on
+// 262144, 183 on 1048576.
+double gather_cost(const std::vector<Instance> &all, const std::vector<int> &members)
+{
+    double tiles = 0.0, node = 0.0;
+    for (int b : members) {
+        const double t = (all[b].nx + 63) / 64;
+        tiles += t;
+        node += t * all[b].K * all[b].pb.L;
+    }
+    const double n = std::ceil(tiles / 256.0), kl = node / tiles;
+    const double ex = all[members[0]].pb.driver == BSDE_DRIVER_EXP ? 0.0186 * kl : 0.0;
+    return 8.0 + 0.39 * kl + std::max(0.0, n - 6.0) * (0.23 + 0.037 * kl + ex);
+}
+
+// Whether an instance's located nodes go through LDS windows: where these take at
+// most 128 KB for 64 points and the fused sweep is the faster on this instance
+// alone (a rule on the instance, so that a batch gives the bits of its instances
+// alone).  Measured a step, fused against HBM/L2: K = 4, L = 16, ratio 60 (102 KB)
+// 18.7 and 34.3 us on 65536 points, 64.4 and 61.2 on 262144; K = 1, L = 8, ratio
+// 120 9.0 and 12.0, 17.4 and 15.5; ratio 16 faster throughout (34 and 62 us on
+// 262144 points).  Wider windows keep the kernel whose separate spline launches
 // show in the launch counts of bsde_profile_kernels.
+bool takes_windows(const std::vector<Instance> &all, int b, size_t max_lds)
+{
+    if (!all[b].located) return false;
+    const SweepConfig narrow = located_config(all, {b}, kLocatedShapes[0], max_lds);
+    if (!narrow.lds || narrow.lds > kLocatedLds) return false;
+    double t = 0.0;
+    (void)best_located(all, {b}, max_lds, t);
+    return t <= gather_cost(all, {b});
+}
+
+// State-dependent coefficients: in the fused sweep where every member is one for
+// it (the same for all members of a plan's group), else from HBM/L2.
 SweepConfig gather_config(const std::vector<Instance> &all, const std::vector<int> &members, size_t max_lds)
 {
-    bool ok = true;
-    for (int b : members) ok = ok && all[b].located;
-    if (ok) {
-        SweepConfig c = fused_config(all, members, 1, 1, 8, max_lds);
-        c.path = PATH_GATHER;
-        if (c.lds && c.lds <= kLocatedLds) return c;
-    }
+    bool windows = true;
+    for (int b : members) windows = windows && takes_windows(all, b, max_lds);
+    double t = 0.0;
+    if (windows) return best_located(all, members, max_lds, t);
     return SweepConfig{PATH_GATHER, 1, 1, 0};
 }
 
@@ -1186,10 +1245,12 @@ SweepConfig default_config(const std::vector<Instance> &all, const Group &g, siz
     return c1.G > 1 ? c1 : direct_config(all, g.members, g.f32, 2);
 }
 
+// State-dependent coefficients in the fused sweep's LDS windows.
+bool in_windows(const SweepConfig &c) { return c.path == PATH_GATHER && c.lds > 0; }
+
 int sweep_tiles(const Instance &in, const SweepConfig &c)
 {
-    const bool located = c.path == PATH_GATHER && c.W == 1;
-    const int T = c.path == PATH_FUSED || located ? 64 * c.P * c.W
+    const int T = c.path == PATH_FUSED || in_windows(c) ? 64 * c.P * c.W
                   : c.path == PATH_TOEPLITZ && c.W == 1 ? bsde::kExactTile
                                                          : kBlock * c.P;
     return (in.nx + T - 1) / T;
@@ -1204,8 +1265,8 @@ bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
     if (c.path == PATH_FUSED && c.lds > 65536)
         HIP_OK(bsde::set_fused_lds_limit(c.P, c.W, c.G, g.f32, g.driver, pl.max_lds));
     const bool exact_b = c.path == PATH_TOEPLITZ && c.W == 1;  // on B-spline coefficients
-    const bool located = c.path == PATH_GATHER && c.W == 1;    // in the fused sweep
-    if (located && c.lds > 65536) HIP_OK(bsde::set_located_lds_limit(g.driver, pl.max_lds));
+    const bool located = in_windows(c);
+    if (located && c.lds > 65536) HIP_OK(bsde::set_located_lds_limit(c.W, g.driver, pl.max_lds));
     if (exact_b && c.lds > 65536) HIP_OK(bsde::set_exact_lds_limit(c.G, pl.max_lds));
     if (c.path == PATH_TOEPLITZ && !exact_b && c.lds > 65536) HIP_OK(bsde::set_toeplitz_lds_limit());
     g.cfg = c;
@@ -1360,8 +1421,8 @@ bsde_status enqueue_step(const bsde_plan_s &pl, const Group &g, char *ws, int s,
         if (tm) HIP_OK(tm->mark(tm->sweep, st));
     } else {
         if (c.path == PATH_GATHER)
-            HIP_OK(c.W == 1 ? bsde::launch_sweep_located(g.driver, a, blocks, c.lds, st)
-                            : bsde::launch_sweep_gather(g.f32, g.driver, a, blocks, st));
+            HIP_OK(in_windows(c) ? bsde::launch_sweep_located(c.W, g.driver, a, blocks, c.lds, st)
+                                 : bsde::launch_sweep_gather(g.f32, g.driver, a, blocks, st));
         else if (c.path == PATH_TOEPLITZ)
             HIP_OK(c.W == 1 ? bsde::launch_sweep_exact(a, blocks, c.G, c.lds, st)
                             : bsde::launch_sweep_toeplitz(a, blocks, c.G, st));
@@ -1372,7 +1433,7 @@ bsde_status enqueue_step(const bsde_plan_s &pl, const Group &g, char *ws, int s,
         // and so do the Toeplitz sweep on coefficients and the split one's
         // finishing kernel)
         if (c.path == PATH_TOEPLITZ && (c.W == 1 || c.G > 1)) return BSDE_OK;
-        if (c.path == PATH_GATHER && c.W == 1) return BSDE_OK;
+        if (in_windows(c)) return BSDE_OK;
         if (tm) HIP_OK(tm->mark(tm->spline, st));
         HIP_OK(bsde::launch_spline(g.f32, step_args(pl, g, ws, s, false, true), 1,
                                    g.spline_prefix[act], st));
@@ -1991,7 +2052,8 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         one.members = {b};
         own[b] = default_config(pl->inst, one, pl->max_lds);
         if (own[b].path == PATH_FUSED) fits[b] = fitting_shapes(pl->inst, b, pl->max_lds);
-        if (own[b].path == PATH_TOEPLITZ || own[b].path == PATH_GATHER) fits[b] = own[b].W;
+        if (own[b].path == PATH_TOEPLITZ) fits[b] = own[b].W;
+        if (own[b].path == PATH_GATHER) fits[b] = in_windows(own[b]) ? 1 : 0;
         int gi = -1;
         for (size_t k = 0; k < pl->groups.size(); ++k) {
             const Group &g = pl->groups[k];
@@ -2407,7 +2469,19 @@ bsde_status bsde_autotune(bsde_plan_t plan, void *ws, const bsde_io *io, void *s
             for (const Shape &q : kShapes32) consider(q);
         else
             for (const Shape &q : kShapes64) consider(q);
-        if (group_gathers(plan->inst, g.members)) cand.assign(1, gather_config(plan->inst, g.members, plan->max_lds));
+        if (group_gathers(plan->inst, g.members)) {
+            cand.clear();
+            double t = 0.0;
+            if (in_windows(gather_config(plan->inst, g.members, plan->max_lds))) {
+                for (const Shape &q : kLocatedShapes) {
+                    const SweepConfig c = located_config(plan->inst, g.members, q, plan->max_lds);
+                    if (c.lds) cand.push_back(c);
+                }
+                (void)best_located(plan->inst, g.members, plan->max_lds, t);
+            }
+            if (cand.empty() || gather_cost(plan->inst, g.members) < 1.3 * t)
+                cand.push_back(SweepConfig{PATH_GATHER, 1, 1, 0});
+        }
         if (group_exact(plan->inst, g.members)) cand.assign(1, toeplitz_config(plan->inst, g.members, plan->max_lds));
         // both kernels where neither is much the faster by estimate (a large batch
         // of small grids with wide windows is the direct kernel's)

@@ -787,6 +787,20 @@ __global__ void __launch_bounds__(64 * WP * G) sweep_fused(const StepArgs s)
             }
         } else {
             const NodeRecB *recb = const_load(&dn->hot.recb);
+            // the nodes of one list into y, z
+            auto list_nodes = [&](const NodeRecB *recs, int n, const int2 &at, double (&y)[P], double (&z)[P]) {
+                if constexpr (GATHER) {
+                    const double pos = min(first, nx - 1);
+                    gather_nodes<DRV, false>(smem, edge, recs, n, at, a, drv, pos, cax, cbx, t0, nx, y[0], z[0]);
+                    if (__any(!isfinite(y[0] + z[0]))) {
+                        y[0] = z[0] = 0.0;
+                        gather_nodes<DRV, true>(smem, edge, recs, n, at, a, drv, pos, cax, cbx, t0, nx, y[0],
+                                                z[0]);
+                    }
+                } else {
+                    class_nodes<P, DRV>(lane_rec, edge, recs, n, at, a, drv, first, wfirst, wlast, nx, y, z);
+                }
+            };
             if constexpr (G < 4) {
                 // four or eight classes one after the other: a class and its
                 // partner are added as soon as both are there, in the order of
@@ -809,8 +823,7 @@ __global__ void __launch_bounds__(64 * WP * G) sweep_fused(const StepArgs s)
                     }
 #pragma unroll
                     for (int q = 0; q < P; ++q) Y[0][q] = Z[0][q] = 0.0;
-                    class_nodes<P, DRV>(lane_rec, edge, recs, n, ac, a, drv, first, wfirst, wlast, nx, Y[0],
-                                        Z[0]);
+                    list_nodes(recs, n, ac, Y[0], Z[0]);
                     auto meet = [&](int d) {
 #pragma unroll
                         for (int q = 0; q < P; ++q) {
@@ -842,21 +855,9 @@ __global__ void __launch_bounds__(64 * WP * G) sweep_fused(const StepArgs s)
                         }
                     }
                 }
-            }
+            } else {
 #pragma unroll
-            for (int k = 0; k < (G < 4 ? 0 : C); ++k) {
-                if constexpr (GATHER) {
-                    const double pos = min(first, nx - 1);
-                    gather_nodes<DRV, false>(smem, edge, recb + list0[k], lcnt[k], av[k], a, drv, pos, cax,
-                                             cbx, t0, nx, Y[k][0], Z[k][0]);
-                    if (__any(!isfinite(Y[k][0] + Z[k][0]))) {
-                        Y[k][0] = Z[k][0] = 0.0;
-                        gather_nodes<DRV, true>(smem, edge, recb + list0[k], lcnt[k], av[k], a, drv, pos, cax,
-                                                cbx, t0, nx, Y[k][0], Z[k][0]);
-                    }
-                } else
-                    class_nodes<P, DRV>(lane_rec, edge, recb + list0[k], lcnt[k], av[k], a, drv, first,
-                                        wfirst, wlast, nx, Y[k], Z[k]);
+                for (int k = 0; k < C; ++k) list_nodes(recb + list0[k], lcnt[k], av[k], Y[k], Z[k]);
             }
         }
     }

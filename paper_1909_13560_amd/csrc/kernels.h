@@ -35,10 +35,10 @@ bool direct_p_supported(int P);
 hipError_t launch_sweep_fused(int P, int WP, int G, bool f32, int driver, const StepArgs &a, int blocks,
                               size_t lds, hipStream_t s);
 hipError_t set_fused_lds_limit(int P, int WP, int G, bool f32, int driver, size_t lds);
-// state-dependent coefficients in the fused sweep (FP64): 64-point tiles, eight
-// node groups, nodes located per point
-hipError_t launch_sweep_located(int driver, const StepArgs &a, int blocks, size_t lds, hipStream_t s);
-hipError_t set_located_lds_limit(int driver, size_t lds);
+// state-dependent coefficients in the fused sweep (FP64), nodes located per
+// point: WP = 1, 64-point tiles with eight node groups; 4, 256-point tiles with one
+hipError_t launch_sweep_located(int WP, int driver, const StepArgs &a, int blocks, size_t lds, hipStream_t s);
+hipError_t set_located_lds_limit(int WP, int driver, size_t lds);
 hipError_t launch_sweep_direct(int P, bool f32, int driver, const StepArgs &a, int blocks,
                                size_t lds, hipStream_t s);
 // state-dependent forward coefficients: one point per lane, nodes located per point

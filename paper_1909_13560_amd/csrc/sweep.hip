@@ -575,32 +575,42 @@ hipError_t launch_sweep_fused(int P, int WP, int G, bool F32, int driver, const 
 }
 
 namespace {
-template <int DRV>
+template <int WP, int G, int DRV>
 hipError_t located_t(const StepArgs *a, int blocks, size_t lds, hipStream_t s)
 {
     if (!a)
-        return hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep_fused<1, 1, 8, DRV, false, true>),
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep_fused<1, WP, G, DRV, false, true>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL((sweep_fused<1, 1, 8, DRV, false, true>), dim3(blocks), dim3(512), lds, s, *a);
+    hipLaunchKernelGGL((sweep_fused<1, WP, G, DRV, false, true>), dim3(blocks), dim3(64 * WP * G), lds, s, *a);
     return hipGetLastError();
 }
-hipError_t located(int driver, const StepArgs *a, int blocks, size_t lds, hipStream_t s)
+template <int WP, int G>
+hipError_t located_by_driver(int driver, const StepArgs *a, int blocks, size_t lds, hipStream_t s)
 {
     switch (driver) {
-    case BSDE_DRIVER_LINEAR: return located_t<BSDE_DRIVER_LINEAR>(a, blocks, lds, s);
-    case BSDE_DRIVER_BIDASK: return located_t<BSDE_DRIVER_BIDASK>(a, blocks, lds, s);
-    case BSDE_DRIVER_CUBIC: return located_t<BSDE_DRIVER_CUBIC>(a, blocks, lds, s);
-    default: return located_t<BSDE_DRIVER_EXP>(a, blocks, lds, s);
+    case BSDE_DRIVER_LINEAR: return located_t<WP, G, BSDE_DRIVER_LINEAR>(a, blocks, lds, s);
+    case BSDE_DRIVER_BIDASK: return located_t<WP, G, BSDE_DRIVER_BIDASK>(a, blocks, lds, s);
+    case BSDE_DRIVER_CUBIC: return located_t<WP, G, BSDE_DRIVER_CUBIC>(a, blocks, lds, s);
+    default: return located_t<WP, G, BSDE_DRIVER_EXP>(a, blocks, lds, s);
     }
+}
+// 64-point tiles with eight node groups, or 256-point tiles with one
+hipError_t located(int WP, int driver, const StepArgs *a, int blocks, size_t lds, hipStream_t s)
+{
+    return WP == 1 ? located_by_driver<1, 8>(driver, a, blocks, lds, s)
+                   : located_by_driver<4, 1>(driver, a, blocks, lds, s);
 }
 }  // namespace
 
-hipError_t launch_sweep_located(int driver, const StepArgs &a, int blocks, size_t lds, hipStream_t s)
+hipError_t launch_sweep_located(int WP, int driver, const StepArgs &a, int blocks, size_t lds, hipStream_t s)
 {
-    return located(driver, &a, blocks, lds, s);
+    return located(WP, driver, &a, blocks, lds, s);
 }
 
-hipError_t set_located_lds_limit(int driver, size_t lds) { return located(driver, nullptr, 0, lds, nullptr); }
+hipError_t set_located_lds_limit(int WP, int driver, size_t lds)
+{
+    return located(WP, driver, nullptr, 0, lds, nullptr);
+}
 
 hipError_t set_fused_lds_limit(int P, int WP, int G, bool F32, int driver, size_t lds)
 {

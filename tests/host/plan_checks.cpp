@@ -264,6 +264,49 @@ int check_fused_or_direct()
     return fails;
 }
 
+// Located nodes, FP64: windows or HBM/L2, and the tile, against the measured
+// times of a step (us: HBM/L2, 64-point tiles, 256-point tiles): within 8% of the
+// fastest on a single solve.
+int check_located_shapes()
+{
+    struct Row {
+        int nx, K, L;
+        double R, us[3];
+    };
+    const std::vector<Row> rows = {
+        {500, 1, 4, 6, {10.0, 4.9, 6.8}},         {2001, 4, 16, 16, {35.5, 7.5, 15.3}},
+        {16384, 6, 64, 8, {147.5, 19.4, 70.6}},   {16384, 4, 16, 60, {34.3, 9.0, 18.3}},
+        {65536, 1, 4, 6, {9.8, 9.3, 7.1}},        {65536, 2, 16, 16, {21.7, 12.5, 10.8}},
+        {65536, 4, 16, 60, {34.3, 27.1, 18.7}},   {131072, 1, 4, 6, {10.5, 16.1, 8.4}},
+        {131072, 4, 16, 16, {42.7, 27.9, 20.8}},  {262144, 1, 4, 6, {12.5, 28.5, 11.5}},
+        {262144, 2, 8, 6, {21.6, 34.3, 15.7}},    {262144, 4, 16, 16, {62.3, 51.3, 34.2}},
+        {262144, 4, 16, 60, {61.2, 98.6, 64.4}},  {262144, 2, 16, 100, {33.1, 89.2, 46.4}},
+        {262144, 6, 64, 8, {290.8, 150.2, 162.8}}, {1048576, 1, 16, 6, {60.6, 117.6, 44.2}},
+        {1048576, 3, 16, 9, {141.1, 163.6, 83.8}}, {1048576, 4, 16, 60, {181.0, 388.7, 253.9}},
+        {1048576, 1, 8, 120, {41.0, 143.6, 49.6}},
+    };
+    std::vector<Instance> all(rows.size());
+    for (size_t k = 0; k < rows.size(); ++k) {
+        const Row &r = rows[k];
+        bsde_problem p = problem(r.nx, r.K, r.L, r.R, 0.3);
+        p.driver = BSDE_DRIVER_BIDASK;
+        p.p[3] = 0.2;
+        p.vol_x = 0.1 * p.vol[0][0] / r.nx;  // b grows by a tenth over the grid, to ratio R
+        p.vol[0][0] *= 0.9;
+        EXPECT(build_instance(p, all[k]), "n_x %d", r.nx);
+    }
+    for (size_t k = 0; k < rows.size(); ++k) {
+        const Row &r = rows[k];
+        const SweepConfig c = gather_config(all, {(int)k}, kLds);
+        const double t = r.us[!in_windows(c) ? 0 : c.W == 1 ? 1 : 2];
+        EXPECT(c.path == PATH_GATHER && t <= 1.08 * *std::min_element(r.us, r.us + 3),
+               "n_x %d K %d L %d ratio %g: LDS %d, W %d", r.nx, r.K, r.L, r.R, (int)c.lds, c.W);
+        // the kernel (not the tile) is the instance's own in any batch
+        EXPECT(in_windows(c) == in_windows(gather_config(all, std::vector<int>(100, (int)k), kLds)), "n_x %d", r.nx);
+    }
+    return fails;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -274,6 +317,7 @@ int main(int argc, char **argv)
     if (what == "located_ghosts") return check_located_ghosts() != 0;
     if (what == "shapes") return check_shapes() != 0;
     if (what == "fused_or_direct") return check_fused_or_direct() != 0;
+    if (what == "located_shapes") return check_located_shapes() != 0;
     std::printf("unknown check\n");
     return 2;
 }

@@ -51,3 +51,7 @@ def test_shapes_follow_the_measured_times(checks):
 
 def test_fused_or_direct_is_the_faster(checks):
     checks("fused_or_direct")
+
+
+def test_located_shapes_follow_the_measured_times(checks):
+    checks("located_shapes")
