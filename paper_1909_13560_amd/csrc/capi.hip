@@ -1114,27 +1114,69 @@ ExactLds exact_layout(const Instance &in, int G)
     return l;
 }
 
-// Exact expectations: on B-spline coefficients where the windows and bands of
-// every member fit in LDS (W = 1; stability ratios up to about 40 at K = 4),
-// with a second group of four wavefronts where a tile has more than one chunk
-// of 256 taps; else the chunked sweep on values and second derivatives.
+// Dynamic LDS of the exact-expectation sweep on B-spline coefficients, 0 where an
+// instance's windows and bands do not fit (stability ratios from about 40 at K = 4).
+size_t exact_lds(const Instance &in, int G, size_t max_lds)
+{
+    for (int j = 1; j <= in.K; ++j)
+        if ((long)in.band[j].ec.size() > (long)(max_lds / 16)) return 0;
+    const size_t need = exact_layout(in, G).total;
+    return need <= max_lds ? need : 0;
+}
+
+// Exact expectations: the cheapest of the sweep on B-spline coefficients with one
+// or two groups of four wavefronts (W = 1, where every member fits LDS) and the
+// chunked sweep on values and second derivatives, by their measured times (us a
+// step; n 64-point tiles a CU): a block of the former takes `lat` alone on a CU
+// and hides most of it behind the others that the LDS leaves room for; the
+// chunked sweep pays per tap.  Measured, one group / two / chunked: K = 4, ratio
+// 16: 19.9, 13.0, 25.0 on 16384 points, 156, 107, 126 on 262144; ratio 4: 11.5,
+// 9.9, 16.0 and 48, 69, 52; 1048576 points: 177, 267, 167; K = 2, ratio 45 (one
+// block a CU), 262144 points: 164, 159, 131.  The choice follows the group's
+// tiles, so a batch may sum in another order than its instances alone.
 SweepConfig toeplitz_config(const std::vector<Instance> &all, const std::vector<int> &members, size_t max_lds)
 {
-    int G = 1;
-    size_t lds = 0;
+    double tiles = 0.0, layers = 0.0, taps = 0.0;  // the latter two: tile by tile
+    int chunks = 1;
     for (int b : members) {
         const Instance &in = all[b];
+        const double t = (in.nx + bsde::kExactTile - 1) / bsde::kExactTile;
+        tiles += t;
+        layers += t * in.K;
         int c = 0;
         for (int j = 1; j <= in.K; ++j) {
-            if ((long)in.band[j].ec.size() > (long)(max_lds / 16)) c = 1 << 20;
+            taps += t * (double)in.band[j].ev.size();
             c += bsde::toeplitz_chunks((int)in.band[j].ev.size());
         }
-        if (c > 1) G = 2;
-        lds = c >= (1 << 20) ? max_lds + 1 : std::max(lds, exact_layout(in, 2).total);
-        if (lds > max_lds) break;
+        chunks = std::max(chunks, c);
     }
-    if (lds <= max_lds) return SweepConfig{PATH_TOEPLITZ, 1, G, lds, 1};
-    return SweepConfig{PATH_TOEPLITZ, 1, toeplitz_splits(all, members), bsde::toeplitz_lds_bytes()};
+    const double n = std::ceil(tiles / 256.0), K = layers / tiles;
+    taps /= tiles;
+    SweepConfig best{PATH_TOEPLITZ, 1, toeplitz_splits(all, members), bsde::toeplitz_lds_bytes()};
+    // (split over blocks, on fewer than 1024 tiles, it needs partial sums in the
+    // workspace and is at most 6% the faster)
+    double cost = best.G > 1 ? 1e300 : 7.0 + K + 0.0075 * taps + n * (0.3 + 0.15 * K + 0.0046 * taps);
+    for (int G = 1; G <= (chunks > 1 ? 2 : 1); ++G) {  // (two share more than one chunk of taps)
+        size_t lds = 0;
+        bool fits = true;
+        for (int b : members) {
+            const size_t need = exact_lds(all[b], G, max_lds);
+            fits = fits && need > 0;
+            lds = std::max(lds, need);
+        }
+        if (!fits) continue;
+        const double kb = lds / 1024.0;
+        const int res = (int)std::min((size_t)163840 / lds, (size_t)8 / G);
+        const double lat = G == 1 ? 2.4 + 0.70 * K + 0.235 * kb : 3.6 + 0.87 * K + 0.09 * kb;
+        constexpr double kShared2[5] = {0.0, -0.3, 1.3, 2.3, 2.0};
+        const double shared = G == 2 ? kShared2[std::min(res, 4)] : res > 1 ? 0.6 + 0.07 * K : 0.0;
+        const double t = lat + (n - 1.0) * ((lat - 2.5) / res + shared);
+        if (t < cost) {
+            cost = t;
+            best = SweepConfig{PATH_TOEPLITZ, 1, G, lds, 1};
+        }
+    }
+    return best;
 }
 
 constexpr size_t kLocatedLds = 131072;
@@ -2052,7 +2094,7 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         one.members = {b};
         own[b] = default_config(pl->inst, one, pl->max_lds);
         if (own[b].path == PATH_FUSED) fits[b] = fitting_shapes(pl->inst, b, pl->max_lds);
-        if (own[b].path == PATH_TOEPLITZ) fits[b] = own[b].W;
+        if (own[b].path == PATH_TOEPLITZ) fits[b] = exact_lds(in, 2, pl->max_lds) ? 1 : 0;
         if (own[b].path == PATH_GATHER) fits[b] = in_windows(own[b]) ? 1 : 0;
         int gi = -1;
         for (size_t k = 0; k < pl->groups.size(); ++k) {

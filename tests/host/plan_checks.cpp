@@ -307,6 +307,61 @@ int check_located_shapes()
     return fails;
 }
 
+// Exact expectations: the kernel against the measured times of a step (us: the
+// chunked sweep, one and two groups on B-spline coefficients), within 12% of the
+// fastest, on a single solve and on a batch of the same number of tiles.
+int check_exact_shapes()
+{
+    struct Row {
+        int nx, K;
+        double R, us[3];
+    };
+    const std::vector<Row> rows = {
+        {16384, 1, 2, {11.8, 5.9, 6.0}}, {16384, 1, 16, {16.4, 8.1, 6.8}},
+        {16384, 2, 8, {16.1, 8.8, 7.7}}, {16384, 2, 16, {18.7, 11.6, 8.7}},
+        {16384, 2, 45, {24.6, 20.1, 12.5}}, {16384, 3, 8, {17.3, 11.3, 9.2}},
+        {16384, 4, 2, {14.3, 10.3, 9.4}}, {16384, 4, 8, {18.6, 13.9, 10.7}},
+        {16384, 4, 16, {25.0, 19.9, 13.0}}, {16384, 4, 25, {31.8, 25.9, 15.6}},
+        {16384, 6, 2, {18.1, 13.4, 11.9}}, {16384, 6, 8, {24.8, 20.2, 14.2}},
+        {16384, 6, 16, {33.3, 29.9, 18.2}}, {16384, 6, 25, {41.7, 40.7, 22.4}},
+        {131072, 1, 2, {13.6, 12.3, 20.5}}, {131072, 1, 16, {21.4, 18.8, 24.6}},
+        {131072, 2, 8, {28.4, 20.5, 28.3}}, {131072, 2, 16, {38.5, 29.2, 33.9}},
+        {131072, 2, 45, {76.3, 83.4, 80.7}}, {131072, 3, 8, {41.1, 27.6, 35.0}},
+        {131072, 4, 2, {27.4, 22.4, 33.7}}, {131072, 4, 8, {47.3, 35.7, 42.1}},
+        {131072, 4, 16, {77.2, 79.6, 55.5}}, {131072, 4, 25, {104.3, 187.0, 102.4}},
+        {131072, 6, 2, {35.4, 30.0, 42.8}}, {131072, 6, 8, {69.4, 78.6, 58.4}},
+        {131072, 6, 16, {121.3, 215.5, 120.1}}, {131072, 6, 25, {167.2, 302.6, 153.2}},
+        {262144, 1, 2, {18.5, 21.6, 38.1}}, {262144, 1, 16, {32.6, 33.4, 46.1}},
+        {262144, 2, 8, {39.8, 37.3, 54.1}}, {262144, 2, 16, {59.4, 53.8, 64.7}},
+        {262144, 2, 45, {131.4, 164.0, 159.3}}, {262144, 3, 8, {55.5, 50.2, 66.8}},
+        {262144, 4, 2, {39.8, 40.8, 63.9}}, {262144, 4, 8, {76.0, 65.9, 80.8}},
+        {262144, 4, 16, {126.0, 155.7, 106.9}}, {262144, 4, 25, {184.0, 371.2, 201.7}},
+        {262144, 6, 2, {54.9, 55.8, 81.9}}, {262144, 6, 8, {119.0, 153.2, 112.3}},
+        {262144, 6, 16, {208.8, 428.1, 236.5}}, {262144, 6, 25, {309.6, 604.3, 302.6}},
+        {1048576, 1, 2, {50.8, 74.4, 143.1}}, {1048576, 1, 16, {99.9, 118.9, 174.5}},
+        {1048576, 2, 8, {121.8, 133.0, 208.9}}, {1048576, 2, 16, {195.8, 196.1, 249.3}},
+        {1048576, 2, 45, {470.3, 640.3, 632.6}}, {1048576, 3, 8, {183.5, 185.3, 258.2}},
+        {1048576, 4, 2, {121.7, 147.5, 246.1}}, {1048576, 4, 8, {255.6, 242.6, 313.2}},
+        {1048576, 4, 16, {448.3, 610.7, 415.3}}, {1048576, 4, 25, {664.5, 1489.5, 797.1}},
+        {1048576, 6, 2, {177.5, 201.7, 313.1}}, {1048576, 6, 8, {412.1, 599.3, 434.7}},
+        {1048576, 6, 16, {753.6, 1717.5, 937.7}}, {1048576, 6, 25, {1126.0, 2422.1, 1199.6}}
+    };
+    for (const Row &r : rows)
+        for (int parts : {1, 16}) {
+            bsde_problem p = problem(r.nx / parts, r.K, 16, r.R, 0.3);
+            p.quad = BSDE_QUAD_EXACT;
+            std::vector<Instance> all(1);
+            EXPECT(build_instance(p, all[0]), "n_x %d", r.nx);
+            const SweepConfig c = toeplitz_config(all, std::vector<int>(parts, 0), kLds);
+            const double t = r.us[c.W == 1 ? c.G : 0];
+            // (one chunk of taps has nothing for a second group)
+            const int last = r.K == 1 ? 2 : 3;
+            EXPECT(t <= 1.12 * *std::min_element(r.us, r.us + last), "n_x %d in %d K %d ratio %g: G %d W %d, %g us", r.nx,
+                   parts, r.K, r.R, c.G, c.W, t);
+        }
+    return fails;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -318,6 +373,7 @@ int main(int argc, char **argv)
     if (what == "shapes") return check_shapes() != 0;
     if (what == "fused_or_direct") return check_fused_or_direct() != 0;
     if (what == "located_shapes") return check_located_shapes() != 0;
+    if (what == "exact_shapes") return check_exact_shapes() != 0;
     std::printf("unknown check\n");
     return 2;
 }

@@ -55,3 +55,7 @@ def test_fused_or_direct_is_the_faster(checks):
 
 def test_located_shapes_follow_the_measured_times(checks):
     checks("located_shapes")
+
+
+def test_exact_kernels_follow_the_measured_times(checks):
+    checks("exact_shapes")
