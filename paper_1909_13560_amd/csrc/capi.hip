@@ -75,7 +75,7 @@ struct Instance {
     const double *d_ex_band = nullptr;
     const double2 *d_ex_corr = nullptr;
     const bsde::NodeRecB *d_recb = nullptr;
-    int2 *d_addr = nullptr;  // fused sweep: node addresses of the bound shape
+    int2 *d_addr = nullptr;  // FP64 fused sweep: node addresses of the bound shape (in its group's)
     int steps;  // layers computed: N - K - n_stop + 1
     bsde::DriverParams drv;
     std::vector<int> m, win_lo, win_hi;
@@ -96,6 +96,7 @@ struct Group {
     std::vector<int> members;
     std::vector<int> tile_prefix, spline_prefix;  // members + 1 entries
     int *d_tile_inst = nullptr;    // grid tile -> instance (sized for kMinTile)
+    int2 *d_addr = nullptr;        // FP64: the members' node addresses, one after the other
     int *d_spline_inst = nullptr;  // spline tile -> instance
     int max_steps = 0;
     size_t part_off = 0;  // partial sums in the workspace: Toeplitz splits or direct chunks
@@ -623,8 +624,10 @@ bsde_status build_instance2(const bsde_problem &p, Instance2 &in)
     if (!bsde::spline_gamma(1, p.k_y, gy) || !bsde::spline_gamma(2, p.k_z, gz)) return BSDE_EINVAL;
     const double inv_sqrt_pi = 0.56418958354775628695;
     const int K = in.K, L = p.L;
+    // the B-spline form has node tables of its own (build_instance2b)
+    in.bspline = !in.f32 && p.interp != BSDE_INTERP_BICUBIC_FD;
     in.rows.assign((size_t)K * L, bsde::Node2Row{});
-    in.nodes.assign((size_t)K * L * L, bsde::Node2{});
+    in.nodes.assign(in.bspline ? 0 : (size_t)K * L * L, bsde::Node2{});
     in.m1.assign((size_t)K * L * L, 0);
     int m0min = 0, m0max = 0, m1min = 0, m1max = 0;
     in.win = 0;
@@ -662,9 +665,13 @@ bsde_status build_instance2(const bsde_problem &p, Instance2 &in)
                     (p.drift[1] * j * in.dt + p.vol[1][0] * dW0 + p.vol[1][1] * dW1) / in.dx1;
                 const double f1 = std::floor(s1);
                 if (!(std::fabs(f1) < 1e8)) return BSDE_EINVAL;
+                const size_t k = ((size_t)(j - 1) * L + l0) * L + l1;
+                in.m1[k] = (int)f1;
+                lo = std::min(lo, (int)f1);
+                hi = std::max(hi, (int)f1);
+                if (in.bspline) continue;
                 const double ph1 = s1 - f1, u1 = 1.0 - ph1;
                 const double wgt = w[l0] * inv_sqrt_pi * w[l1] * inv_sqrt_pi;
-                const size_t k = ((size_t)(j - 1) * L + l0) * L + l1;
                 bsde::Node2 &nd = in.nodes[k];
                 if (bicubic) {
                     nd.B1 = ph1 * ph1 * (3.0 - 2.0 * ph1);
@@ -683,9 +690,6 @@ bsde_status build_instance2(const bsde_problem &p, Instance2 &in)
                 nd.cy = (j == p.k_y) ? wgt : 0.0;
                 nd.cyz1 = (j == 1 && ydw) ? wgt * dW0 / (in.dt * gz[0]) : 0.0;
                 nd.cyz2 = (j == 1 && ydw) ? wgt * dW1 / (in.dt * gz[0]) : 0.0;
-                in.m1[k] = (int)f1;
-                lo = std::min(lo, (int)f1);
-                hi = std::max(hi, (int)f1);
             }
             row.m1lo = lo;
             row.m1hi = hi;
@@ -698,7 +702,6 @@ bsde_status build_instance2(const bsde_problem &p, Instance2 &in)
         }
     }
     in.h0 = p.k_y * in.dt * gy[0];
-    in.bspline = !in.f32 && !bicubic;
     if (in.bspline) {
         // one plane element per grid point; the widest node spread and the
         // columns next to the ends of axis 1 that a node's correction reaches
@@ -1315,6 +1318,7 @@ bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
     g.tile_prefix.assign(g.members.size() + 1, 0);
     g.spline_prefix.assign(g.members.size() + 1, 0);
     std::vector<int> tmap, smap;
+    std::vector<int2> addr;  // of all members: one copy
     for (size_t k = 0; k < g.members.size(); ++k) {
         const int b = g.members[k];
         const Instance &in = pl.inst[b];
@@ -1362,8 +1366,10 @@ bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
         }
         if (c.path == PATH_FUSED || located) {
             const FusedLds l = fused_layout(in, c.P, c.W, c.G);
-            const std::vector<int2> addr = fused_addresses(in, l, c.P);
-            HIP_OK(hipMemcpy(in.d_addr, addr.data(), addr.size() * sizeof(int2), hipMemcpyHostToDevice));
+            if (!in.f32) {  // (the FP32 form has the offsets)
+                const std::vector<int2> own = fused_addresses(in, l, c.P);
+                addr.insert(addr.end(), own.begin(), own.end());
+            }
             bsde::FusedHot &h = d.hot;
             h.ring_off = d.ring_off;
             h.addr = in.d_addr;
@@ -1398,9 +1404,15 @@ bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
         tmap.insert(tmap.end(), d.a.ntiles, b);
         smap.insert(smap.end(), d.spline_tiles, b);
     }
-    HIP_OK(hipMemcpy(g.d_tile_inst, tmap.data(), tmap.size() * sizeof(int), hipMemcpyHostToDevice));
-    HIP_OK(hipMemcpy(g.d_spline_inst, smap.data(), smap.size() * sizeof(int),
-                     hipMemcpyHostToDevice));
+    // the maps and the addresses lie side by side: one copy
+    char *const base = reinterpret_cast<char *>(g.d_tile_inst);
+    const size_t smap_at = reinterpret_cast<char *>(g.d_spline_inst) - base;
+    const size_t addr_at = addr.empty() ? 0 : reinterpret_cast<char *>(g.d_addr) - base;
+    std::vector<char> maps(std::max(smap_at + smap.size() * sizeof(int), addr_at + addr.size() * sizeof(int2)));
+    std::memcpy(maps.data(), tmap.data(), tmap.size() * sizeof(int));
+    std::memcpy(maps.data() + smap_at, smap.data(), smap.size() * sizeof(int));
+    if (!addr.empty()) std::memcpy(maps.data() + addr_at, addr.data(), addr.size() * sizeof(int2));
+    HIP_OK(hipMemcpy(base, maps.data(), maps.size(), hipMemcpyHostToDevice));
     HIP_OK(hipMemcpy(pl.d_desc, pl.desc.data(), pl.desc.size() * sizeof(bsde::InstDesc),
                      hipMemcpyHostToDevice));
     pl.drop_graphs();
@@ -1808,7 +1820,7 @@ bsde_status plan_2d(const bsde_problem *pb, int batch, bsde_plan_t *out)
     for (int b = 0; b < batch; ++b) {
         const Instance2 &in = pl->inst2[b];
         toff[b] = tbytes;
-        tbytes += align_up(in.rows.size() * sizeof(bsde::Node2Row), 256) +
+        tbytes += (in.bspline ? 0 : align_up(in.rows.size() * sizeof(bsde::Node2Row), 256)) +
                   align_up(in.nodes.size() * sizeof(bsde::Node2), 256) +
                   align_up(in.m1.size() * sizeof(int), 256) +
                   align_up(in.rowsb.size() * sizeof(bsde::Row2B), 256) +
@@ -1833,10 +1845,12 @@ bsde_status plan_2d(const bsde_problem *pb, int batch, bsde_plan_t *out)
             o += align_up(bytes, 256);
             return d;
         };
-        in.d_rows = static_cast<const bsde::Node2Row *>(
-            put(in.rows.data(), in.rows.size() * sizeof(bsde::Node2Row)));
-        in.d_nodes =
-            static_cast<const bsde::Node2 *>(put(in.nodes.data(), in.nodes.size() * sizeof(bsde::Node2)));
+        if (!in.bspline) {
+            in.d_rows = static_cast<const bsde::Node2Row *>(
+                put(in.rows.data(), in.rows.size() * sizeof(bsde::Node2Row)));
+            in.d_nodes =
+                static_cast<const bsde::Node2 *>(put(in.nodes.data(), in.nodes.size() * sizeof(bsde::Node2)));
+        }
         in.d_m1 = static_cast<const int *>(put(in.m1.data(), in.m1.size() * sizeof(int)));
         if (in.bspline) {
             in.d_rowsb = static_cast<const bsde::Row2B *>(
@@ -2133,7 +2147,6 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
                   align_up(kl * sizeof(bsde::NodeRec32), 256) + align_up(kl * sizeof(double), 256) +
                   align_up(kl * sizeof(bsde::NodeRecB), 256);
         size_t nbw = 0;
-        tbytes += align_up(kl * sizeof(int2), 256);
         for (int j = 1; j <= in.K; ++j) nbw += 4 * in.band[j].ev.size();
         tbytes += align_up(nbw * sizeof(double), 256) + align_up(in.ex_band.size() * sizeof(double), 256) +
                   align_up(in.ex_corr.size() * sizeof(double2), 256);
@@ -2141,22 +2154,25 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
     }
     const size_t desc_off = tbytes;
     tbytes += align_up((size_t)batch * sizeof(bsde::InstDesc), 256);
-    std::vector<size_t> map_off(pl->groups.size());
+    std::vector<size_t> map_off(pl->groups.size()), addr_off(pl->groups.size());
     for (size_t k = 0; k < pl->groups.size(); ++k) {
-        size_t tiles = 0, stiles = 0;
+        size_t tiles = 0, stiles = 0, nodes = 0;
         for (int b : pl->groups[k].members) {
             tiles += tiles_of(pl->inst[b], kMinTile);
             stiles += spline_tiles(pl->inst[b]);
+            nodes += (size_t)pl->inst[b].K * pl->inst[b].pb.L;
         }
         map_off[k] = tbytes;
         tbytes += align_up(tiles * sizeof(int), 256) + align_up(stiles * sizeof(int), 256);
+        addr_off[k] = tbytes;
+        if (!pl->groups[k].f32) tbytes += align_up(nodes * sizeof(int2), 256);
     }
     if (hipMalloc(&pl->d_tables, std::max<size_t>(tbytes, 256)) != hipSuccess) {
         delete pl;
         return BSDE_ENOMEM;
     }
     char *dev = static_cast<char *>(pl->d_tables);
-    std::vector<char> host(tbytes);
+    std::vector<char> host(desc_off);
     for (int b = 0; b < batch; ++b) {
         Instance &in = pl->inst[b];
         const size_t kl = (size_t)in.K * in.pb.L;
@@ -2209,7 +2225,6 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         in.d_recb =
             static_cast<const bsde::NodeRecB *>(put(recsb.data(), kl * sizeof(bsde::NodeRecB)));
         in.dtab.m = static_cast<const int *>(put(in.m.data(), kl * sizeof(int)));
-        in.d_addr = static_cast<int2 *>(put(std::vector<int2>(kl).data(), kl * sizeof(int2)));
         in.dtab.dw = static_cast<const double *>(put(in.dw.data(), kl * sizeof(double)));
         std::vector<double> bw;
         for (int j = 1; j <= in.K; ++j) {
@@ -2237,6 +2252,13 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         for (int b : g.members) tiles += tiles_of(pl->inst[b], kMinTile);
         g.d_tile_inst = reinterpret_cast<int *>(dev + map_off[k]);
         g.d_spline_inst = reinterpret_cast<int *>(dev + map_off[k] + align_up(tiles * sizeof(int), 256));
+        if (g.f32) continue;
+        g.d_addr = reinterpret_cast<int2 *>(dev + addr_off[k]);
+        size_t nodes = 0;
+        for (int b : g.members) {  // in the members' order, as apply_config fills it
+            pl->inst[b].d_addr = g.d_addr + nodes;
+            nodes += (size_t)pl->inst[b].K * pl->inst[b].pb.L;
+        }
     }
     // workspace: rings, then the final layers, then the statistics (per-wave
     // slots of every instance, then the totals)

@@ -1,6 +1,43 @@
 // Checks of the plan's host arithmetic (tables, LDS layouts, dispatch rules)
 // against what the kernels do with it.  No device is touched.  Each check
 // prints what fails and returns the number of failures.
+#include <hip/hip_runtime.h>
+
+#include <cstdlib>
+#include <cstring>
+
+// The device calls of the plan source, on host memory, with a count of the copies.
+namespace fake {
+int copies = 0;
+inline hipError_t get(int *d) { return *d = 0, hipSuccess; }
+inline hipError_t attribute(int *v, hipDeviceAttribute_t, int) { return *v = 163840, hipSuccess; }
+template <typename T>
+hipError_t alloc(T **p, size_t n)
+{
+    *p = static_cast<T *>(std::calloc(1, n));
+    return hipSuccess;
+}
+inline hipError_t release(void *p) { return std::free(p), hipSuccess; }
+inline hipError_t copy(void *d, const void *s, size_t n, hipMemcpyKind)
+{
+    ++copies;
+    if (n) std::memcpy(d, s, n);
+    return hipSuccess;
+}
+inline hipError_t symbol(void **p, const void *)
+{
+    static char byte;
+    *p = &byte;
+    return hipSuccess;
+}
+}  // namespace fake
+#define hipGetDevice fake::get
+#define hipDeviceGetAttribute fake::attribute
+#define hipMalloc fake::alloc
+#define hipFree fake::release
+#define hipMemcpy fake::copy
+#define hipGetSymbolAddress fake::symbol
+
 #ifndef BSDE_CAPI
 #define BSDE_CAPI "../../paper_1909_13560_amd/csrc/capi.hip"
 #endif
@@ -362,6 +399,47 @@ int check_exact_shapes()
     return fails;
 }
 
+// A plan copies its tables group by group, not instance by instance, and the
+// node addresses of every FP64 member are those of its shape.
+int check_plan_copies()
+{
+    for (int kind = 0; kind < 4; ++kind) {  // FP64, FP32, located, both forms mixed
+        std::vector<bsde_problem> pbs;
+        for (int b = 0; b < 150; ++b) {
+            bsde_problem p = problem(200 + 7 * (b % 40), 1 + b % 4, 5 + b % 9, 2.0 + b % 3, 0.3);
+            p.driver = BSDE_DRIVER_CUBIC;
+            if (kind == 1 || (kind == 3 && b % 2)) p.prec = BSDE_FP32_COMP;
+            if (kind == 2) p.vol_x = 0.1 * p.vol[0][0] / p.n_x[0];
+            pbs.push_back(p);
+        }
+        fake::copies = 0;
+        bsde_plan_t pl = nullptr;
+        EXPECT(bsde_plan(pbs.data(), (int)pbs.size(), &pl) == BSDE_OK, "kind %d", kind);
+        if (!pl) return fails;
+        EXPECT(fake::copies <= 1 + 2 * (int)pl->groups.size() && pl->groups.size() <= 8,
+               "kind %d: %d copies for %d groups", kind, fake::copies, (int)pl->groups.size());
+        for (size_t b = 0; b < pbs.size(); ++b) {
+            const Instance &in = pl->inst[b];
+            if (in.f32) continue;
+            const SweepConfig &c = pl->groups[in.group].cfg;
+            const std::vector<int2> v = fused_addresses(in, fused_layout(in, c.P, c.W, c.G), c.P);
+            EXPECT(std::memcmp(pl->d_desc[b].hot.addr, v.data(), v.size() * sizeof(int2)) == 0,
+                   "kind %d instance %d", kind, (int)b);
+        }
+        bsde_plan_destroy(pl);
+    }
+    // a 2-D plan on B-spline coefficients holds the tables of that form only
+    bsde_problem p = problem(65, 3, 16, 2.0, 0.3);
+    p.d = 2;
+    p.n_x[1] = 65;
+    p.x_max[1] = 64.0;
+    p.vol[1][1] = p.vol[0][0];
+    Instance2 in;
+    EXPECT(build_instance2(p, in) == BSDE_OK, "2-D");
+    EXPECT(in.nodes.empty() && (int)in.nodesb.size() == 3 * 16 * 16 && (int)in.m1.size() == 3 * 16 * 16, "2-D");
+    return fails;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -374,6 +452,7 @@ int main(int argc, char **argv)
     if (what == "fused_or_direct") return check_fused_or_direct() != 0;
     if (what == "located_shapes") return check_located_shapes() != 0;
     if (what == "exact_shapes") return check_exact_shapes() != 0;
+    if (what == "plan_copies") return check_plan_copies() != 0;
     std::printf("unknown check\n");
     return 2;
 }

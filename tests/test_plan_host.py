@@ -59,3 +59,7 @@ def test_located_shapes_follow_the_measured_times(checks):
 
 def test_exact_kernels_follow_the_measured_times(checks):
     checks("exact_shapes")
+
+
+def test_plans_copy_their_tables_by_group(checks):
+    checks("plan_copies")
