@@ -832,260 +832,277 @@ sweep2b(const Sweep2Args a)
     const int col = c0 + lane * 4;  // the lane's first column
     const bool near_l = c0 < a.nl, near_r = c0 + kTile2B > n1 - a.nr;
     const int nrows = a.K * a.L;
-    // the row ahead: its first window columns (kPre per lane) are loaded while
-    // the nodes of the row before are evaluated
-    constexpr int kPre = 1;
-    int nslot = a.n % S, njc = 0, nl0 = grp;  // layer and l0 of the row ahead
-    const double *nq0 = nullptr;
-    size_t nst = 0;  // bytes from one source row to the next
-    int nw0 = 0;
-    double pf[kPre][12];
-    auto load_column = [&](const double *q0, size_t st, int q, double (&r)[12]) {
-        // scalar row bases and one 32-bit column offset (a row is below 4 GiB)
-        const unsigned o = (unsigned)q * 8u;
+    // the node rows of this wavefront.  GUARD: no value that a node does not touch
+    // is multiplied by a zero weight, which would spread a non-finite one (end
+    // corrections of columns that have none, the rows beside the end row for cells
+    // outside the grid along axis 0).  The guards in every pass cost 3-5 % on grids up
+    // to 256^2 (16 nodes: 156 -> 161 us a step), so only a wavefront whose sums are not
+    // finite makes the guarded pass, and then all of its rows again
+    auto rows = [&](auto guard) {
+        constexpr bool GUARD = decltype(guard)::value;
+        // the row ahead: its first window columns (kPre per lane) are loaded while
+        // the nodes of the row before are evaluated
+        constexpr int kPre = 1;
+        int nslot = a.n % S, njc = 0, nl0 = grp;  // layer and l0 of the row ahead
+        const double *nq0 = nullptr;
+        int nw0 = 0;
+        double pf[kPre][12];
+        auto load_column = [&](const double *q0, int q, double (&r)[12]) {
+            // scalar row bases and one 32-bit column offset (a row is below 4 GiB)
+            const unsigned o = (unsigned)q * 8u;
+            const size_t st = (size_t)n1 * 8;
 #pragma unroll
-        for (int f = 0; f < 3; ++f) {
-            const char *v = reinterpret_cast<const char *>(q0 + (size_t)f * a.plane);
+            for (int f = 0; f < 3; ++f) {
+                const char *v = reinterpret_cast<const char *>(q0 + (size_t)f * a.plane);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) r[4 * f + k] = *reinterpret_cast<const double *>(v + k * st + o);
-        }
-    };
-    auto column = [&](int w0, int e) { return min(max(w0 + e, 0), n1 - 1); };
-    auto ahead = [&](int rowi) {  // loads for row rowi
-        while (nl0 >= a.L || njc == 0) {  // rows are ordered by layer
-            if (njc != 0) nl0 -= a.L;
-            ++njc;
-            nslot = nslot + 1 == S ? 0 : nslot + 1;
-        }
-        nl0 += kGroups2B;
-        const Row2B *rp = a.rowsb + rowi;
-        // a cell outside the grid takes the end row's value: all four rows are that
-        // row, so that nothing else, times zero, enters
-        const int p = i0 + const_load(&rp->m0);
-        const bool in = p >= 0 && p <= n0 - 2;
-        const int r0 = in ? min(max(p - 1, 0), n0 - 4) : p < 0 ? 0 : n0 - 1;
-        nst = in ? (size_t)n1 * 8 : 0;
-        nq0 = plane2<double>(a, nslot, 3) + (size_t)r0 * n1;
-        nw0 = c0 + const_load(&rp->m1lo) - 1;
-#pragma unroll
-        for (int u = 0; u < kPre; ++u) load_column(nq0, nst, column(nw0, lane + 64 * u), pf[u]);
-    };
-    if (grp < nrows) ahead(grp);
-    for (int rowi = grp; rowi < nrows; rowi += kGroups2B) {
-        const Row2B *rp = a.rowsb + rowi;
-        const int m0 = const_load(&rp->m0), m1lo = const_load(&rp->m1lo), m1hi = const_load(&rp->m1hi);
-        const bool extra = const_load(&rp->extra) != 0;
-        const int W = kTile2B + (m1hi - m1lo) + 3;
-        const int slots = W + (W >> 2) + 2;
-        double2 *wa = reinterpret_cast<double2 *>(mine);      // (s0, s1)
-        double *wb = reinterpret_cast<double *>(wa + slots);  // s2, then y in pass 2
-        double *we = wb + slots;                              // end columns: s0, s1, s2 each
-        const int mv = a.m1[(size_t)rowi * a.L + min(lane, a.L - 1)] - m1lo;
-        // axis-0 weights on four rows r0 .. r0 + 3 inside the grid
-        double b0 = const_load(&rp->b[0]), b1 = const_load(&rp->b[1]), b2 = const_load(&rp->b[2]),
-               b3 = const_load(&rp->b[3]);
-        // (the loads take the rows min(max(p - 1, 0), n0 - 4) ..)
-        const int p = i0 + m0;
-        if (p < 0 || p > n0 - 2) {  // the value at the end row
-            b0 = 1.0;
-            b1 = b2 = b3 = 0.0;
-        } else {
-            if (p == 0) {  // c(-1) = 2 c(0) - c(1)
-                const double x = b0;
-                b0 = fma(2.0, x, b1);
-                b1 = b2 - x;
-                b2 = b3;
-                b3 = 0.0;
-            }
-            if (p == n0 - 2) {  // c(n0) = 2 c(n0 - 1) - c(n0 - 2); rows shift down by one
-                const double x = b3;
-                b3 = fma(2.0, x, b2);
-                b2 = b1 - x;
-                b1 = b0;
-                b0 = 0.0;
-            }
-        }
-        const double *q0 = nq0;
-        const size_t st = nst;
-        const int w0 = nw0;  // window column 0
-        const double H = const_load(&rp->H), Gu = const_load(&rp->Gu), Gy = const_load(&rp->Gy),
-                     C = const_load(&rp->C), ey = const_load(&rp->ey);
-        const double p0 = a.drv.p0, p1 = a.drv.p1, p2 = a.drv.p2;
-        auto combine = [&](const double *r) { return fma(b3, r[3], fma(b0, r[0], fma(b2, r[2], b1 * r[1]))); };
-        auto put = [&](int e, const double (&r)[12]) {
-            const double y = combine(r), z1 = combine(r + 4), z2 = combine(r + 8);
-            const double u = fma(p0, y, fma(p1, z1, p2 * z2));
-            const double s1 = fma(C, z1, fma(Gu, u, Gy * y)), s2 = C * z2;
-            if (e < W) {
-                wa[slot4(e)] = make_double2(u, s1);
-                wb[slot4(e)] = s2;
-            } else if (e < W + kEdge2B) {  // the end columns
-                we[3 * (e - W)] = u;
-                we[3 * (e - W) + 1] = s1;
-                we[3 * (e - W) + 2] = s2;
+                for (int k = 0; k < 4; ++k) r[4 * f + k] = *reinterpret_cast<const double *>(v + k * st + o);
             }
         };
-        // element e of the staging: window column, then the four end columns
-        auto staged = [&](int e) {
-            const int x = min(e - W, kEdge2B - 1);
-            return x < 0 ? column(w0, e) : x < 2 ? x : n1 - 4 + x;
+        auto column = [&](int w0, int e) { return min(max(w0 + e, 0), n1 - 1); };
+        auto ahead = [&](int rowi) {  // loads for row rowi
+            while (nl0 >= a.L || njc == 0) {  // rows are ordered by layer
+                if (njc != 0) nl0 -= a.L;
+                ++njc;
+                nslot = nslot + 1 == S ? 0 : nslot + 1;
+            }
+            nl0 += kGroups2B;
+            const Row2B *rp = a.rowsb + rowi;
+            const int r0 = min(max(i0 + const_load(&rp->m0) - 1, 0), n0 - 4);
+            nq0 = plane2<double>(a, nslot, 3) + (size_t)r0 * n1;
+            nw0 = c0 + const_load(&rp->m1lo) - 1;
+#pragma unroll
+            for (int u = 0; u < kPre; ++u) load_column(nq0, column(nw0, lane + 64 * u), pf[u]);
         };
-        wave_lds_fence();  // the last row's reads are done
-#pragma unroll
-        for (int u = 0; u < kPre; ++u) put(lane + 64 * u, pf[u]);
-#pragma unroll 1
-        for (int e = lane + 64 * kPre; e - lane < W + kEdge2B; e += 128) {
-            double r[2][12];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) load_column(q0, st, staged(e + 64 * u), r[u]);
-#pragma unroll
-            for (int u = 0; u < 2; ++u) put(e + 64 * u, r[u]);
-        }
-        wave_lds_fence();
-        // corrections of the lane's columns: of the left end where the tile is
-        // near both (the right one's then follow after the nodes)
-        const double4 *ct = near_l ? a.corr_l + (size_t)rowi * a.nl : a.corr_r + (size_t)rowi * a.nr;
-        const int cn = near_l ? a.nl : a.nr;
-        double2 kc[4];
-        if (near_l || near_r) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int c = near_l ? col + k : n1 - 1 - (col + k);
-                const double2 v = *reinterpret_cast<const double2 *>(ct + min(max(c, 0), cn - 1));
-                kc[k] = c >= 0 && c < cn ? v : make_double2(0.0, 0.0);
-            }
-        }
-        if (rowi + kGroups2B < nrows) ahead(rowi + kGroups2B);
-        const double2 *la = wa + slot4(lane * 4);
-        const double *lb = wb + slot4(lane * 4);
-        const Node2B *nodes = a.nodesb + (size_t)rowi * a.L;
-#pragma unroll 1
-        for (int l = 0; l < a.L; ++l) {
-            const Node2B nd = load_node2b(nodes + l);
-            const int off = __builtin_amdgcn_readlane(mv, l), so = off + (off >> 2);
-            double2 ra[7];
-            double rb[7];
-            // (the comments keep the four patterns apart: merged into one, every
-            // read would compute its address and lose its alignment)
-            switch (off & 3) {
-            case 0:
-                fetch7<0>(la + so, ra);
-                fetch7<0>(lb + so, rb);
-                asm volatile("; pattern 0");
-                break;
-            case 1:
-                fetch7<1>(la + so, ra);
-                fetch7<1>(lb + so, rb);
-                asm volatile("; pattern 1");
-                break;
-            case 2:
-                fetch7<2>(la + so, ra);
-                fetch7<2>(lb + so, rb);
-                asm volatile("; pattern 2");
-                break;
-            default:
-                fetch7<3>(la + so, ra);
-                fetch7<3>(lb + so, rb);
-                asm volatile("; pattern 3");
-                break;
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const double t = fma(nd.w3, ra[k + 3].x,
-                                     fma(nd.w0, ra[k].x, fma(nd.w2, ra[k + 2].x, nd.w1 * ra[k + 1].x)));
-                Y[k] = fma(H, t, Y[k]);
-                Z1[k] = fma(nd.w0, ra[k].y, Z1[k]);
-                Z1[k] = fma(nd.w1, ra[k + 1].y, Z1[k]);
-                Z1[k] = fma(nd.w2, ra[k + 2].y, Z1[k]);
-                Z1[k] = fma(nd.w3, ra[k + 3].y, Z1[k]);
-                double z = fma(nd.gu, t, Z2[k]);
-                z = fma(nd.w0, rb[k], z);
-                z = fma(nd.w1, rb[k + 1], z);
-                z = fma(nd.w2, rb[k + 2], z);
-                Z2[k] = fma(nd.w3, rb[k + 3], z);
-            }
-        }
-        // corrections next to the ends of axis 1: x the sum of the weights, y
-        // of the weights times gu.  Non-finite end values enter the columns that
-        // have a weight only: zero times one would spread it over the tile
-        auto correct = [&](const double2 (&c)[4], int i, int o) {  // end columns i (inner), o (outer)
-            const double e0 = we[3 * i] - we[3 * o], e1 = we[3 * i + 1] - we[3 * o + 1],
-                         e2 = we[3 * i + 2] - we[3 * o + 2];
-            const bool finite = __all(isfinite(fabs(e0) + (fabs(e1) + fabs(e2))));
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (finite || c[k].x != 0.0) {
-                    Y[k] = fma(-H * c[k].x, e0, Y[k]);
-                    Z1[k] = fma(-c[k].x, e1, Z1[k]);
-                    Z2[k] = fma(-c[k].y, e0, fma(-c[k].x, e2, Z2[k]));
+        if (grp < nrows) ahead(grp);
+        for (int rowi = grp; rowi < nrows; rowi += kGroups2B) {
+            const Row2B *rp = a.rowsb + rowi;
+            const int m0 = const_load(&rp->m0), m1lo = const_load(&rp->m1lo), m1hi = const_load(&rp->m1hi);
+            const bool extra = const_load(&rp->extra) != 0;
+            const int W = kTile2B + (m1hi - m1lo) + 3;
+            const int slots = W + (W >> 2) + 2;
+            double2 *wa = reinterpret_cast<double2 *>(mine);      // (s0, s1)
+            double *wb = reinterpret_cast<double *>(wa + slots);  // s2, then y in pass 2
+            double *we = wb + slots;                              // end columns: s0, s1, s2 each
+            const int mv = a.m1[(size_t)rowi * a.L + min(lane, a.L - 1)] - m1lo;
+            // axis-0 weights on four rows r0 .. r0 + 3 inside the grid
+            double b0 = const_load(&rp->b[0]), b1 = const_load(&rp->b[1]), b2 = const_load(&rp->b[2]),
+                   b3 = const_load(&rp->b[3]);
+            // (the loads take the rows min(max(p - 1, 0), n0 - 4) ..)
+            const int p = i0 + m0;
+            if (p < 0) {  // the value at the first row
+                b0 = 1.0;
+                b1 = b2 = b3 = 0.0;
+            } else if (p > n0 - 2) {  // the value at the last row
+                b3 = 1.0;
+                b0 = b1 = b2 = 0.0;
+            } else {
+                if (p == 0) {  // c(-1) = 2 c(0) - c(1)
+                    const double x = b0;
+                    b0 = fma(2.0, x, b1);
+                    b1 = b2 - x;
+                    b2 = b3;
+                    b3 = 0.0;
                 }
-        };
-        if (near_l || near_r) correct(kc, near_l ? 1 : 2, near_l ? 0 : 3);
-        if (near_l && near_r) {
-            double2 k2[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int d = n1 - 1 - (col + k);
-                const double2 v = *reinterpret_cast<const double2 *>(a.corr_r + (size_t)rowi * a.nr +
-                                                                     min(max(d, 0), a.nr - 1));
-                k2[k] = d >= 0 && d < a.nr ? v : make_double2(0.0, 0.0);
+                if (p == n0 - 2) {  // c(n0) = 2 c(n0 - 1) - c(n0 - 2); rows shift down by one
+                    const double x = b3;
+                    b3 = fma(2.0, x, b2);
+                    b2 = b1 - x;
+                    b1 = b0;
+                    b0 = 0.0;
+                }
             }
-            correct(k2, 2, 3);
-        }
-        if (extra) {  // pass 2: the expectation of y
-            wave_lds_fence();
+            const double *q0 = nq0;
+            const int w0 = nw0;  // window column 0
+            const double H = const_load(&rp->H), Gu = const_load(&rp->Gu), Gy = const_load(&rp->Gy),
+                         C = const_load(&rp->C), ey = const_load(&rp->ey);
+            const double p0 = a.drv.p0, p1 = a.drv.p1, p2 = a.drv.p2;
+            auto combine = [&](const double *r) {
+                if (GUARD && p < 0) return r[0];
+                if (GUARD && p > n0 - 2) return r[3];
+                return fma(b3, r[3], fma(b0, r[0], fma(b2, r[2], b1 * r[1])));
+            };
+            auto put = [&](int e, const double (&r)[12]) {
+                const double y = combine(r), z1 = combine(r + 4), z2 = combine(r + 8);
+                const double u = fma(p0, y, fma(p1, z1, p2 * z2));
+                const double s1 = fma(C, z1, fma(Gu, u, Gy * y)), s2 = C * z2;
+                if (e < W) {
+                    wa[slot4(e)] = make_double2(u, s1);
+                    wb[slot4(e)] = s2;
+                } else if (e < W + kEdge2B) {  // the end columns
+                    we[3 * (e - W)] = u;
+                    we[3 * (e - W) + 1] = s1;
+                    we[3 * (e - W) + 2] = s2;
+                }
+            };
+            // element e of the staging: window column, then the four end columns
+            auto staged = [&](int e) {
+                const int x = min(e - W, kEdge2B - 1);
+                return x < 0 ? column(w0, e) : x < 2 ? x : n1 - 4 + x;
+            };
+            wave_lds_fence();  // the last row's reads are done
+#pragma unroll
+            for (int u = 0; u < kPre; ++u) put(lane + 64 * u, pf[u]);
 #pragma unroll 1
-            for (int e = lane; e - lane < W + kEdge2B; e += 256) {
-                double r[4][4];
+            for (int e = lane + 64 * kPre; e - lane < W + kEdge2B; e += 128) {
+                double r[2][12];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const unsigned o = (unsigned)staged(e + 64 * u) * 8u;
+                for (int u = 0; u < 2; ++u) load_column(q0, staged(e + 64 * u), r[u]);
 #pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        r[u][k] = *reinterpret_cast<const double *>(reinterpret_cast<const char *>(q0) +
-                                                                    k * st + o);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int x = e + 64 * u;
-                    const double y = combine(r[u]);
-                    if (x < W)
-                        wb[slot4(x)] = y;
-                    else if (x < W + kEdge2B)
-                        we[x - W] = y;
-                }
+                for (int u = 0; u < 2; ++u) put(e + 64 * u, r[u]);
             }
             wave_lds_fence();
+            // corrections of the lane's columns: of the left end where the tile is
+            // near both (the right one's then follow after the nodes)
+            const double4 *ct = near_l ? a.corr_l + (size_t)rowi * a.nl : a.corr_r + (size_t)rowi * a.nr;
+            const int cn = near_l ? a.nl : a.nr;
+            double2 kc[4];
+            if (near_l || near_r) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int c = near_l ? col + k : n1 - 1 - (col + k);
+                    const double2 v = *reinterpret_cast<const double2 *>(ct + min(max(c, 0), cn - 1));
+                    kc[k] = c >= 0 && c < cn ? v : make_double2(0.0, 0.0);
+                }
+            }
+            if (rowi + kGroups2B < nrows) ahead(rowi + kGroups2B);
+            const double2 *la = wa + slot4(lane * 4);
+            const double *lb = wb + slot4(lane * 4);
+            const Node2B *nodes = a.nodesb + (size_t)rowi * a.L;
 #pragma unroll 1
             for (int l = 0; l < a.L; ++l) {
                 const Node2B nd = load_node2b(nodes + l);
                 const int off = __builtin_amdgcn_readlane(mv, l), so = off + (off >> 2);
+                double2 ra[7];
                 double rb[7];
-                fetch7(lb + so, off, rb);
+                // (the comments keep the four patterns apart: merged into one, every
+                // read would compute its address and lose its alignment)
+                switch (off & 3) {
+                case 0:
+                    fetch7<0>(la + so, ra);
+                    fetch7<0>(lb + so, rb);
+                    asm volatile("; pattern 0");
+                    break;
+                case 1:
+                    fetch7<1>(la + so, ra);
+                    fetch7<1>(lb + so, rb);
+                    asm volatile("; pattern 1");
+                    break;
+                case 2:
+                    fetch7<2>(la + so, ra);
+                    fetch7<2>(lb + so, rb);
+                    asm volatile("; pattern 2");
+                    break;
+                default:
+                    fetch7<3>(la + so, ra);
+                    fetch7<3>(lb + so, rb);
+                    asm volatile("; pattern 3");
+                    break;
+                }
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const double t = fma(nd.w3, rb[k + 3],
-                                         fma(nd.w0, rb[k], fma(nd.w2, rb[k + 2], nd.w1 * rb[k + 1])));
-                    Y[k] = fma(ey, t, Y[k]);
-                    Z2[k] = fma(nd.gy, t, Z2[k]);
+                    const double t = fma(nd.w3, ra[k + 3].x,
+                                         fma(nd.w0, ra[k].x, fma(nd.w2, ra[k + 2].x, nd.w1 * ra[k + 1].x)));
+                    Y[k] = fma(H, t, Y[k]);
+                    Z1[k] = fma(nd.w0, ra[k].y, Z1[k]);
+                    Z1[k] = fma(nd.w1, ra[k + 1].y, Z1[k]);
+                    Z1[k] = fma(nd.w2, ra[k + 2].y, Z1[k]);
+                    Z1[k] = fma(nd.w3, ra[k + 3].y, Z1[k]);
+                    double z = fma(nd.gu, t, Z2[k]);
+                    z = fma(nd.w0, rb[k], z);
+                    z = fma(nd.w1, rb[k + 1], z);
+                    z = fma(nd.w2, rb[k + 2], z);
+                    Z2[k] = fma(nd.w3, rb[k + 3], z);
                 }
             }
-            // x the sum of the weights, z of the weights times gy
-            auto correct_y = [&](const double4 *t, int n, bool left) {
-                const double e0 = left ? we[1] - we[0] : we[2] - we[3];
+            // corrections next to the ends of axis 1: x the sum of the weights, y
+            // of the weights times gu
+            auto correct = [&](const double2 (&c)[4], int i, int o) {  // end columns i (inner), o (outer)
+                const double e0 = we[3 * i] - we[3 * o], e1 = we[3 * i + 1] - we[3 * o + 1],
+                             e2 = we[3 * i + 2] - we[3 * o + 2];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const int c = left ? col + k : n1 - 1 - (col + k);
-                    const double4 v = t[(size_t)rowi * n + min(max(c, 0), n - 1)];
-                    if (c >= 0 && c < n && v.x != 0.0) {
-                        Y[k] = fma(-ey * v.x, e0, Y[k]);
-                        Z2[k] = fma(-v.z, e0, Z2[k]);
-                    }
+                    if (GUARD && c[k].x == 0.0) continue;
+                    Y[k] = fma(-H * c[k].x, e0, Y[k]);
+                    Z1[k] = fma(-c[k].x, e1, Z1[k]);
+                    Z2[k] = fma(-c[k].y, e0, fma(-c[k].x, e2, Z2[k]));
                 }
             };
-            if (near_l) correct_y(a.corr_l, a.nl, true);
-            if (near_r) correct_y(a.corr_r, a.nr, false);
+            if (near_l || near_r) correct(kc, near_l ? 1 : 2, near_l ? 0 : 3);
+            if (near_l && near_r) {
+                double2 k2[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int d = n1 - 1 - (col + k);
+                    const double2 v = *reinterpret_cast<const double2 *>(a.corr_r + (size_t)rowi * a.nr +
+                                                                         min(max(d, 0), a.nr - 1));
+                    k2[k] = d >= 0 && d < a.nr ? v : make_double2(0.0, 0.0);
+                }
+                correct(k2, 2, 3);
+            }
+            if (extra) {  // pass 2: the expectation of y
+                wave_lds_fence();
+#pragma unroll 1
+                for (int e = lane; e - lane < W + kEdge2B; e += 256) {
+                    double r[4][4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const unsigned o = (unsigned)staged(e + 64 * u) * 8u;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            r[u][k] = *reinterpret_cast<const double *>(reinterpret_cast<const char *>(q0) +
+                                                                        k * (size_t)n1 * 8 + o);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int x = e + 64 * u;
+                        const double y = combine(r[u]);
+                        if (x < W)
+                            wb[slot4(x)] = y;
+                        else if (x < W + kEdge2B)
+                            we[x - W] = y;
+                    }
+                }
+                wave_lds_fence();
+#pragma unroll 1
+                for (int l = 0; l < a.L; ++l) {
+                    const Node2B nd = load_node2b(nodes + l);
+                    const int off = __builtin_amdgcn_readlane(mv, l), so = off + (off >> 2);
+                    double rb[7];
+                    fetch7(lb + so, off, rb);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const double t = fma(nd.w3, rb[k + 3],
+                                             fma(nd.w0, rb[k], fma(nd.w2, rb[k + 2], nd.w1 * rb[k + 1])));
+                        Y[k] = fma(ey, t, Y[k]);
+                        Z2[k] = fma(nd.gy, t, Z2[k]);
+                    }
+                }
+                // x the sum of the weights, z of the weights times gy
+                auto correct_y = [&](const double4 *t, int n, bool left) {
+                    const double e0 = left ? we[1] - we[0] : we[2] - we[3];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int c = left ? col + k : n1 - 1 - (col + k);
+                        const double4 v = t[(size_t)rowi * n + min(max(c, 0), n - 1)];
+                        const bool in = c >= 0 && c < n;
+                        if (GUARD && (!in || v.x == 0.0)) continue;
+                        Y[k] = fma(in ? -ey * v.x : 0.0, e0, Y[k]);
+                        Z2[k] = fma(in ? -v.z : 0.0, e0, Z2[k]);
+                    }
+                };
+                if (near_l) correct_y(a.corr_l, a.nl, true);
+                if (near_r) correct_y(a.corr_r, a.nr, false);
+            }
         }
+    };
+    rows(std::false_type());
+    double sum = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sum += Y[k] + (Z1[k] + Z2[k]);
+    if (__any(!isfinite(sum))) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) Y[k] = Z1[k] = Z2[k] = 0.0;
+        rows(std::true_type());
     }
     // the groups' sums meet in LDS (each over its own window); thread t
     // finishes column t of the tile
