@@ -80,7 +80,7 @@ struct Instance {
     bsde::DriverParams drv;
     std::vector<int> m, win_lo, win_hi;
     std::vector<double> B, C, D, phi, cfy, cfz, cz, cy, cyz, dw;
-    bsde::NodeTable dtab;
+    bsde::NodeTable dtab{};
     size_t ring_off, fin_off, stat_off;
     int nwaves;  // per-wave statistics slots (P = 1 has the most waves)
     int group;
@@ -2135,7 +2135,7 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         });
         g.max_steps = pl->inst[g.members[0]].steps;
     }
-    // device tables: per instance node records (both forms) and offsets; the
+    // device tables: per instance node records (of its form) and offsets; the
     // descriptors (with the window bounds); per group the tile maps
     size_t tbytes = 0;
     std::vector<size_t> toff(batch);
@@ -2143,9 +2143,9 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         const Instance &in = pl->inst[b];
         toff[b] = tbytes;
         const size_t kl = (size_t)in.K * in.pb.L;
-        tbytes += align_up(kl * sizeof(int), 256) + align_up(kl * sizeof(bsde::NodeRec), 256) +
-                  align_up(kl * sizeof(bsde::NodeRec32), 256) + align_up(kl * sizeof(double), 256) +
-                  align_up(kl * sizeof(bsde::NodeRecB), 256);
+        tbytes += align_up(kl * sizeof(int), 256) + align_up(kl * sizeof(double), 256) +
+                  (in.f32 ? align_up(kl * sizeof(bsde::NodeRec32), 256)
+                          : align_up(kl * sizeof(bsde::NodeRec), 256) + align_up(kl * sizeof(bsde::NodeRecB), 256));
         size_t nbw = 0;
         for (int j = 1; j <= in.K; ++j) nbw += 4 * in.band[j].ev.size();
         tbytes += align_up(nbw * sizeof(double), 256) + align_up(in.ex_band.size() * sizeof(double), 256) +
@@ -2183,47 +2183,54 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
             o += align_up(bytes, 256);
             return d;
         };
-        std::vector<bsde::NodeRec> recs(kl);
-        std::vector<bsde::NodeRec32> recs32(kl);
-        std::vector<bsde::NodeRecB> recsb(kl);
-        for (size_t k = 0; k < kl; ++k) {
-            const int l = (int)(k % in.pb.L), j = (int)(k / in.pb.L) + 1;
-            const double cy = (j == in.pb.k_y) ? in.cy[l] : 0.0;
-            recs[k] = bsde::NodeRec{in.B[k],   in.C[k],  in.D[k], in.cfy[k],
-                                    in.cfz[k], in.cz[k], cy,      in.cyz[k]};
-            recs32[k] = bsde::NodeRec32{(float)in.B[k],   (float)in.C[k],   (float)in.D[k],
-                                        (float)in.cfy[k], (float)in.cfz[k], (float)in.cz[k],
-                                        (float)cy,        (float)in.cyz[k], in.cz[k],
-                                        cy,               in.cyz[k],        0.0};
-            // cubic B-spline weights at the fraction; for the linear driver
-            // f = p0 y + p1 z + p3 folded into the weights
-            const double ph = in.phi[k], u = 1.0 - ph;
-            bsde::NodeRecB &rb = recsb[fused_position(in.K, in.pb.L, j, l)];
-            rb.b0 = u * u * u / 6.0;
-            rb.b1 = 2.0 / 3.0 - 0.5 * ph * ph * (2.0 - ph);
-            rb.b2 = 2.0 / 3.0 - 0.5 * u * u * (2.0 - u);
-            rb.b3 = ph * ph * ph / 6.0;
-            if (in.located) {  // located nodes: the increments in cells
-                rb.b0 = in.dw[k] / in.dx;
-                rb.b1 = j * in.dt / in.dx;
+        if (in.f32) {
+            std::vector<bsde::NodeRec32> recs(kl);
+            for (size_t k = 0; k < kl; ++k) {
+                const int l = (int)(k % in.pb.L), j = (int)(k / in.pb.L) + 1;
+                const double cy = (j == in.pb.k_y) ? in.cy[l] : 0.0;
+                recs[k] = bsde::NodeRec32{(float)in.B[k],   (float)in.C[k],   (float)in.D[k],
+                                          (float)in.cfy[k], (float)in.cfz[k], (float)in.cz[k],
+                                          (float)cy,        (float)in.cyz[k], in.cz[k],
+                                          cy,               in.cyz[k],        0.0};
             }
-            if (in.pb.driver == BSDE_DRIVER_LINEAR) {
-                rb.w0 = in.cfy[k] * in.pb.p[0] + cy;
-                rb.w1 = in.cfy[k] * in.pb.p[1];
-                rb.w2 = in.cfz[k] * in.pb.p[0];
-                rb.w3 = in.cfz[k] * in.pb.p[1] + in.cz[k];
-            } else {
-                rb.w0 = in.cfy[k];
-                rb.w1 = in.cfz[k];
-                rb.w2 = in.cz[k];
-                rb.w3 = cy;
+            in.dtab.rec32 =
+                static_cast<const bsde::NodeRec32 *>(put(recs.data(), kl * sizeof(bsde::NodeRec32)));
+        } else {
+            std::vector<bsde::NodeRec> recs(kl);
+            std::vector<bsde::NodeRecB> recsb(kl);
+            for (size_t k = 0; k < kl; ++k) {
+                const int l = (int)(k % in.pb.L), j = (int)(k / in.pb.L) + 1;
+                const double cy = (j == in.pb.k_y) ? in.cy[l] : 0.0;
+                recs[k] = bsde::NodeRec{in.B[k],   in.C[k],  in.D[k], in.cfy[k],
+                                        in.cfz[k], in.cz[k], cy,      in.cyz[k]};
+                // cubic B-spline weights at the fraction; for the linear driver
+                // f = p0 y + p1 z + p3 folded into the weights
+                const double ph = in.phi[k], u = 1.0 - ph;
+                bsde::NodeRecB &rb = recsb[fused_position(in.K, in.pb.L, j, l)];
+                rb.b0 = u * u * u / 6.0;
+                rb.b1 = 2.0 / 3.0 - 0.5 * ph * ph * (2.0 - ph);
+                rb.b2 = 2.0 / 3.0 - 0.5 * u * u * (2.0 - u);
+                rb.b3 = ph * ph * ph / 6.0;
+                if (in.located) {  // located nodes: the increments in cells
+                    rb.b0 = in.dw[k] / in.dx;
+                    rb.b1 = j * in.dt / in.dx;
+                }
+                if (in.pb.driver == BSDE_DRIVER_LINEAR) {
+                    rb.w0 = in.cfy[k] * in.pb.p[0] + cy;
+                    rb.w1 = in.cfy[k] * in.pb.p[1];
+                    rb.w2 = in.cfz[k] * in.pb.p[0];
+                    rb.w3 = in.cfz[k] * in.pb.p[1] + in.cz[k];
+                } else {
+                    rb.w0 = in.cfy[k];
+                    rb.w1 = in.cfz[k];
+                    rb.w2 = in.cz[k];
+                    rb.w3 = cy;
+                }
             }
+            in.dtab.rec = static_cast<const bsde::NodeRec *>(put(recs.data(), kl * sizeof(bsde::NodeRec)));
+            in.d_recb =
+                static_cast<const bsde::NodeRecB *>(put(recsb.data(), kl * sizeof(bsde::NodeRecB)));
         }
-        in.dtab.rec = static_cast<const bsde::NodeRec *>(put(recs.data(), kl * sizeof(bsde::NodeRec)));
-        in.dtab.rec32 =
-            static_cast<const bsde::NodeRec32 *>(put(recs32.data(), kl * sizeof(bsde::NodeRec32)));
-        in.d_recb =
-            static_cast<const bsde::NodeRecB *>(put(recsb.data(), kl * sizeof(bsde::NodeRecB)));
         in.dtab.m = static_cast<const int *>(put(in.m.data(), kl * sizeof(int)));
         in.dtab.dw = static_cast<const double *>(put(in.dw.data(), kl * sizeof(double)));
         std::vector<double> bw;

@@ -420,6 +420,9 @@ int check_plan_copies()
                "kind %d: %d copies for %d groups", kind, fake::copies, (int)pl->groups.size());
         for (size_t b = 0; b < pbs.size(); ++b) {
             const Instance &in = pl->inst[b];
+            const bsde::NodeTable &tab = pl->d_desc[b].a.tab;  // the records of the form alone
+            EXPECT(!tab.rec == in.f32 && !tab.rec32 == !in.f32 && !pl->d_desc[b].hot.recb == in.f32,
+                   "kind %d instance %d", kind, (int)b);
             if (in.f32) continue;
             const SweepConfig &c = pl->groups[in.group].cfg;
             const std::vector<int2> v = fused_addresses(in, fused_layout(in, c.P, c.W, c.G), c.P);
