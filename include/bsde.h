@@ -373,16 +373,17 @@ typedef struct {
                              the spline of the newest layer in-kernel, 1 = direct
                              loads, 2 = the two-dimensional sweep, 3 = nodes
                              located per point (state-dependent coefficients;
-                             in LDS windows in FP64 where they fit), 4 = exact
+                             with LDS windows, lds_bytes > 0, in FP64 where they
+                             fit and are the faster), 4 = exact
                              expectations as banded Toeplitz products on matrix
                              cores (BSDE_QUAD_EXACT)                             */
     int points_per_lane;  /* grid points per lane of the sweep kernel            */
     int node_groups;      /* thread groups sharing the nodes of one tile; for
                              path 4 the groups of four wavefronts sharing its
-                             band, or, for bands beyond LDS and for path 1, the
-                             blocks that split one tile's band or node chunks
-                             (their partial sums are added by a second launch
-                             when > 1)                                           */
+                             band, or, where the band passes LDS in chunks, and
+                             for path 1, the blocks that split one tile's band
+                             or node chunks (their partial sums are added by a
+                             second launch when > 1)                             */
     int blocks;           /* tiles of the first sweep launch of group 0          */
     long long lds_bytes;  /* dynamic LDS per block of the sweep kernel           */
 } bsde_kernel_times;
@@ -407,9 +408,11 @@ typedef struct {
 /*
  * bsde_autotune -- choose the sweep kernel shape of every group of the plan
  * by measurement: the initial layers of io are loaded into ws, and for each
- * shape that fits (fused kernel with 1, 2 or 4 points per lane and 1 or 2
- * node groups; when none fits, the direct kernel with one point per lane,
- * split over blocks on a small grid, and with two) the group's first time step
+ * shape that fits (the fused kernel's tiles of 64 to 1024 points; the direct
+ * kernel with one point per lane, split over blocks on a small grid, and with
+ * two, when no fused shape fits or, in FP64, its estimate is close; located
+ * nodes in LDS windows and from HBM/L2 likewise; exact expectations have one
+ * shape) the group's first time step
  * and three more spread over its steps (so a batch's shrinking set of active
  * instances counts) are run `reps` times, replayed from a captured graph as
  * a solve would run them (directly when BSDE_GRAPH=0), and timed with

@@ -7,9 +7,9 @@
 //                 elements: (y, z), then a spline plane (16 bytes each in
 //                 FP64, 8 in FP32), so each launch writes whole planes.  The
 //                 spline plane holds the B-spline coefficients (c_y, c_z) for
-//                 the fused and the one-launch exact sweep in FP64, the second
-//                 derivatives (M_y, M_z) for the other kernels and the FP32
-//                 form; the FP32 form adds a third plane, the rounding
+//                 the fused sweep in FP64 (located nodes in LDS windows too) and
+//                 the one-launch exact sweep, the second derivatives (M_y, M_z)
+//                 for the other kernels and the FP32 form; the FP32 form adds a third plane, the rounding
 //                 residuals (e_y, e_z) of the stored values (error feedback)
 //   per instance: per-wavefront Picard counters (statistics)
 //   totals      : 4 x u64 reduced statistics
@@ -1035,11 +1035,6 @@ SweepConfig direct_config(const std::vector<Instance> &all, const std::vector<in
     return c;
 }
 
-// Default shape: the fused kernel in the shape that the cost estimate favours;
-// the direct kernel where that is faster (takes_fused) or no window fits in LDS.
-// BSDE_SWEEP = "fused:P:G",
-// "fused:P:G:W" or "direct:P:S" overrides; bsde_autotune replaces the choice
-// by the fastest measured shape.
 bool group_gathers(const std::vector<Instance> &all, const std::vector<int> &members)
 {
     for (int b : members)
@@ -1239,8 +1234,10 @@ double gather_cost(const std::vector<Instance> &all, const std::vector<int> &mem
 // alone).  Measured a step, fused against HBM/L2: K = 4, L = 16, ratio 60 (102 KB)
 // 18.7 and 34.3 us on 65536 points, 64.4 and 61.2 on 262144; K = 1, L = 8, ratio
 // 120 9.0 and 12.0, 17.4 and 15.5; ratio 16 faster throughout (34 and 62 us on
-// 262144 points).  Wider windows keep the kernel whose separate spline launches
-// show in the launch counts of bsde_profile_kernels.
+// 262144 points).  The 128 KB are no speed limit: wider windows would be faster in
+// LDS as well on grids up to about 60000 points (139 KB: 1.13 ms a solve and 4.35
+// from HBM/L2 on 2001 points, 3.63 and 4.21 on 60000).  They keep the launches that
+// bsde_profile_kernels has reported for them, a sweep and a spline launch a step.
 bool takes_windows(const std::vector<Instance> &all, int b, size_t max_lds)
 {
     if (!all[b].located) return false;
@@ -1262,6 +1259,10 @@ SweepConfig gather_config(const std::vector<Instance> &all, const std::vector<in
     return SweepConfig{PATH_GATHER, 1, 1, 0};
 }
 
+// Default shape: the fused kernel in the shape that the cost estimate favours;
+// the direct kernel where that is faster (takes_fused) or no window fits in LDS.
+// BSDE_SWEEP = "fused:P:G", "fused:P:G:W" or "direct:P:S" overrides;
+// bsde_autotune replaces the choice by the fastest measured shape.
 SweepConfig default_config(const std::vector<Instance> &all, const Group &g, size_t max_lds)
 {
     if (group_gathers(all, g.members)) return gather_config(all, g.members, max_lds);

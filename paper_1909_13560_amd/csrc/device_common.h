@@ -394,11 +394,6 @@ template <int P>
 struct WinStore64 {
     double2 *wy;
     static constexpr int kM = kSplineSlots;
-    __device__ void put(int sl, const double2 &v, const double2 &m) const
-    {
-        wy[sl] = v;
-        wy[sl + kM] = m;
-    }
     __device__ void val(int sl, double y, double z) const { wy[sl] = make_double2(y, z); }
     __device__ void der(int sl, double my, double mz) const { wy[sl + kM] = make_double2(my, mz); }
     __device__ double2 ders(int sl) const { return wy[sl + kM]; }
@@ -407,10 +402,6 @@ struct WinStore64 {
 template <int P>
 struct WinStore32 {
     float4 *w;
-    __device__ void put(int sl, const float2 &v, const float2 &m) const
-    {
-        w[sl] = make_float4(v.x, v.y, m.x, m.y);
-    }
     __device__ void val(int sl, double y, double z) const
     {
         reinterpret_cast<float2 *>(w + sl)[0] = make_float2((float)y, (float)z);

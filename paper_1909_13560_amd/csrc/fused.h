@@ -6,10 +6,11 @@
 // points per lane, WP wavefronts along the points) and has G groups of WP
 // wavefronts that share the nodes.  It stages every layer's window (the
 // records its nodes touch: the tile widened by the layer's node offsets) in
-// LDS with all loads in flight at once, builds the spline of layer n+1 from
-// that layer's values on its own window, runs the node loops of layers K..2
-// while the spline's first pass drains, then layer 1, adds the groups' sums in
-// a fixed order and solves the implicit y equation, one point per thread.
+// LDS with all loads in flight at once: layer n+1's values come first, and both
+// passes of its spline run on them, with a barrier after each, before the other
+// layers' records are written to LDS.  The node loops of all K layers follow;
+// then the groups' sums are added in a fixed order and the implicit y equation is
+// solved, one point per thread.
 //
 // FP64 form: the spline is kept by its cubic B-spline coefficients
 //   c_i = v_i - dx^2/6 M_i   (v = sum_k b_k(phi) c_{p-1+k}, k = 0..3),

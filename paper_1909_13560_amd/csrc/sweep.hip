@@ -12,12 +12,13 @@
 // The sweep kernels that compute layer n from layers n+1..n+K:
 //   sweep_fused  (fused.h) LDS windows of every layer, the spline of layer n+1
 //                built in-kernel: one launch per step.
-//   sweep_direct (windows too wide for LDS): records are read straight from
-//                HBM/L2, P consecutive points per lane; the natural spline of
-//                the new layer is a separate launch.
-//   sweep_gather (state-dependent coefficients whose windows do not fit LDS, the
-//                FP32 form, the E[y dW]/dt z form): nodes located per point
-//                and read from HBM/L2.
+//   sweep_direct (windows too wide for LDS or, in FP64, so wide that only small
+//                tiles fit a large grid; the E[y dW]/dt z form): records are
+//                read straight from HBM/L2, P consecutive points per lane; the
+//                natural spline of the new layer is a separate launch.
+//   sweep_gather (state-dependent coefficients; in FP64 with windows for LDS they
+//                take sweep_fused where that is the faster): nodes located per
+//                point and read from HBM/L2.
 #include "device_common.h"
 #include "fused.h"
 #include "kernels.h"

@@ -14,7 +14,8 @@
 // per-point combination.
 //
 // Bands that fit LDS take sweep_exact (below): on B-spline coefficients, one
-// launch per step.  Wider ones take sweep_toeplitz, described here.
+// launch per step.  Wider ones, and those of large grids where it is the faster,
+// take sweep_toeplitz, described here.
 //
 // A block computes the 256 consecutive points of one tile as a 16 x 16 tile
 // D[r][q] = sum_k A[r][k] B[k][q] of v_mfma_f64_16x16x4f64 products: point
@@ -423,8 +424,9 @@ __global__ void __launch_bounds__(256) toeplitz_finish(const StepArgs s, int S)
 // Coefficients beyond the grid continue as constants; the expectations of the
 // points within reach of an end are corrected in the finish (GaussBand).
 // Per step on 16384 points, R = 16, K = 4: 23.4 -> 11.6 us (two launches -> one);
-// the matrix products need 2.4 us of it, the loads, the spline's passes and the
-// launch the rest.
+// the matrix products need 2.4 us of it.  The rest is the chain of a step at two
+// wavefronts a SIMD: the launch, the loads, the spline's passes between barriers
+// and the waits of the products for their LDS reads.
 // ---------------------------------------------------------------------------
 template <int G>
 __global__ void __launch_bounds__(256 * G) sweep_exact(const StepArgs s)
