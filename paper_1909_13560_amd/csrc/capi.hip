@@ -880,10 +880,11 @@ std::vector<int2> fused_addresses(const Instance &in, const FusedLds &lds, int P
 // measured, in us: 256 CUs share the tiles, the first of a CU takes
 //   first + first_node K L + first_kb LDS     and each further one
 //   tile + node K L + kb LDS (+ alone + alone_node K L where the LDS leaves room
-// for one block), and both exp K L T / 64 where the driver has an exponential.  LDS in KiB.  Fitted to solves of 500 to 1048576 points, K L = 4 to 128 and
+// for one block), and both exp K L T / 64 where the driver has an exponential.
+// LDS in KiB.  Fitted to solves of 500 to 1048576 points, K L = 4 to 128 and
 // stability ratios 3 to 180 (max error 7 to 10% in FP64, 8 to 25% in the FP32
-// form).  Where the lines cross, measured a step: 65536 points, K =
-// 4, L = 16: 64-point tiles 14.0 us, 256 10.3, 1024 19.5; 262144: 42.2, 23.3, 21.1.
+// form).  Where the lines cross, measured a step: 65536 points, K = 4, L = 16:
+// 64-point tiles 14.0 us, 256 10.3, 1024 19.5; 262144: 42.2, 23.3, 21.1.
 // 1048576 points, K = 1, L = 16: four groups a 1024-point tile 38.7 us, two 30.0,
 // where few nodes leave little to share out; K = 4: 74.4 and 82.7.  FP32 form, K
 // L = 16: 256-point tiles 8.0, 512 8.3, 1024 10.7 us on 32768 points, 34.5, 34.3
@@ -1117,7 +1118,9 @@ ExactLds exact_layout(const Instance &in, int G)
 size_t exact_lds(const Instance &in, int G, size_t max_lds)
 {
     for (int j = 1; j <= in.K; ++j)
-        if ((long)in.band[j].ec.size() > (long)(max_lds / 16)) return 0;
+        if ((long)in.band[j].ec.size() > (long)(max_lds / 16) ||
+            std::max({in.ex_il[j], in.ex_ir[j], in.ex_nl[j], in.ex_nr[j]}) > 32767)
+            return 0;  // (the latter: packed in ExactHot; no band that fits comes near)
     const size_t need = exact_layout(in, G).total;
     return need <= max_lds ? need : 0;
 }
@@ -1357,10 +1360,8 @@ bsde_status apply_config(bsde_plan_s &pl, Group &g, const SweepConfig &c)
                 h.lds_band[j] = l.band[j];
                 h.nb[j] = (int)in.band[j].ec.size();
                 h.boff[j] = in.ex_boff[j];
-                h.nl[j] = in.ex_nl[j];
-                h.nr[j] = in.ex_nr[j];
-                h.il[j] = in.ex_il[j];
-                h.ir[j] = in.ex_ir[j];
+                h.cl[j] = in.ex_il[j] | in.ex_nl[j] << 16;
+                h.cr[j] = in.ex_ir[j] | in.ex_nr[j] << 16;
                 h.loff[j] = in.ex_loff[j];
                 h.roff[j] = in.ex_roff[j];
             }
@@ -2166,7 +2167,8 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         map_off[k] = tbytes;
         tbytes += align_up(tiles * sizeof(int), 256) + align_up(stiles * sizeof(int), 256);
         addr_off[k] = tbytes;
-        if (!pl->groups[k].f32) tbytes += align_up(nodes * sizeof(int2), 256);
+        // (a wavefront without nodes may read the entry after the last, class_address)
+        if (!pl->groups[k].f32) tbytes += align_up((nodes + 1) * sizeof(int2), 256);
     }
     if (hipMalloc(&pl->d_tables, std::max<size_t>(tbytes, 256)) != hipSuccess) {
         delete pl;

@@ -193,9 +193,9 @@ struct alignas(64) FusedHot {
 struct alignas(64) ExactHot {
     size_t ring_off;
     const double *band;      // per layer ec, wc (nb[j] weights each) at boff[j]
-    const double2 *corr;     // per layer the end corrections (E, E[. dW]) of nl[j] points at loff[j]
-                             // (il[j], ... from the left end) and of nr[j] at roff[j] (ir[j], ...
-                             // from the right end)
+    const double2 *corr;     // per layer the end corrections (E, E[. dW]) at loff[j] and roff[j], of
+                             // the points that cl[j] and cr[j] tell: how many (high half), and
+                             // the first one's distance from the left or right end (low half)
     int nx, npad, pad_l, K;
     int n0, n0_mod, mod_magic, tile_base;
     int ntiles, lds_d, lds_a, lds_edge;
@@ -204,8 +204,7 @@ struct alignas(64) ExactHot {
     int shift[kMaxOrder + 1], steps[kMaxOrder + 1];  // band start in the window (a multiple of 8), 4-tap steps
     int nb[kMaxOrder + 1], boff[kMaxOrder + 1];
     int lds_win[kMaxOrder + 1], lds_band[kMaxOrder + 1];
-    int nl[kMaxOrder + 1], nr[kMaxOrder + 1], loff[kMaxOrder + 1], roff[kMaxOrder + 1];
-    int il[kMaxOrder + 1], ir[kMaxOrder + 1];
+    int cl[kMaxOrder + 1], cr[kMaxOrder + 1], loff[kMaxOrder + 1], roff[kMaxOrder + 1];
 };
 constexpr int kExactTile = 64;  // points of a block of that sweep
 

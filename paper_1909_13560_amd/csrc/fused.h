@@ -308,7 +308,8 @@ struct LdsWindow {
 };
 
 // The list of class c (nodes l = c mod 8 of all layers) in the tables, and the
-// address that a lane holds for it.
+// address that a lane holds for it (an empty list may start at the table's end:
+// one entry more is allocated).
 static_assert(kMaxOrder * 8 <= 64, "a class's node addresses fit the lanes of a wavefront");
 __device__ inline void class_list(int K, int L, int c, int &start, int &cnt)
 {
@@ -317,7 +318,7 @@ __device__ inline void class_list(int K, int L, int c, int &start, int &cnt)
 }
 __device__ inline int2 class_address(const int2 *addr, int start, int cnt, int lane)
 {
-    return addr[cnt > 0 ? start + min(lane, cnt - 1) : 0];
+    return addr[start + max(min(lane, cnt - 1), 0)];
 }
 
 // The nodes of one class (FP64 form): cnt consecutive table entries, whose

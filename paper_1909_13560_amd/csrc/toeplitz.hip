@@ -598,7 +598,8 @@ __global__ void __launch_bounds__(256 * G) sweep_exact(const StepArgs s)
     const SweepArgs &r = d.a;
     for (int j = 1; j <= K; ++j) {
         const ToepTable &t = r.toep;
-        const int nl = const_load(&d.ex.nl[j]), nr = const_load(&d.ex.nr[j]);
+        const int cl = const_load(&d.ex.cl[j]), cr = const_load(&d.ex.cr[j]);
+        const int nl = cl >> 16, nr = cr >> 16;
         Yc += const_load(&t.cy_1[j]);
         auto correct = [&](const double2 &k, const double2 &in, const double2 &out) {
             const double ey = in.x - out.x, ez = in.y - out.y;
@@ -607,7 +608,7 @@ __global__ void __launch_bounds__(256 * G) sweep_exact(const StepArgs s)
                   k.y * (const_load(&t.cz_wy[j]) * ey + const_load(&t.cz_wz[j]) * ez);
         };
         const double2 *e = edge + 4 * (j - 1);
-        const int p = i - const_load(&d.ex.il[j]), q = nx - 1 - i - const_load(&d.ex.ir[j]);
+        const int p = i - (cl & 0xffff), q = nx - 1 - i - (cr & 0xffff);
         if (p >= 0 && p < nl) correct(h.corr[const_load(&d.ex.loff[j]) + p], e[1], e[0]);
         if (q >= 0 && q < nr) correct(h.corr[const_load(&d.ex.roff[j]) + q], e[2], e[3]);
     }
