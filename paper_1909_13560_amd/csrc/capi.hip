@@ -885,6 +885,7 @@ std::vector<int2> fused_addresses(const Instance &in, const FusedLds &lds, int P
 // stability ratios 3 to 180 (max error 7 to 10% in FP64, 8 to 25% in the FP32
 // form).  Where the lines cross, measured a step: 65536 points, K = 4, L = 16:
 // 64-point tiles 14.0 us, 256 10.3, 1024 19.5; 262144: 42.2, 23.3, 21.1.
+// 4194304 points: 256-point tiles 298, 1024 289 (at ratio 4 283 and 285).
 // 1048576 points, K = 1, L = 16: four groups a 1024-point tile 38.7 us, two 30.0,
 // where few nodes leave little to share out; K = 4: 74.4 and 82.7.  FP32 form, K
 // L = 16: 256-point tiles 8.0, 512 8.3, 1024 10.7 us on 32768 points, 34.5, 34.3
@@ -895,7 +896,7 @@ struct Shape {
 };
 constexpr Shape kShapes64[] = {{1, 1, 8, 4.0, 0.032, 0.023, 1.37, 0.0114, 0.0063, 1.9, 0.0105, 0.0300},
                                {2, 1, 8, 3.9, 0.038, 0.023, 1.49, 0.0196, 0.0061, 1.4, 0.0105, 0.0220},
-                               {4, 1, 8, 4.8, 0.064, 0.021, 1.14, 0.0330, 0.0189, 2.0, 0.0105, 0.0165},
+                               {4, 1, 8, 4.8, 0.064, 0.021, 1.34, 0.0330, 0.0189, 2.0, 0.0105, 0.0165},
                                {4, 4, 4, 8.5, 0.178, 0.0, 6.08, 0.169, 0.0041, 0.0, 0.0, 0.0130},
                                {4, 4, 2, 6.6, 0.200, 0.033, 0.5, 0.130, 0.0550, 3.20, 0.0, 0.0130}};
 constexpr Shape kShapes32[] = {{1, 4, 1, 5.5, 0.096, 0.046, 0.73, 0.0338, 0.0216, 0.0, 0.0, 0.0125},
@@ -919,10 +920,13 @@ double fused_cost(const std::vector<Instance> &all, const std::vector<int> &memb
             const Instance &in = all[b];
             if (in.steps <= (long)longest * k / 4) continue;
             const double t = (in.nx + T - 1) / T, kl = (double)in.K * in.pb.L;
+            // (wavefronts beyond the end of the grid have no nodes to do)
+            const double tn = (in.nx + 64 * c.P - 1) / (64 * c.P) / (double)c.W;
             const double ex = in.pb.driver == BSDE_DRIVER_EXP ? q.exp * T / 64.0 * kl : 0.0;
             tiles += t;
             first += t * (q.first + q.first_node * kl + ex);
-            more += t * (q.tile + q.node * kl + (alone ? q.alone + q.alone_node * kl : 0.0) + ex);
+            more += t * (q.tile + (alone ? q.alone : 0.0)) +
+                    tn * ((q.node + (alone ? q.alone_node : 0.0)) * kl + ex);
         }
         first = first / tiles + q.first_kb * kb;
         more = more / tiles + q.kb * kb;
