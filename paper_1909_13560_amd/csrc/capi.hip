@@ -901,7 +901,7 @@ constexpr Shape kShapes64[] = {{1, 1, 8, 4.0, 0.032, 0.023, 1.37, 0.0114, 0.0063
                                {4, 4, 2, 6.6, 0.200, 0.033, 0.5, 0.130, 0.0550, 3.20, 0.0, 0.0130}};
 constexpr Shape kShapes32[] = {{1, 4, 1, 5.5, 0.096, 0.046, 0.73, 0.0338, 0.0216, 0.0, 0.0, 0.0125},
                                {1, 8, 1, 5.4, 0.106, 0.035, 1.95, 0.0496, 0.0266, 8.08, 0.0, 0.0125},
-                               {1, 16, 1, 6.5, 0.161, 0.026, 5.41, 0.183, 0.0209, 0.0, 0.0, 0.0125}};
+                               {1, 16, 1, 7.1, 0.160, 0.038, 5.41, 0.183, 0.0209, 0.0, 0.0, 0.0125}};
 
 // Estimated time of a step of a group with a fused shape (us), the mean of four
 // steps spread over the group's length (the set of active instances shrinks).
