@@ -520,6 +520,19 @@ bool build_instance(const bsde_problem &p, Instance &in)
     return true;
 }
 
+// The four cubic B-spline weights at the fraction ph of a cell, which sum to one
+// to the last bit of the second.  The expectations' weights have to sum to one: a
+// constant is a fixed point of the scheme, and what a sum is short of one is lost
+// in every step (4e-16 a step of z in the basket, 6e-14 over its solve).
+void spline_basis(double ph, double *b)
+{
+    const long double t = ph, u = 1.0L - t;
+    b[0] = (double)(u * u * u / 6.0L);
+    b[2] = (double)(2.0L / 3.0L - 0.5L * u * u * (1.0L + t));
+    b[3] = (double)(t * t * t / 6.0L);
+    b[1] = (double)(1.0L - b[0] - b[2] - b[3]);
+}
+
 // Tables of the two-dimensional B-spline form (sweep2b): node rows, nodes,
 // and the corrections of the columns next to the ends of axis 1 (see sweep2b:
 // node offset m errs by w b_3 at column -1 - m and by w b_0 at column -m, and
@@ -529,14 +542,7 @@ void build_instance2b(const bsde_problem &p, Instance2 &in, const double *a, con
                       const double *gy, const double *gz, int m1min, int m1max)
 {
     const int K = in.K, L = p.L;
-    const double inv_pi = 0.56418958354775628695 * 0.56418958354775628695;
-    auto basis = [](double ph, double *b) {
-        const double u = 1.0 - ph;
-        b[0] = u * u * u / 6.0;
-        b[1] = 2.0 / 3.0 - 0.5 * ph * ph * (2.0 - ph);
-        b[2] = 2.0 / 3.0 - 0.5 * u * u * (2.0 - u);
-        b[3] = ph * ph * ph / 6.0;
-    };
+    const long double inv_pi = 0.318309886183790671538L;
     in.rowsb.assign((size_t)K * L, bsde::Row2B{});
     in.nodesb.assign((size_t)K * L * L, bsde::Node2B{});
     in.nl = std::min(std::max(0, -m1min) + 1, in.n1);
@@ -557,7 +563,7 @@ void build_instance2b(const bsde_problem &p, Instance2 &in, const double *a, con
             r.m1lo = in.rows[ri].m1lo;
             r.m1hi = in.rows[ri].m1hi;
             in.spread = std::max(in.spread, r.m1hi - r.m1lo);
-            basis(s0 - std::floor(s0), r.b);
+            spline_basis(s0 - std::floor(s0), r.b);
             r.H = fy;
             r.Gu = fz * dW0;
             r.Gy = yw * dW0;
@@ -569,14 +575,14 @@ void build_instance2b(const bsde_problem &p, Instance2 &in, const double *a, con
                 const double dW1 = sq * a[l1];
                 const double s1 =
                     (p.drift[1] * j * in.dt + p.vol[1][0] * dW0 + p.vol[1][1] * dW1) / in.dx1;
-                const double wgt = w[l0] * w[l1] * inv_pi;
+                const long double wgt = w[l0] * (w[l1] * inv_pi);
                 double b[4];
-                basis(s1 - std::floor(s1), b);
+                spline_basis(s1 - std::floor(s1), b);
                 bsde::Node2B &nd = in.nodesb[k];
-                nd.w0 = wgt * b[0];
-                nd.w1 = wgt * b[1];
-                nd.w2 = wgt * b[2];
-                nd.w3 = wgt * b[3];
+                nd.w0 = (double)(wgt * b[0]);
+                nd.w2 = (double)(wgt * b[2]);
+                nd.w3 = (double)(wgt * b[3]);
+                nd.w1 = (double)(wgt - nd.w0 - nd.w2 - nd.w3);
                 nd.gu = fz * dW1;  // t carries the quadrature weight
                 nd.gy = yw * dW1;
                 const int m = in.m1[k];
@@ -591,13 +597,34 @@ void build_instance2b(const bsde_problem &p, Instance2 &in, const double *a, con
                 add(in.corr_l, in.nl, -m, nd.w0);
                 add(in.corr_r, in.nr, m, nd.w0);      // distance from the last column
                 add(in.corr_r, in.nr, m + 1, nd.w3);
-                const double c3 = p.p[3] * wgt;
+                const double c3 = (double)(p.p[3] * wgt);
                 in.lin_y += fy * c3;
                 in.lin_z1 += fz * dW0 * c3;
                 in.lin_z2 += fz * dW1 * c3;
             }
         }
     }
+    // E[y] of layer K_y and the E[z] terms: the rest to one goes to the layer's row
+    // of the largest weight
+    auto sum = [&](size_t ri) {
+        const bsde::Row2B &r = in.rowsb[ri];
+        long double s = 0.0L;
+        for (int l = 0; l < L; ++l) {
+            const bsde::Node2B &nd = in.nodesb[ri * L + l];
+            s += (long double)nd.w0 + nd.w1 + nd.w2 + nd.w3;
+        }
+        return s * ((long double)r.b[0] + r.b[1] + r.b[2] + r.b[3]);
+    };
+    long double sy = 0.0L, sz = 0.0L;
+    for (size_t ri = 0; ri < in.rowsb.size(); ++ri) {
+        const long double s = sum(ri);
+        sy += in.rowsb[ri].ey * s;
+        sz += in.rowsb[ri].C * s;
+    }
+    const int mid = (int)(std::max_element(w, w + L) - w);
+    const size_t ky = (size_t)(p.k_y - 1) * L + mid, kz = mid;
+    in.rowsb[ky].ey = (double)(in.rowsb[ky].ey + (1.0L - sy) / sum(ky));
+    if (!ydw) in.rowsb[kz].C = (double)(in.rowsb[kz].C + (1.0L - sz) / sum(kz));
 }
 
 // Two-dimensional node tables (eq (20)-(21) with tensor Gauss-Hermite nodes):
@@ -2205,6 +2232,8 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
         } else {
             std::vector<bsde::NodeRec> recs(kl);
             std::vector<bsde::NodeRecB> recsb(kl);
+            const bool linear = in.pb.driver == BSDE_DRIVER_LINEAR;
+            long double rest_y = 1.0L, rest_z = 1.0L;
             for (size_t k = 0; k < kl; ++k) {
                 const int l = (int)(k % in.pb.L), j = (int)(k / in.pb.L) + 1;
                 const double cy = (j == in.pb.k_y) ? in.cy[l] : 0.0;
@@ -2212,28 +2241,43 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
                                         in.cfz[k], in.cz[k], cy,      in.cyz[k]};
                 // cubic B-spline weights at the fraction; for the linear driver
                 // f = p0 y + p1 z + p3 folded into the weights
-                const double ph = in.phi[k], u = 1.0 - ph;
+                double b[4];
+                spline_basis(in.phi[k], b);
                 bsde::NodeRecB &rb = recsb[fused_position(in.K, in.pb.L, j, l)];
-                rb.b0 = u * u * u / 6.0;
-                rb.b1 = 2.0 / 3.0 - 0.5 * ph * ph * (2.0 - ph);
-                rb.b2 = 2.0 / 3.0 - 0.5 * u * u * (2.0 - u);
-                rb.b3 = ph * ph * ph / 6.0;
+                rb.b0 = b[0];
+                rb.b1 = b[1];
+                rb.b2 = b[2];
+                rb.b3 = b[3];
+                long double s = (long double)b[0] + b[1] + b[2] + b[3];
                 if (in.located) {  // located nodes: the increments in cells
                     rb.b0 = in.dw[k] / in.dx;
                     rb.b1 = j * in.dt / in.dx;
+                    s = 1.0L;
                 }
-                if (in.pb.driver == BSDE_DRIVER_LINEAR) {
+                if (linear) {
                     rb.w0 = in.cfy[k] * in.pb.p[0] + cy;
                     rb.w1 = in.cfy[k] * in.pb.p[1];
                     rb.w2 = in.cfz[k] * in.pb.p[0];
                     rb.w3 = in.cfz[k] * in.pb.p[1] + in.cz[k];
+                    rest_y += (long double)in.cfy[k] * in.pb.p[0];
+                    rest_z += (long double)in.cfz[k] * in.pb.p[1];
                 } else {
                     rb.w0 = in.cfy[k];
                     rb.w1 = in.cfz[k];
                     rb.w2 = in.cz[k];
                     rb.w3 = cy;
                 }
+                rest_y -= (linear ? rb.w0 : rb.w3) * s;
+                rest_z -= (linear ? rb.w3 : rb.w2) * s;
             }
+            // what E[y] of layer K_y and the E[z] terms lack to one (spline_basis) goes
+            // to the layer's node of the largest weight
+            const int mid = (int)(std::max_element(in.cy.begin(), in.cy.end()) - in.cy.begin());
+            bsde::NodeRecB &ry = recsb[fused_position(in.K, in.pb.L, in.pb.k_y, mid)];
+            bsde::NodeRecB &rz = recsb[fused_position(in.K, in.pb.L, 1, mid)];
+            double &wy = linear ? ry.w0 : ry.w3, &wz = linear ? rz.w3 : rz.w2;
+            wy = (double)(wy + rest_y);
+            if (in.pb.z_form == BSDE_ZFORM_EZ) wz = (double)(wz + rest_z);
             in.dtab.rec = static_cast<const bsde::NodeRec *>(put(recs.data(), kl * sizeof(bsde::NodeRec)));
             in.d_recb =
                 static_cast<const bsde::NodeRecB *>(put(recsb.data(), kl * sizeof(bsde::NodeRecB)));
@@ -2379,6 +2423,11 @@ bsde_status bsde_plan(const bsde_problem *pb, int batch, bsde_plan_t *out)
                 t.cz_ez[j] = ((j == 1 && !ydw ? 1.0 : 0.0) - fz) / gz[0];
                 t.cz_wy[j] = (fz * p0 + (j == 1 && ydw ? 1.0 / in.dt : 0.0)) / gz[0];
                 t.cz_wz[j] = fz * p1 / gz[0];
+            }
+            if (!ydw) {  // the E[z] terms sum to one
+                long double rest = 1.0L;
+                for (int j = 1; j <= in.K; ++j) rest -= t.cz_ez[j];
+                t.cz_ez[1] = (double)(t.cz_ez[1] + rest);
             }
         }
         for (size_t k = 0; k < in.cfy.size(); ++k) {

@@ -242,6 +242,12 @@ bool gaussian_spline_band(double m0, double rho, double h, double dx, GaussBand 
         out.j0[k0] = Q[0];
         out.j3[k0] = Q[3];
     }
+    // the expectation of a constant is that constant: the largest weight takes what
+    // the sum lacks to one
+    long double rest = 1.0L;
+    for (double v : out.ec) rest -= v;
+    double &top = *std::max_element(out.ec.begin(), out.ec.end());
+    top = (double)(top + rest);
     return true;
 }
 

@@ -462,6 +462,79 @@ int check_plan_copies()
     return fails;
 }
 
+// The weights that a plan stores sum to one: a constant is a fixed point of the
+// scheme, so every step would add what a sum is off.  Bound: half a unit in the last
+// place of the one weight that carries the rest (below 1; below 4 for the layer's
+// coefficient of the exact expectations).
+int check_weights()
+{
+    using ld = long double;
+    for (int K = 1; K <= 6; ++K) {
+        for (int L : {2, 7, 16, 33}) {
+            for (int driver : {(int)BSDE_DRIVER_LINEAR, (int)BSDE_DRIVER_CUBIC}) {
+                bsde_problem p = problem(4097, K, L, 10.0, 0.3);
+                p.driver = driver;
+                bsde_plan_t pl = nullptr;
+                EXPECT(bsde_plan(&p, 1, &pl) == BSDE_OK, "K %d L %d", K, L);
+                if (!pl) return fails;
+                const bool linear = driver == BSDE_DRIVER_LINEAR;
+                const Instance &in = pl->inst[0];
+                ld sy = 0, sz = 0, iy = 1, iz = 1;
+                for (int j = 1; j <= K; ++j)
+                    for (int l = 0; l < L; ++l) {
+                        const bsde::NodeRecB &r = in.d_recb[fused_position(K, L, j, l)];
+                        const ld b = (ld)r.b0 + r.b1 + r.b2 + r.b3;
+                        sy += b * (linear ? r.w0 : r.w3);
+                        sz += b * (linear ? r.w3 : r.w2);
+                        if (!linear) continue;  // with the driver's part of the weights
+                        iy += (ld)in.cfy[(j - 1) * L + l] * p.p[0];
+                        iz += (ld)in.cfz[(j - 1) * L + l] * p.p[1];
+                    }
+                EXPECT(std::fabs(sy - iy) <= 0x1p-54L && std::fabs(sz - iz) <= 0x1p-54L,
+                       "1-D K %d L %d driver %d: %Lg %Lg", K, L, driver, sy - iy, sz - iz);
+                bsde_plan_destroy(pl);
+            }
+            bsde_problem p = problem(65, K, L, 2.0, 0.3);
+            p.d = 2;
+            p.n_x[1] = 65;
+            p.x_max[1] = 64.0;
+            p.vol[1][0] = 0.4 * p.vol[0][0];
+            p.vol[1][1] = 0.9 * p.vol[0][0];
+            Instance2 in;
+            EXPECT(build_instance2(p, in) == BSDE_OK, "2-D");
+            ld sy = 0, sz = 0;
+            for (int r = 0; r < K * L; ++r) {
+                const bsde::Row2B &q = in.rowsb[r];
+                ld n = 0;
+                for (int l = 0; l < L; ++l) {
+                    const bsde::Node2B &d = in.nodesb[(size_t)r * L + l];
+                    n += (ld)d.w0 + d.w1 + d.w2 + d.w3;
+                }
+                n *= (ld)q.b[0] + q.b[1] + q.b[2] + q.b[3];
+                sy += q.ey * n;
+                sz += q.C * n;
+            }
+            EXPECT(std::fabs(sy - 1) <= 0x1p-53L && std::fabs(sz - 1) <= 0x1p-53L, "2-D K %d L %d: %Lg %Lg", K, L,
+                   sy - 1, sz - 1);
+        }
+        bsde_problem p = problem(4097, K, 16, 4.0, 0.3);
+        p.quad = BSDE_QUAD_EXACT;
+        bsde_plan_t pl = nullptr;
+        EXPECT(bsde_plan(&p, 1, &pl) == BSDE_OK, "exact K %d", K);
+        if (!pl) return fails;
+        ld sz = 0;
+        for (int j = 1; j <= K; ++j) {
+            ld m = 0;
+            for (double v : pl->inst[0].band[j].ec) m += v;
+            EXPECT(std::fabs(m - 1) <= 0x1p-54L, "exact K %d layer %d: %Lg", K, j, m - 1);
+            sz += pl->desc[0].a.toep.cz_ez[j];
+        }
+        EXPECT(std::fabs(sz - 1) <= 0x1p-52L, "exact K %d: %Lg", K, sz - 1);
+        bsde_plan_destroy(pl);
+    }
+    return fails;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -475,6 +548,7 @@ int main(int argc, char **argv)
     if (what == "located_shapes") return check_located_shapes() != 0;
     if (what == "exact_shapes") return check_exact_shapes() != 0;
     if (what == "plan_copies") return check_plan_copies() != 0;
+    if (what == "weights") return check_weights() != 0;
     std::printf("unknown check\n");
     return 2;
 }

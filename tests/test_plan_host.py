@@ -63,3 +63,7 @@ def test_exact_kernels_follow_the_measured_times(checks):
 
 def test_plans_copy_their_tables_by_group(checks):
     checks("plan_copies")
+
+
+def test_the_weights_of_a_plan_sum_to_one(checks):
+    checks("weights")
