@@ -127,6 +127,34 @@ __host__ __device__ constexpr PcrFilters pcr_filters()
     return r;
 }
 
+// Sum of n numbers and its own rounding (Knuth's two-sum), exact to about 1e-32.
+struct TapSum {
+    double hi, lo;
+};
+__host__ __device__ constexpr TapSum tap_sum(double start, const double *v, int n)
+{
+    TapSum s{start, 0.0};
+    for (int k = 0; k < n; ++k) {
+        const double z = s.hi + v[k], b = z - s.hi;
+        s.lo += (s.hi - (z - b)) + (v[k] - b);
+        s.hi = z;
+    }
+    return s;
+}
+// The filters of the B-spline coefficients: the first one's taps sum to zero, so
+// that a constant is its own coefficient (as rounded they sum to -6e-16, which adds
+// 1.7e-16 of the values in every step).  The FP32 form and the second derivatives
+// keep the taps as rounded.
+__host__ __device__ constexpr PcrFilters coef_filters()
+{
+    PcrFilters r = pcr_filters();
+    double all[17] = {};
+    for (int q = -8; q <= 8; ++q) all[q + 8] = r.fa[q < 0 ? -q : q];
+    const TapSum s = tap_sum(0.0, all, 17);
+    r.fa[3] -= 0.5 * (s.hi + s.lo);
+    return r;
+}
+
 // Exact Gaussian expectations as banded Toeplitz operators (toeplitz.hip):
 // per layer j the band of ev, em, wv, wm (nb[j] weights each, records
 // klo[j] .. klo[j] + nb[j] - 1 relative to the point) at w + off[j], and the

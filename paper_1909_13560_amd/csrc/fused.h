@@ -94,7 +94,7 @@ __device__ inline double2 layer_value(const Slot &g, int k)
 template <int NT, int kA>
 __device__ inline void fir_pass_a(int W, const double2 *D, double2 *A)
 {
-    constexpr PcrFilters F = pcr_filters();
+    constexpr PcrFilters F = coef_filters();
     for (int t = threadIdx.x; kA * t < W + 48; t += NT) {
         const int e = kA * t;
         double vy[kA], vz[kA];
@@ -126,7 +126,7 @@ __device__ inline void fir_pass_a(int W, const double2 *D, double2 *A)
 template <int NT, int kB, typename Out>
 __device__ inline void fir_pass_b(int W, const double2 *A, Out out)
 {
-    constexpr PcrFilters F = pcr_filters();
+    constexpr PcrFilters F = coef_filters();
     for (int t = threadIdx.x;; t += NT) {
         const int e = (t & 7) + 8 * kB * (t >> 3);  // outputs e, e + 8, ...
         if (e >= W) break;

@@ -130,6 +130,10 @@ __host__ __device__ constexpr SplineTaps spline_taps()
     }
     t.inv_b = 1.0 / bv;
     for (int k = 0; k < T + 2; ++k) t.e[k] = (k == H + 1 ? 1.0 : 0.0) - t.inv_b * t.d[k];
+    // they sum to one, so that a constant is its own coefficient (a tap beside the
+    // largest, whose unit in the last place is too coarse)
+    const TapSum s = tap_sum(-1.0, t.e, T + 2);
+    t.e[H + 2] -= s.hi + s.lo;
     return t;
 }
 

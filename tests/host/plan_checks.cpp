@@ -469,6 +469,13 @@ int check_plan_copies()
 int check_weights()
 {
     using ld = long double;
+    // the filters that make coefficients of values: a constant stays one
+    ld a = 0, e = 0;
+    const bsde::PcrFilters f = bsde::coef_filters();
+    const bsde::SplineTaps t = bsde::spline_taps();
+    for (int q = -8; q <= 8; ++q) a += f.fa[std::abs(q)];
+    for (double v : t.e) e += v;
+    EXPECT(std::fabs(a) <= 0x1p-55L && std::fabs(e - 1) <= 0x1p-55L, "filters: %Lg %Lg", a, e - 1);
     for (int K = 1; K <= 6; ++K) {
         for (int L : {2, 7, 16, 33}) {
             for (int driver : {(int)BSDE_DRIVER_LINEAR, (int)BSDE_DRIVER_CUBIC}) {
