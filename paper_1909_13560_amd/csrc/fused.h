@@ -438,7 +438,7 @@ __device__ inline void gather_nodes(const char *base, const double2 *edge, const
     auto node = [&](int k, const NodeRecB &c, const double2 (&r)[4], double ph, double s) {
         const double u = 1.0 - ph, p2 = ph * ph, u2 = u * u;
         const double b0 = u2 * u * (1.0 / 6.0), b3 = p2 * ph * (1.0 / 6.0);
-        const double b1 = fma(-0.5 * p2, 2.0 - ph, 2.0 / 3.0), b2 = fma(-0.5 * u2, 1.0 + ph, 2.0 / 3.0);
+        const double b2 = fma(-0.5 * u2, 1.0 + ph, 2.0 / 3.0), b1 = (1.0 - b2) - (b0 + b3);  // (they sum to one)
         double yh = fma(b3, r[3].x, fma(b0, r[0].x, fma(b2, r[2].x, b1 * r[1].x)));
         double zh = fma(b3, r[3].y, fma(b0, r[0].y, fma(b2, r[2].y, b1 * r[1].y)));
         if constexpr (ENDS) {
